@@ -1308,41 +1308,37 @@ ddgs_status ddgs_rads_prepare(ddgs_ctx *c, const ddgs_volume *vol, float *level,
     hipStream_t s = c->stream;
     RadsVol v{vol->nx, vol->ny, vol->nz, vol->spacing[0], vol->spacing[1], vol->spacing[2],
               vol->origin[0], vol->origin[1], vol->origin[2], vol->hu};
-    const int64_t nb = rads_minmax_blocks(n, c->num_cu), nb64 = rads_scan64_blocks(n);
+    const int64_t nb = rads_minmax_blocks(n, c->num_cu), nseg = rads_segments(n);
     float2 *part;
-    float *mm;
-    uint32_t *cnt, *off;
-    uint64_t *tot, *bsum, *cdf;
+    uint64_t *tot, *swt, *edge;
+    uint32_t *scnt;
+    uint16_t *w16;
     DDGS_TRY(ensure_t(c, "rads_part", (size_t)nb, &part));
-    DDGS_TRY(ensure_t(c, "rads_mm", 4, &mm));
-    DDGS_TRY(ensure_t(c, "rads_cnt", (size_t)n, &cnt));
-    DDGS_TRY(ensure_t(c, "rads_off", (size_t)n, &off));
-    DDGS_TRY(ensure_t(c, "rads_tot", 1, &tot));
-    DDGS_TRY(ensure_t(c, "rads_bsum", (size_t)nb64 + 1, &bsum));
-    DDGS_TRY(ensure_t(c, "rads_cdf", (size_t)n, &cdf));
-    SortWs ws;
-    DDGS_TRY(aux_sort_ws(c, n, &ws));
+    DDGS_TRY(ensure_t(c, "rads_tot", 4, &tot));  // crossings, weight; min, max, level
+    DDGS_TRY(ensure_t(c, "rads_scnt", (size_t)nseg + 1, &scnt));
+    DDGS_TRY(ensure_t(c, "rads_swt", (size_t)nseg + 1, &swt));
+    DDGS_TRY(ensure_t(c, "rads_w16", rads_weight_words(n), &w16));
+    DDGS_TRY(ensure_t(c, "rads_edge", rads_edge_words(n), &edge));
+    float *mm = (float *)(tot + 2);
     HIP_TRY(c, launch_rads_level(v, part, nb, mm, s));
-    HIP_TRY(c, launch_mc_count(v, mm, cnt, s));
-    HIP_TRY(c, launch_exclusive_scan(cnt, nullptr, off, n, ws, tot, s));
-    HIP_TRY(c, launch_rads_cdf(v, mm, bsum, cdf, s));
-    uint64_t m_h = 0, w_h = 0;
-    float mm_h[3] = {0.0f, 0.0f, 0.0f};
-    HIP_TRY(c, hipMemcpyAsync(&m_h, tot, 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipMemcpyAsync(&w_h, bsum + nb64, 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipMemcpyAsync(mm_h, mm, sizeof(mm_h), hipMemcpyDeviceToHost, s));
+    HIP_TRY(c, launch_rads_segments(v, mm, w16, edge, scnt, swt, tot, s));
+    struct {
+        uint64_t m, w;
+        float mm[4];
+    } h{};
+    HIP_TRY(c, hipMemcpyAsync(&h, tot, sizeof(h), hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
     float *pts;
-    DDGS_TRY(ensure_t(c, "rads_pts", (size_t)std::max<uint64_t>(3 * m_h, 1), &pts));
-    HIP_TRY(c, launch_mc_emit(v, mm, off, pts, (int64_t)m_h, s));
+    DDGS_TRY(ensure_t(c, "rads_pts", (size_t)std::max<uint64_t>(3 * h.m, 1), &pts));
+    HIP_TRY(c, launch_mc_emit(v, mm, edge, scnt, pts, (int64_t)h.m, s));
     v.hu = nullptr;  // not read after this call
     c->rads_vol = v;
-    c->rads_m = (int64_t)m_h;
-    c->rads_w = w_h;
+    c->rads_m = (int64_t)h.m;
+    c->rads_w = h.w;
     c->rads_ok = true;
-    *level = mm_h[2];
-    *n_crossings = (int64_t)m_h;
-    *total_weight = w_h;
+    *level = h.mm[2];
+    *n_crossings = (int64_t)h.m;
+    *total_weight = h.w;
     return DDGS_OK;
 }
 
@@ -1374,8 +1370,28 @@ ddgs_status ddgs_rads_sample(ddgs_ctx *c, int64_t n1, const uint32_t *mc_keys, i
         HIP_TRY(c, radix_sort_pairs(k0, v0, k1, v1, M, nullptr, 32, ws, &in_k1, s));
         HIP_TRY(c, launch_rads_gather(buf<float>(c, "rads_pts"), M, in_k1 ? v1 : v0, n1e, points, N, s));
     }
-    HIP_TRY(c, launch_rads_draws(c->rads_vol, buf<uint64_t>(c, "rads_cdf"), dw_draws, n2, points, N, n1e, s));
-    if (log_scale) HIP_TRY(c, launch_knn3(points, N, log_scale, s));
+    HIP_TRY(c, launch_rads_draws(c->rads_vol, buf<uint64_t>(c, "rads_swt"), buf<uint16_t>(c, "rads_w16"), dw_draws, n2,
+                                 points, N, n1e, s));
+    if (log_scale && !knn_uses_grid(N)) {
+        HIP_TRY(c, launch_knn_brute(points, N, log_scale, s));
+    } else if (log_scale) {
+        const KnnGrid g = knn_grid(c->rads_vol, N);
+        const int64_t G = g.cells();
+        uint32_t *cnt, *cur, *list;
+        uint64_t *tot;
+        float4 *sorted;
+        DDGS_TRY(ensure_t(c, "knn_cnt", (size_t)G + 1, &cnt));  // [G]: length of the list of open points
+        DDGS_TRY(ensure_t(c, "knn_cur", (size_t)G, &cur));
+        DDGS_TRY(ensure_t(c, "knn_list", (size_t)N, &list));
+        DDGS_TRY(ensure_t(c, "knn_sorted", (size_t)N, &sorted));
+        DDGS_TRY(ensure_t(c, "knn_tot", 1, &tot));
+        SortWs ws;
+        DDGS_TRY(aux_sort_ws(c, std::max(M, G), &ws));
+        HIP_TRY(c, launch_fill_u32(cnt, 0u, G + 1, s));
+        HIP_TRY(c, launch_knn_count(g, points, N, cnt, s));
+        HIP_TRY(c, launch_exclusive_scan(cnt, nullptr, cur, G, ws, tot, s));
+        HIP_TRY(c, launch_knn_grid(g, points, N, cur, sorted, list, cnt + G, log_scale, s));
+    }
     *n_iso = n1e + n2 / 2;
     return DDGS_OK;
 }

@@ -508,19 +508,39 @@ struct RadsVol {
     const float *hu;   // [nz][ny][nx]
 };
 int64_t rads_minmax_blocks(int64_t n, int num_cu);
-int64_t rads_scan64_blocks(int64_t n);
 // mm[0..2] = min, max, level (min + max) / 2
 hipError_t launch_rads_level(const RadsVol &v, float2 *part, int64_t nb, float *mm, hipStream_t s);
-hipError_t launch_mc_count(const RadsVol &v, const float *mm, uint32_t *cnt, hipStream_t s);
-hipError_t launch_mc_emit(const RadsVol &v, const float *mm, const uint32_t *off, float *pts, int64_t M, hipStream_t s);
-// cdf[i]: inclusive sum of the 16-bit weights; bsum [blocks + 1], bsum[blocks] = total
-hipError_t launch_rads_cdf(const RadsVol &v, const float *mm, uint64_t *bsum, uint64_t *cdf, hipStream_t s);
+// Segments of consecutive voxels: running crossing counts scnt and weight
+// sums swt before each ([rads_segments + 1], the last entry the total), the
+// voxels' 16-bit weights w16 [rads_weight_words] and crossing edges
+// [rads_edge_words], and tot = (crossings, weight)
+int64_t rads_segments(int64_t n);
+size_t rads_edge_words(int64_t n);
+size_t rads_weight_words(int64_t n);
+hipError_t launch_rads_segments(const RadsVol &v, const float *mm, uint16_t *w16, uint64_t *edge, uint32_t *scnt,
+                                uint64_t *swt, uint64_t *tot, hipStream_t s);
+hipError_t launch_mc_emit(const RadsVol &v, const float *mm, const uint64_t *edge, const uint32_t *scnt, float *pts,
+                          int64_t M, hipStream_t s);
 hipError_t launch_iota(uint32_t *p, int64_t n, hipStream_t s);
 hipError_t launch_rads_gather(const float *src, int64_t M, const uint32_t *idx, int64_t n1, float *out, int64_t N,
                               hipStream_t s);
-hipError_t launch_rads_draws(const RadsVol &v, const uint64_t *cdf, const uint64_t *draws, int64_t n2, float *out,
-                             int64_t N, int64_t first, hipStream_t s);
-hipError_t launch_knn3(const float *pts, int64_t N, float *ls, hipStream_t s);
+hipError_t launch_rads_draws(const RadsVol &v, const uint64_t *swt, const uint16_t *w16, const uint64_t *draws,
+                             int64_t n2, float *out, int64_t N, int64_t first, hipStream_t s);
+// Nearest-neighbour scales of pts [3][N] (log_scale ls [3][N]): by brute force,
+// or (knn_uses_grid) through a grid of cells: cnt [cells, cleared] receives
+// the cells' point counts; launch_knn_grid takes their exclusive prefix sums
+// in cur and places, queries and finishes (sorted [N], list [N], *n_list cleared).
+struct KnnGrid {
+    float x0[3], inv[3], h[3], slack[3];
+    int n[3];
+    int64_t cells() const { return (int64_t)n[0] * n[1] * n[2]; }
+};
+bool knn_uses_grid(int64_t N);
+KnnGrid knn_grid(const RadsVol &v, int64_t N);
+hipError_t launch_knn_brute(const float *pts, int64_t N, float *ls, hipStream_t s);
+hipError_t launch_knn_count(const KnnGrid &g, const float *pts, int64_t N, uint32_t *cnt, hipStream_t s);
+hipError_t launch_knn_grid(const KnnGrid &g, const float *pts, int64_t N, uint32_t *cur, float4 *sorted,
+                           uint32_t *list, uint32_t *n_list, float *ls, hipStream_t s);
 
 // loss.hip
 // SSIM output tile (pixels): one workgroup of kLossTileW x kLossTileH threads

@@ -14,8 +14,8 @@ namespace ddgs {
 namespace {
 
 constexpr int kRadsBlock = 256;
-constexpr int kScan64IPT = 16;
-constexpr int kScan64Tile = kRadsBlock * kScan64IPT;
+constexpr int kRadsSeg = 1024;  // voxels per segment (one wave)
+constexpr int kRadsRounds = kRadsSeg / kWave;
 
 __device__ __forceinline__ bool below(float v, float iso) { return v < iso; }
 
@@ -67,130 +67,213 @@ __global__ __launch_bounds__(kRadsBlock) void minmax_final_kernel(const float2 *
     }
 }
 
-// crossings of the +x, +y, +z edges leaving each voxel centre
-__global__ __launch_bounds__(kRadsBlock) void mc_count_kernel(RadsVol v, const float *mm, uint32_t *cnt)
-{
-    const int64_t nxy = (int64_t)v.nx * v.ny, n = nxy * v.nz;
-    const int64_t i = (int64_t)blockIdx.x * kRadsBlock + threadIdx.x;
-    if (i >= n) return;
-    const float iso = mm[2];
-    const int x = (int)(i % v.nx), y = (int)((i / v.nx) % v.ny), z = (int)(i / nxy);
-    const bool a = below(v.hu[i], iso);
-    uint32_t c = 0;
-    if (x + 1 < v.nx) c += a != below(v.hu[i + 1], iso) ? 1u : 0u;
-    if (y + 1 < v.ny) c += a != below(v.hu[i + v.nx], iso) ? 1u : 0u;
-    if (z + 1 < v.nz) c += a != below(v.hu[i + nxy], iso) ? 1u : 0u;
-    cnt[i] = c;
-}
-
-// the crossing points, [3][M], in edge order (voxel, then axis)
-__global__ __launch_bounds__(kRadsBlock) void mc_emit_kernel(RadsVol v, const float *mm, const uint32_t *off,
-                                                             float *pts, int64_t M)
-{
-    const int64_t nxy = (int64_t)v.nx * v.ny, n = nxy * v.nz;
-    const int64_t i = (int64_t)blockIdx.x * kRadsBlock + threadIdx.x;
-    if (i >= n) return;
-    const float iso = mm[2];
-    const int x = (int)(i % v.nx), y = (int)((i / v.nx) % v.ny), z = (int)(i / nxy);
-    const float a = v.hu[i];
-    const bool ba = below(a, iso);
-    uint32_t o = off[i];
-    const int64_t step[3] = {1, v.nx, nxy};
-    const bool inside[3] = {x + 1 < v.nx, y + 1 < v.ny, z + 1 < v.nz};
-    for (int ax = 0; ax < 3; ++ax) {
-        if (!inside[ax]) continue;
-        const float b = v.hu[i + step[ax]];
-        if (ba == below(b, iso)) continue;
-        const float t = (iso - a) / (b - a);
-        const float gx = (float)x + (ax == 0 ? t : 0.0f);
-        const float gy = (float)y + (ax == 1 ? t : 0.0f);
-        const float gz = (float)z + (ax == 2 ? t : 0.0f);
-        pts[o] = v.ox + gx * v.sx;
-        pts[M + o] = v.oy + gy * v.sy;
-        pts[2 * M + o] = v.oz + gz * v.sz;
-        ++o;
-    }
-}
-
 // 16-bit radiodensity weight: floor((hu - min) / (max - min) * 65535)
-__device__ __forceinline__ uint32_t weight_of(float hu, const float *mm)
+__device__ __forceinline__ uint32_t weight_of(float hu, float mn, float mx)
 {
-    const float mn = mm[0], mx = mm[1];
     if (!(mx > mn)) return 0u;
     return (uint32_t)floorf(((hu - mn) / (mx - mn)) * 65535.0f);
 }
 
-__device__ __forceinline__ uint64_t block_excl_scan_u64(uint64_t x, uint64_t *sh, uint64_t *total)
+// The volume is cut into segments of kRadsSeg consecutive voxels, one wave
+// each (64 voxels a round, lane = voxel, so every load is a coalesced row).
+// One pass finds a segment's level crossings (the +x, +y, +z edges leaving
+// its voxel centres; three bits per voxel are kept), sums its weights and
+// keeps them as 16-bit words; a scan of the segment totals places crossings
+// and draws, a second launch writes the points from the kept bits, and a draw
+// searches the segments and then the words of one.  The pass over the volume
+// is bound by HBM and the arithmetic of the weights: per voxel 4 B read, 2.4 B
+// written (the running sums per voxel this replaces moved 60 B: the eight
+// launches from the counts to the points of a 256^3 volume took 324 us, these
+// three take 90).
+struct RadsVoxel {
+    int x, y, z;
+};
+__device__ __forceinline__ RadsVoxel voxel_of(const RadsVol &v, uint32_t i)
 {
-    // inclusive scan over the block's threads in LDS (Hillis-Steele), then shift
-    sh[threadIdx.x] = x;
-    __syncthreads();
-    for (int o = 1; o < kRadsBlock; o <<= 1) {
-        const uint64_t add = threadIdx.x >= (unsigned)o ? sh[threadIdx.x - o] : 0ull;
+    const uint32_t row = i / (uint32_t)v.nx, z = row / (uint32_t)v.ny;
+    return RadsVoxel{(int)(i - row * (uint32_t)v.nx), (int)(row - z * (uint32_t)v.ny), (int)z};
+}
+// kWave voxels on (the divisions are done once per segment); step64 is
+// voxel_of(kWave)
+__device__ __forceinline__ void next_round(const RadsVol &v, const RadsVoxel &step64, RadsVoxel &c)
+{
+    c.x += step64.x;
+    const int cx = c.x >= v.nx ? 1 : 0;
+    c.x -= cx ? v.nx : 0;
+    c.y += step64.y + cx;
+    const int cy = c.y >= v.ny ? 1 : 0;
+    c.y -= cy ? v.ny : 0;
+    c.z += step64.z + cy;
+}
+// which of the three edges leaving voxel i (at c) cross the level, and their
+// far ends
+__device__ __forceinline__ uint32_t crossing_edges(const RadsVol &v, uint32_t i, const RadsVoxel &c, float a, float iso,
+                                                   float (&far_end)[3])
+{
+    const uint32_t step[3] = {1u, (uint32_t)v.nx, (uint32_t)v.nx * (uint32_t)v.ny};
+    const bool in[3] = {c.x + 1 < v.nx, c.y + 1 < v.ny, c.z + 1 < v.nz};
+    uint32_t m = 0u;
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        far_end[ax] = in[ax] ? v.hu[i + step[ax]] : a;
+        m |= below(far_end[ax], iso) != below(a, iso) ? 1u << ax : 0u;
+    }
+    return m;
+}
+
+// edge: per segment the crossing edges of its 16 rounds of 64 voxels, one word
+// per round and axis (word 3 round + axis, bit = lane)
+__global__ __launch_bounds__(kRadsBlock) void seg_count_kernel(RadsVol v, uint32_t n, const float *mm, int64_t nseg,
+                                                               uint16_t *w16, uint64_t *edge, uint32_t *scnt,
+                                                               uint64_t *swt)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t seg = (int64_t)blockIdx.x * (kRadsBlock / kWave) + threadIdx.x / kWave;
+    if (seg >= nseg) return;
+    const float mn = mm[0], mx = mm[1], iso = mm[2];
+    uint32_t cnt = 0, wt = 0;  // (at most 3 and 65535 per voxel)
+    uint64_t mine = 0;         // lane 3 round + axis keeps that word
+    RadsVoxel c = voxel_of(v, (uint32_t)(seg * kRadsSeg) + (uint32_t)lane);
+    const RadsVoxel step64 = voxel_of(v, kWave);
+#pragma unroll 4
+    for (int r = 0; r < kRadsRounds; ++r) {
+        const uint32_t i = (uint32_t)(seg * kRadsSeg) + (uint32_t)(r * kWave + lane);
+        uint32_t w = 0u, m = 0u;
+        if (i < n) {
+            const float a = v.hu[i];
+            w = weight_of(a, mn, mx);
+            float far_end[3];
+            m = crossing_edges(v, i, c, a, iso, far_end);
+        }
+        next_round(v, step64, c);
+        w16[i] = (uint16_t)w;  // (zero up to the segment's end)
+        wt += w;
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            const uint64_t b = __builtin_amdgcn_ballot_w64((m >> ax) & 1u);
+            cnt += (uint32_t)__popcll(b);
+            mine = lane == 3 * r + ax ? b : mine;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) wt += (uint32_t)__shfl_xor((int)wt, o, kWave);
+    if (lane < 3 * kRadsRounds) edge[seg * (3 * kRadsRounds) + lane] = mine;
+    if (lane == 0) {
+        scnt[seg] = cnt;
+        swt[seg] = wt;
+    }
+}
+
+// Exclusive scans of the segment totals in place, by one block; entry nseg of
+// each receives the total, and tot both (crossings, weight).  A wave takes 16
+// rounds of 64 consecutive segments (coalesced loads, all in flight together;
+// one thread per 16 segments instead took 46 us for 16384 of them).
+constexpr int kSegScanBlock = 1024;
+__global__ __launch_bounds__(kSegScanBlock) void seg_scan_kernel(uint32_t *scnt, uint64_t *swt, int64_t nseg,
+                                                                 uint64_t *tot)
+{
+    constexpr int NW = kSegScanBlock / kWave, PER = 16;
+    // (64 segments weigh at most 64 x 1024 x 65535 < 2^32)
+    static_assert((uint64_t)kWave * kRadsSeg * 65535u <= 0xFFFFFFFFull, "a round's weight fits 32 bits");
+    __shared__ uint64_t lc[NW], lw[NW];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    uint64_t cc = 0, cw = 0;  // totals of the passes before
+    for (int64_t b0 = 0; b0 < nseg; b0 += kSegScanBlock * PER) {
+        const int64_t b = b0 + (int64_t)w * (kWave * PER) + lane;
+        uint32_t xc[PER], xw[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int64_t j = b + q * kWave;
+            xc[q] = j < nseg ? scnt[j] : 0u;
+            xw[q] = j < nseg ? (uint32_t)swt[j] : 0u;
+        }
+        // inclusive scan of every round, then the rounds' totals in order
+        uint32_t ic[PER], iw[PER];
+        uint64_t sc = 0, sw = 0;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            ic[q] = wave_incl_scan(xc[q]);
+            iw[q] = wave_incl_scan(xw[q]);
+            sc += (uint32_t)__builtin_amdgcn_readlane((int)ic[q], kWave - 1);
+            sw += (uint32_t)__builtin_amdgcn_readlane((int)iw[q], kWave - 1);
+        }
+        if (lane == 0) {
+            lc[w] = sc;
+            lw[w] = sw;
+        }
         __syncthreads();
-        sh[threadIdx.x] += add;
+        uint64_t pc = cc, pw = cw;
+        for (int q = 0; q < NW; ++q) {
+            if (q < w) {
+                pc += lc[q];
+                pw += lw[q];
+            }
+            cc += lc[q];
+            cw += lw[q];
+        }
         __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int64_t j = b + q * kWave;
+            if (j < nseg) {
+                scnt[j] = (uint32_t)pc + ic[q] - xc[q];
+                swt[j] = pw + (iw[q] - xw[q]);
+            }
+            pc += (uint32_t)__builtin_amdgcn_readlane((int)ic[q], kWave - 1);
+            pw += (uint32_t)__builtin_amdgcn_readlane((int)iw[q], kWave - 1);
+        }
     }
-    const uint64_t incl = sh[threadIdx.x];
-    *total = sh[kRadsBlock - 1];
-    __syncthreads();
-    return incl - x;
+    if (threadIdx.x == 0) {
+        scnt[nseg] = (uint32_t)cc;
+        swt[nseg] = cw;
+        tot[0] = cc;
+        tot[1] = cw;
+    }
 }
 
-__global__ __launch_bounds__(kRadsBlock) void scan64_reduce_kernel(const float *hu, int64_t n, const float *mm,
-                                                                   uint64_t *bsum)
+// the crossing points, [3][M], in edge order (voxel, then axis): the volume is
+// read only where the kept words have a bit
+__global__ __launch_bounds__(kRadsBlock) void mc_emit_kernel(RadsVol v, const float *mm, int64_t nseg,
+                                                             const uint64_t *edge, const uint32_t *scnt, float *pts,
+                                                             int64_t M)
 {
-    __shared__ uint64_t sh[kRadsBlock];
-    const int64_t base = (int64_t)blockIdx.x * kScan64Tile;
-    uint64_t s = 0;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t seg = (int64_t)blockIdx.x * (kRadsBlock / kWave) + threadIdx.x / kWave;
+    if (seg >= nseg) return;
+    uint32_t base = scnt[seg];
+    if (base == scnt[seg + 1]) return;
+    const float iso = mm[2];
+    const uint64_t mine = lane < 3 * kRadsRounds ? edge[seg * (3 * kRadsRounds) + lane] : 0ull;
+    const uint32_t step[3] = {1u, (uint32_t)v.nx, (uint32_t)v.nx * (uint32_t)v.ny};
+    uint64_t left = __builtin_amdgcn_ballot_w64(mine != 0ull);
+    while (left) {
+        const int r = __builtin_ctzll(left) / 3;
+        left &= ~(7ull << (3 * r));
+        uint32_t m = 0u, o = base;
 #pragma unroll
-    for (int r = 0; r < kScan64IPT; ++r) {
-        const int64_t i = base + (int64_t)r * kRadsBlock + threadIdx.x;
-        if (i < n) s += weight_of(hu[i], mm);
-    }
-    uint64_t tot;
-    (void)block_excl_scan_u64(s, sh, &tot);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
-}
-
-// exclusive scan of the block sums in place (one block); bsum[nb] = total
-__global__ __launch_bounds__(kRadsBlock) void scan64_top_kernel(uint64_t *bsum, int64_t nb)
-{
-    __shared__ uint64_t sh[kRadsBlock];
-    uint64_t carry = 0;
-    for (int64_t b0 = 0; b0 < nb; b0 += kRadsBlock) {
-        const int64_t b = b0 + threadIdx.x;
-        const uint64_t x = b < nb ? bsum[b] : 0ull;
-        uint64_t tot;
-        const uint64_t ex = block_excl_scan_u64(x, sh, &tot);
-        if (b < nb) bsum[b] = carry + ex;
-        carry += tot;
-    }
-    if (threadIdx.x == 0) bsum[nb] = carry;
-}
-
-// cdf[i] = inclusive running weight sum; each thread owns kScan64IPT
-// consecutive voxels of its block's tile
-__global__ __launch_bounds__(kRadsBlock) void scan64_apply_kernel(const float *hu, int64_t n, const float *mm,
-                                                                  const uint64_t *bsum, uint64_t *cdf)
-{
-    __shared__ uint64_t sh[kRadsBlock];
-    const int64_t base = (int64_t)blockIdx.x * kScan64Tile + (int64_t)threadIdx.x * kScan64IPT;
-    uint32_t w[kScan64IPT];
-    uint64_t s = 0;
+        for (int ax = 0; ax < 3; ++ax) {
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, 3 * r + ax);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), 3 * r + ax);
+            m |= (((lane < 32 ? lo : hi) >> (lane & 31)) & 1u) << ax;
+            o += __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+            base += (uint32_t)(__popc(lo) + __popc(hi));
+        }
+        if (m == 0u) continue;  // (no wave-wide step below)
+        const uint32_t i = (uint32_t)(seg * kRadsSeg) + (uint32_t)(r * kWave + lane);
+        const RadsVoxel c = voxel_of(v, i);
+        const float a = v.hu[i];
 #pragma unroll
-    for (int r = 0; r < kScan64IPT; ++r) {
-        const int64_t i = base + r;
-        w[r] = i < n ? weight_of(hu[i], mm) : 0u;
-        s += w[r];
-    }
-    uint64_t tot;
-    uint64_t run = bsum[blockIdx.x] + block_excl_scan_u64(s, sh, &tot);
-#pragma unroll
-    for (int r = 0; r < kScan64IPT; ++r) {
-        const int64_t i = base + r;
-        run += w[r];
-        if (i < n) cdf[i] = run;
+        for (int ax = 0; ax < 3; ++ax) {
+            if (!((m >> ax) & 1u)) continue;
+            const float t = (iso - a) / (v.hu[i + step[ax]] - a);
+            const float gx = (float)c.x + (ax == 0 ? t : 0.0f);
+            const float gy = (float)c.y + (ax == 1 ? t : 0.0f);
+            const float gz = (float)c.z + (ax == 2 ? t : 0.0f);
+            pts[o] = v.ox + gx * v.sx;
+            pts[M + o] = v.oy + gy * v.sy;
+            pts[2 * M + o] = v.oz + gz * v.sz;
+            ++o;
+        }
     }
 }
 
@@ -212,76 +295,273 @@ __global__ __launch_bounds__(kRadsBlock) void gather_kernel(const float *src, in
     out[2 * N + j] = src[2 * M + i];
 }
 
-// draw j: the first voxel whose inclusive weight sum exceeds draws[j]
-__global__ __launch_bounds__(kRadsBlock) void draw_kernel(RadsVol v, const uint64_t *cdf, const uint64_t *draws,
-                                                          int64_t n2, float *out, int64_t N, int64_t first)
+// draw j: the first voxel whose inclusive weight sum exceeds draws[j] (the
+// last voxel if none does), one wave per draw: a 64-way search of the
+// segments' running sums, then the segment's words, 16 consecutive ones per
+// lane.
+__global__ __launch_bounds__(kRadsBlock) void draw_kernel(RadsVol v, uint32_t n, const uint64_t *swt, int64_t nseg,
+                                                          const uint16_t *w16, const uint64_t *draws, int64_t n2,
+                                                          float *out, int64_t N, int64_t first)
 {
-    const int64_t j = (int64_t)blockIdx.x * kRadsBlock + threadIdx.x;
+    constexpr int PER = kRadsSeg / kWave;
+    static_assert(PER == 16, "two 16-byte loads per lane");
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t j = (int64_t)blockIdx.x * (kRadsBlock / kWave) + threadIdx.x / kWave;
     if (j >= n2) return;
     const uint64_t r = draws[j];
-    const int64_t n = (int64_t)v.nx * v.ny * v.nz;
-    int64_t lo = 0, hi = n - 1;  // answer in [lo, hi]; the last voxel if r is past the total
-    while (lo < hi) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        if (cdf[mid] > r) hi = mid;
-        else lo = mid + 1;
+    uint32_t pick = n - 1u;
+    if (r < swt[nseg]) {
+        // the segment: the last one whose running sum before it is at most r
+        int64_t lo = 0, len = nseg;
+        while (len > 1) {
+            const int64_t step = (len + kWave - 1) / kWave, p = (int64_t)lane * step;
+            const uint64_t b = __builtin_amdgcn_ballot_w64(p < len && swt[lo + p] <= r);
+            const int k = 63 - __builtin_clzll(b | 1ull);
+            lo += k * step;
+            len = len - k * step < step ? len - k * step : step;
+        }
+        const uint32_t rel = (uint32_t)(r - swt[lo]);
+        const uint4 *q = reinterpret_cast<const uint4 *>(w16 + lo * kRadsSeg + lane * PER);
+        const uint4 q0 = q[0], q1 = q[1];
+        const uint32_t word[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+        uint32_t sum = 0u;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) sum += (word[t] & 0xFFFFu) + (word[t] >> 16);
+        const uint32_t incl = wave_incl_scan(sum);
+        // the first lane whose words pass rel, then its first such word
+        const uint64_t over = __builtin_amdgcn_ballot_w64(incl > rel);
+        const int who = __builtin_ctzll(over);
+        uint32_t run = incl - sum, at = 0u;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            run += word[t] & 0xFFFFu;
+            at += run <= rel ? 1u : 0u;
+            run += word[t] >> 16;
+            at += run <= rel ? 1u : 0u;
+        }
+        pick = (uint32_t)(lo * kRadsSeg) + (uint32_t)(who * PER) + (uint32_t)__shfl((int)at, who, kWave);
     }
-    const int64_t nxy = (int64_t)v.nx * v.ny;
-    const int x = (int)(lo % v.nx), y = (int)((lo / v.nx) % v.ny), z = (int)(lo / nxy);
-    out[first + j] = v.ox + (float)x * v.sx;
-    out[N + first + j] = v.oy + (float)y * v.sy;
-    out[2 * N + first + j] = v.oz + (float)z * v.sz;
+    if (lane != 0) return;
+    const RadsVoxel c = voxel_of(v, pick);
+    out[first + j] = v.ox + (float)c.x * v.sx;
+    out[N + first + j] = v.oy + (float)c.y * v.sy;
+    out[2 * N + first + j] = v.oz + (float)c.z * v.sz;
 }
 
-// log sqrt(mean squared distance to the 3 nearest other points), by brute
-// force over LDS tiles of the point set
-constexpr int kKnnBlock = 128;
-__global__ __launch_bounds__(kKnnBlock) void knn3_kernel(const float *pts, int64_t N, float *ls)
-{
-    __shared__ float tx[kKnnBlock], ty[kKnnBlock], tz[kKnnBlock];
-    const int64_t i = (int64_t)blockIdx.x * kKnnBlock + threadIdx.x;
-    const bool valid = i < N;
-    const float px = valid ? pts[i] : 0.0f, py = valid ? pts[N + i] : 0.0f, pz = valid ? pts[2 * N + i] : 0.0f;
-    float d0 = INFINITY, d1 = INFINITY, d2 = INFINITY;
-    for (int64_t b = 0; b < N; b += kKnnBlock) {
-        const int64_t j = b + threadIdx.x;
-        if (j < N) {
-            tx[threadIdx.x] = pts[j];
-            ty[threadIdx.x] = pts[N + j];
-            tz[threadIdx.x] = pts[2 * N + j];
+// ---------------------------------------------------- nearest neighbours
+// log sqrt(mean squared distance to the 3 nearest other points), exact.  The
+// three smallest of the float32 squared distances do not depend on the order
+// in which the other points are visited, so the paths below give the same
+// result bit for bit.
+//
+// Up to kKnnBrute points one workgroup per point tests them all.  Beyond, the
+// points are binned in a uniform grid over the volume (about four cells per
+// point, stored cell by cell), and sixteen lanes per point walk the rows of cells
+// around its own, ring by ring, until no cell left can hold a nearer point;
+// a point that three rings do not settle goes to a list that workgroups of
+// the brute-force kernel take afterwards, so points far from all others cost
+// no long serial walk.  What bounds a query is the latency of its row starts
+// and points (about 30 of them), against N of them in a serial loop per lane
+// before: 25000 points of a 256^3 volume 1785 -> 50 us (all seven launches).
+// kKnnBrute: a workgroup per point costs N^2 / 256 lane loads; at 4096 points
+// that is 65k of them, 256 waves deep on the card, and about the 25 us of the
+// grid's small launches.
+constexpr int kKnnBrute = 4096;
+constexpr int kKnnRings = 3;
+constexpr int kKnnLanes = 16;
+constexpr int kKnnFarBlocks = 1024;
+constexpr int64_t kKnnMaxCells = (int64_t)1 << 22;
+
+struct Near3 {
+    float d0, d1, d2;  // ascending
+    __device__ __forceinline__ void insert(float d)
+    {
+        // (NaN distances are never nearer)
+        if (d < d2) {
+            const bool l1 = d < d1, l0 = d < d0;
+            d2 = l1 ? d1 : d;
+            d1 = l0 ? d0 : (l1 ? d : d1);
+            d0 = l0 ? d : d0;
         }
-        __syncthreads();
-        const int cnt = N - b < kKnnBlock ? (int)(N - b) : kKnnBlock;
-        for (int q = 0; q < cnt; ++q) {
-            const float dx = tx[q] - px, dy = ty[q] - py, dz = tz[q] - pz;
-            float d = dx * dx + dy * dy + dz * dz;
-            if (b + q == i) d = INFINITY;
-            if (d < d2) {
-                if (d < d1) {
-                    d2 = d1;
-                    if (d < d0) {
-                        d1 = d0;
-                        d0 = d;
-                    } else {
-                        d1 = d;
-                    }
-                } else {
-                    d2 = d;
-                }
-            }
-        }
-        __syncthreads();
     }
-    if (!valid) return;
+};
+
+__device__ __forceinline__ float dist2(float qx, float qy, float qz, float px, float py, float pz)
+{
+    const float dx = qx - px, dy = qy - py, dz = qz - pz;
+    return dx * dx + dy * dy + dz * dz;
+}
+
+__device__ __forceinline__ void store_scale(const Near3 &b, int64_t N, int64_t i, float *ls)
+{
     const int64_t kk = N - 1 < 3 ? N - 1 : 3;
     float mean = 0.0f;
-    if (kk == 3) mean = (d0 + d1 + d2) / 3.0f;
-    else if (kk == 2) mean = (d0 + d1) * 0.5f;
-    else if (kk == 1) mean = d0;
+    if (kk == 3) mean = (b.d0 + b.d1 + b.d2) / 3.0f;
+    else if (kk == 2) mean = (b.d0 + b.d1) * 0.5f;
+    else if (kk == 1) mean = b.d0;
     const float l = 0.5f * logf(fmaxf(mean, 1e-7f));
     ls[i] = l;
     ls[N + i] = l;
     ls[2 * N + i] = l;
+}
+
+// One workgroup per point at a time: points 0 .. N - 1, or the list[0 ..
+// *n_list) of them.
+__global__ __launch_bounds__(kRadsBlock) void knn_brute_kernel(const float *pts, int64_t N, const uint32_t *list,
+                                                               const uint32_t *n_list, float *ls)
+{
+    __shared__ float sd[kRadsBlock / kWave][3];
+    const int64_t cnt = list ? (int64_t)*n_list : N;
+    for (int64_t q = blockIdx.x; q < cnt; q += gridDim.x) {
+        const int64_t i = list ? (int64_t)list[q] : q;
+        const float px = pts[i], py = pts[N + i], pz = pts[2 * N + i];
+        Near3 b{INFINITY, INFINITY, INFINITY};
+        for (int64_t j = threadIdx.x; j < N; j += kRadsBlock) {
+            const float d = dist2(pts[j], pts[N + j], pts[2 * N + j], px, py, pz);
+            if (j != i) b.insert(d);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const float e0 = __shfl_xor(b.d0, o, kWave), e1 = __shfl_xor(b.d1, o, kWave),
+                        e2 = __shfl_xor(b.d2, o, kWave);
+            b.insert(e0);
+            b.insert(e1);
+            b.insert(e2);
+        }
+        if ((threadIdx.x & (kWave - 1)) == 0) {
+            const int w = threadIdx.x / kWave;
+            sd[w][0] = b.d0;
+            sd[w][1] = b.d1;
+            sd[w][2] = b.d2;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kRadsBlock / kWave; ++w)
+                for (int t = 0; t < 3; ++t) b.insert(sd[w][t]);
+            store_scale(b, N, i, ls);
+        }
+        __syncthreads();
+    }
+}
+
+// Cell of a coordinate along axis a, clamped to the grid (NaN: cell 0).
+__device__ __forceinline__ int grid_cell(const KnnGrid &g, int a, float p)
+{
+    const float t = (p - g.x0[a]) * g.inv[a];
+    return (int)fminf(fmaxf(t, 0.0f), (float)(g.n[a] - 1));
+}
+__device__ __forceinline__ uint32_t grid_cell3(const KnnGrid &g, float x, float y, float z)
+{
+    return (uint32_t)((grid_cell(g, 2, z) * g.n[1] + grid_cell(g, 1, y)) * g.n[0] + grid_cell(g, 0, x));
+}
+
+__global__ __launch_bounds__(kRadsBlock) void knn_count_kernel(KnnGrid g, const float *pts, int64_t N, uint32_t *cnt)
+{
+    const int64_t i = (int64_t)blockIdx.x * kRadsBlock + threadIdx.x;
+    if (i >= N) return;
+    const uint32_t c = grid_cell3(g, pts[i], pts[N + i], pts[2 * N + i]);
+    // lanes that share the first lane's cell (points drawn many times from
+    // one voxel) add their number at once: increments of one address serialise
+    const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
+    const uint64_t same = __builtin_amdgcn_ballot_w64(c == c0);
+    if (c != c0) atomicAdd(&cnt[c], 1u);
+    else if (__builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u)) == 0u)
+        atomicAdd(&cnt[c], (uint32_t)__popcll(same));
+}
+
+// The points cell by cell (cur: the cells' starts, advanced; the order inside
+// a cell does not matter), with their index.
+__global__ __launch_bounds__(kRadsBlock) void knn_place_kernel(KnnGrid g, const float *pts, int64_t N, uint32_t *cur,
+                                                               float4 *out)
+{
+    const int64_t i = (int64_t)blockIdx.x * kRadsBlock + threadIdx.x;
+    if (i >= N) return;
+    const float x = pts[i], y = pts[N + i], z = pts[2 * N + i];
+    const uint32_t c = grid_cell3(g, x, y, z);
+    const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
+    const uint64_t same = __builtin_amdgcn_ballot_w64(c == c0);
+    uint32_t p;
+    if (c != c0) {
+        p = atomicAdd(&cur[c], 1u);
+    } else {
+        const uint32_t rank =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+        uint32_t base = 0;
+        if (rank == 0u) base = atomicAdd(&cur[c], (uint32_t)__popcll(same));
+        p = (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + rank;
+    }
+    out[p] = make_float4(x, y, z, __uint_as_float((uint32_t)i));
+}
+
+// (cur holds the cells' ends by now: cell c's points are [end(c - 1), end(c)))
+// kKnnLanes lanes per point share the rows of a ring, then merge what they
+// found: a lane per point walked its ~9 rows one after the other (109 us at
+// 25000 points, against 27 us).
+__global__ __launch_bounds__(kRadsBlock) void knn_query_kernel(KnnGrid g, const float4 *sp, int64_t N,
+                                                               const uint32_t *end, float *ls, uint32_t *list,
+                                                               uint32_t *n_list)
+{
+    const int64_t t = ((int64_t)blockIdx.x * kRadsBlock + threadIdx.x) / kKnnLanes;
+    const int sub = threadIdx.x % kKnnLanes;
+    if (t >= N) return;  // (whole groups)
+    const float4 p = sp[t];
+    const int cx = grid_cell(g, 0, p.x), cy = grid_cell(g, 1, p.y), cz = grid_cell(g, 2, p.z);
+    Near3 b{INFINITY, INFINITY, INFINITY};
+    auto run = [&](int z, int y, int xa, int xb) {
+        xa = max(xa, 0);
+        xb = min(xb, g.n[0] - 1);
+        if (xa > xb) return;
+        const int row = (z * g.n[1] + y) * g.n[0];
+        const uint32_t e = end[row + xb];
+        for (uint32_t q = row + xa > 0 ? end[row + xa - 1] : 0u; q < e; ++q) {
+            const float4 o = sp[q];
+            const float d = dist2(o.x, o.y, o.z, p.x, p.y, p.z);
+            if ((int64_t)q != t) b.insert(d);
+            if (b.d2 == 0.0f) return;  // three points at this place
+        }
+    };
+    bool done = false;
+    for (int r = 1; r <= kKnnRings && !done; ++r) {
+        const int side = 2 * r + 1;
+        for (int k = sub; k < side * side; k += kKnnLanes) {
+            const int dz = k / side - r, dy = k % side - r, z = cz + dz, y = cy + dy;
+            if (z < 0 || z >= g.n[2] || y < 0 || y >= g.n[1]) continue;
+            if (r == 1 || abs(dz) == r || abs(dy) == r) {
+                run(z, y, cx - r, cx + r);
+            } else {
+                if (cx - r >= 0) run(z, y, cx - r, cx - r);
+                if (cx + r < g.n[0]) run(z, y, cx + r, cx + r);
+            }
+        }
+        // the group's three nearest so far (the lanes' finds are disjoint,
+        // so only lane 0 keeps the merged ones for the next ring)
+        Near3 m = b;
+#pragma unroll
+        for (int o = kKnnLanes / 2; o > 0; o >>= 1) {
+            const float e0 = __shfl_xor(m.d0, o, kWave), e1 = __shfl_xor(m.d1, o, kWave),
+                        e2 = __shfl_xor(m.d2, o, kWave);
+            m.insert(e0);
+            m.insert(e1);
+            m.insert(e2);
+        }
+        b = sub == 0 ? m : Near3{INFINITY, INFINITY, INFINITY};
+        // every point left lies beyond a face of the cells walked that is
+        // not the grid's own; slack covers the rounding of the cell index
+        const float pc[3] = {p.x, p.y, p.z};
+        const int cc[3] = {cx, cy, cz};
+        float lb = INFINITY;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            if (cc[a] - r > 0) lb = fminf(lb, pc[a] - (g.x0[a] + (float)(cc[a] - r) * g.h[a]) - g.slack[a]);
+            if (cc[a] + r < g.n[a] - 1)
+                lb = fminf(lb, (g.x0[a] + (float)(cc[a] + r + 1) * g.h[a]) - pc[a] - g.slack[a]);
+        }
+        done = lb == INFINITY || (lb > 0.0f && m.d2 <= lb * lb * 0.9999f) || m.d2 == 0.0f;
+    }
+    if (sub != 0) return;
+    const uint32_t i = __float_as_uint(p.w);
+    if (done) store_scale(b, N, (int64_t)i, ls);
+    else list[atomicAdd(n_list, 1u)] = i;
 }
 
 int64_t blocks(int64_t n, int per) { return (n + per - 1) / per; }
@@ -289,7 +569,9 @@ int64_t blocks(int64_t n, int per) { return (n + per - 1) / per; }
 }  // namespace
 
 int64_t rads_minmax_blocks(int64_t n, int num_cu) { return std::max<int64_t>(1, std::min<int64_t>(blocks(n, kRadsBlock), (int64_t)num_cu * 8)); }
-int64_t rads_scan64_blocks(int64_t n) { return std::max<int64_t>(1, blocks(n, kScan64Tile)); }
+size_t rads_edge_words(int64_t n) { return (size_t)rads_segments(n) * 3 * kRadsRounds; }
+int64_t rads_segments(int64_t n) { return blocks(n, kRadsSeg); }
+size_t rads_weight_words(int64_t n) { return (size_t)rads_segments(n) * kRadsSeg; }
 
 hipError_t launch_rads_level(const RadsVol &v, float2 *part, int64_t nb, float *mm, hipStream_t s)
 {
@@ -299,28 +581,22 @@ hipError_t launch_rads_level(const RadsVol &v, float2 *part, int64_t nb, float *
     return hipGetLastError();
 }
 
-hipError_t launch_mc_count(const RadsVol &v, const float *mm, uint32_t *cnt, hipStream_t s)
+hipError_t launch_rads_segments(const RadsVol &v, const float *mm, uint16_t *w16, uint64_t *edge, uint32_t *scnt,
+                                uint64_t *swt, uint64_t *tot, hipStream_t s)
 {
-    const int64_t n = (int64_t)v.nx * v.ny * v.nz;
-    mc_count_kernel<<<(unsigned)blocks(n, kRadsBlock), kRadsBlock, 0, s>>>(v, mm, cnt);
+    const int64_t n = (int64_t)v.nx * v.ny * v.nz, nseg = rads_segments(n);
+    seg_count_kernel<<<(unsigned)blocks(nseg, kRadsBlock / kWave), kRadsBlock, 0, s>>>(v, (uint32_t)n, mm, nseg, w16,
+                                                                                        edge, scnt, swt);
+    seg_scan_kernel<<<1, kSegScanBlock, 0, s>>>(scnt, swt, nseg, tot);
     return hipGetLastError();
 }
 
-hipError_t launch_mc_emit(const RadsVol &v, const float *mm, const uint32_t *off, float *pts, int64_t M, hipStream_t s)
+hipError_t launch_mc_emit(const RadsVol &v, const float *mm, const uint64_t *edge, const uint32_t *scnt, float *pts,
+                          int64_t M, hipStream_t s)
 {
-    const int64_t n = (int64_t)v.nx * v.ny * v.nz;
+    const int64_t n = (int64_t)v.nx * v.ny * v.nz, nseg = rads_segments(n);
     if (M == 0) return hipSuccess;
-    mc_emit_kernel<<<(unsigned)blocks(n, kRadsBlock), kRadsBlock, 0, s>>>(v, mm, off, pts, M);
-    return hipGetLastError();
-}
-
-hipError_t launch_rads_cdf(const RadsVol &v, const float *mm, uint64_t *bsum, uint64_t *cdf, hipStream_t s)
-{
-    const int64_t n = (int64_t)v.nx * v.ny * v.nz;
-    const int64_t nb = rads_scan64_blocks(n);
-    scan64_reduce_kernel<<<(unsigned)nb, kRadsBlock, 0, s>>>(v.hu, n, mm, bsum);
-    scan64_top_kernel<<<1, kRadsBlock, 0, s>>>(bsum, nb);
-    scan64_apply_kernel<<<(unsigned)nb, kRadsBlock, 0, s>>>(v.hu, n, mm, bsum, cdf);
+    mc_emit_kernel<<<(unsigned)blocks(nseg, kRadsBlock / kWave), kRadsBlock, 0, s>>>(v, mm, nseg, edge, scnt, pts, M);
     return hipGetLastError();
 }
 
@@ -339,18 +615,76 @@ hipError_t launch_rads_gather(const float *src, int64_t M, const uint32_t *idx, 
     return hipGetLastError();
 }
 
-hipError_t launch_rads_draws(const RadsVol &v, const uint64_t *cdf, const uint64_t *draws, int64_t n2, float *out,
-                             int64_t N, int64_t first, hipStream_t s)
+hipError_t launch_rads_draws(const RadsVol &v, const uint64_t *swt, const uint16_t *w16, const uint64_t *draws,
+                             int64_t n2, float *out, int64_t N, int64_t first, hipStream_t s)
 {
     if (n2 == 0) return hipSuccess;
-    draw_kernel<<<(unsigned)blocks(n2, kRadsBlock), kRadsBlock, 0, s>>>(v, cdf, draws, n2, out, N, first);
+    const int64_t n = (int64_t)v.nx * v.ny * v.nz;
+    draw_kernel<<<(unsigned)blocks(n2, kRadsBlock / kWave), kRadsBlock, 0, s>>>(v, (uint32_t)n, swt, rads_segments(n),
+                                                                                 w16, draws, n2, out, N, first);
     return hipGetLastError();
 }
 
-hipError_t launch_knn3(const float *pts, int64_t N, float *ls, hipStream_t s)
+bool knn_uses_grid(int64_t N) { return N > kKnnBrute; }
+
+// Cubic cells over the box of the voxel centres, about four per point (axes
+// thinner than a cell get one).
+KnnGrid knn_grid(const RadsVol &v, int64_t N)
+{
+    KnnGrid g{};
+    const double L[3] = {(double)(v.nx - 1) * v.sx, (double)(v.ny - 1) * v.sy, (double)(v.nz - 1) * v.sz};
+    const float o[3] = {v.ox, v.oy, v.oz};
+    const double target = std::min<double>(4.0 * (double)N, (double)kKnnMaxCells);
+    bool on[3] = {L[0] > 0.0, L[1] > 0.0, L[2] > 0.0};
+    double h = 0.0;
+    for (int it = 0; it < 3; ++it) {
+        double prod = 1.0;
+        int dims = 0;
+        for (int a = 0; a < 3; ++a)
+            if (on[a]) {
+                prod *= L[a];
+                ++dims;
+            }
+        if (dims == 0) break;
+        h = pow(prod / target, 1.0 / dims);
+        for (int a = 0; a < 3; ++a) on[a] = on[a] && L[a] >= h;
+    }
+    double cells = 1.0;
+    for (int a = 0; a < 3; ++a) {
+        // (the running product keeps the cell count at most kKnnMaxCells)
+        const double room = std::floor((double)kKnnMaxCells / cells);
+        g.n[a] = on[a] && h > 0.0 ? (int)std::max(1.0, std::min(std::floor(L[a] / h), room)) : 1;
+        cells *= g.n[a];
+        const double ha = std::max(L[a], 1e-30) / g.n[a];
+        g.x0[a] = o[a];
+        g.h[a] = (float)ha;
+        g.inv[a] = g.n[a] > 1 ? (float)(1.0 / ha) : 0.0f;
+        g.slack[a] = (float)(8e-7 * (std::fabs((double)o[a]) + std::fabs((double)o[a] + L[a]) + L[a]));
+    }
+    return g;
+}
+
+hipError_t launch_knn_brute(const float *pts, int64_t N, float *ls, hipStream_t s)
 {
     if (N == 0) return hipSuccess;
-    knn3_kernel<<<(unsigned)blocks(N, kKnnBlock), kKnnBlock, 0, s>>>(pts, N, ls);
+    knn_brute_kernel<<<(unsigned)N, kRadsBlock, 0, s>>>(pts, N, nullptr, nullptr, ls);
+    return hipGetLastError();
+}
+
+hipError_t launch_knn_count(const KnnGrid &g, const float *pts, int64_t N, uint32_t *cnt, hipStream_t s)
+{
+    knn_count_kernel<<<(unsigned)blocks(N, kRadsBlock), kRadsBlock, 0, s>>>(g, pts, N, cnt);
+    return hipGetLastError();
+}
+
+hipError_t launch_knn_grid(const KnnGrid &g, const float *pts, int64_t N, uint32_t *cur, float4 *sorted,
+                           uint32_t *list, uint32_t *n_list, float *ls, hipStream_t s)
+{
+    knn_place_kernel<<<(unsigned)blocks(N, kRadsBlock), kRadsBlock, 0, s>>>(g, pts, N, cur, sorted);
+    knn_query_kernel<<<(unsigned)blocks(N, kRadsBlock / kKnnLanes), kRadsBlock, 0, s>>>(g, sorted, N, cur, ls, list,
+                                                                                        n_list);
+    // (what the rings left open; a fixed grid, most of it idle)
+    knn_brute_kernel<<<kKnnFarBlocks, kRadsBlock, 0, s>>>(pts, N, list, n_list, ls);
     return hipGetLastError();
 }
 

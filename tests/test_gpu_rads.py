@@ -123,3 +123,36 @@ def test_initial_model_renders(R):
     host = synth.Scene(**{name: p[name].cpu().numpy() for name in binding.PARAM_NAMES}, n_iso=n_iso, L=L)
     o = ref.render(host, [v])[0].ravel()
     assert np.linalg.norm(img - o) / np.linalg.norm(o) < 1e-4
+
+
+def _scattered(kind):
+    """Volumes whose points sit badly for a uniform grid of cells."""
+    rng = np.random.default_rng(11)
+    if kind == "thin":  # one slice: a flat grid
+        return rng.uniform(0.0, 100.0, (1, 70, 90)).astype(np.float32)
+    hu = np.zeros((65, 63, 66), np.float32)
+    if kind == "one voxel":  # every draw lands on the same point
+        hu[40, 30, 20] = 900.0
+    else:  # a small dense cluster and a few voxels far from it
+        hu[2:10, 3:12, 1:9] = rng.uniform(500.0, 900.0, (8, 9, 8))
+        hu[60, 60, 60] = hu[5, 58, 61] = hu[62, 4, 3] = 1.0
+        hu[33, 31, 35] = 850.0
+    return hu
+
+
+# (2^-24 relative rounding of coordinates up to ~120 mm and of the squared
+# distances stays below the 1e-4 of the reference comparison)
+@pytest.mark.parametrize("kind,n1,n2", [("thin", 9000, 5000), ("one voxel", 6, 5000),
+                                        ("cluster", 3000, 4200), ("cluster", 50, 4096)])
+def test_neighbour_scales_of_uneven_point_sets(R, kind, n1, n2):
+    hu = _scattered(kind)
+    M, W, N = _run(R, hu, (1.0, 1.25, 0.75), (-3.0, 2.0, 10.0), n1, n2, seed=3, full_knn=False)
+    assert N == min(n1, M) + n2
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1023), (1, 1, 1025), (3, 31, 33), (16, 8, 8)])
+def test_volume_segments(R, shape):
+    """Volumes just below, at and above a whole number of 1024-voxel segments."""
+    rng = np.random.default_rng(shape[2])
+    hu = rng.uniform(-1000.0, 1500.0, shape).astype(np.float32)
+    _run(R, hu, (1.0, 1.0, 1.0), (0.0, 0.0, 0.0), 200, 300, seed=1)
