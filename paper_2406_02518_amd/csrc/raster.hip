@@ -20,9 +20,9 @@
 //
 // Backward: the tail S_j = sum_{m>j} c_m s_m T_m is the saved pixel value
 // minus the running sum.  Per-pair image-plane gradients are summed over the
-// wave with DPP row operations (VALU only, no LDS round trip), over the
-// waves of the workgroup in LDS in a fixed order, and written once per tile
-// entry into its own slot (the pair's first slot plus the tile's row-major
+// wave (on the matrix cores for chunked items, with DPP row operations for
+// unchunked ones), over the waves of the workgroup in LDS in a fixed order,
+// and written once per tile entry into its own slot (the pair's first slot plus the tile's row-major
 // place in the pair's rectangle) -- no float atomics, so the gradients are
 // run-to-run deterministic.
 #include "internal.h"
@@ -279,24 +279,31 @@ __global__ __launch_bounds__(TW *TH) void raster_fwd_kernel(RasterArgs a)
     }
 }
 
-// Forward of 8 x 8 tiles in chunks (the tuned shape) with an entry list per
-// 4 x 4 quadrant.  An entry's cut-off ellipse usually covers a part of the
-// tile, and a wave that runs it on all 64 pixels spends most lanes on misses.
-// Here lane l covers pixel (4 (q % 2) + r % 4, 4 (q / 2) + r / 4) of the tile
-// (q = l / 16, r = l % 16); each batch of entries is listed per quadrant
-// whose pixel centres the ellipse's bounding box reaches (half-widths
-// kappa sqrt(Sigma_xx), kappa sqrt(Sigma_yy) of Sigma = A^-1, widened by
-// 0.1 %, far above the rounding of the per-pixel test), and the wave runs the
-// longest list, the lanes of each quadrant taking their own list's entries
-// in depth order (shorter lists are padded with a record that no pixel
-// reaches).  An entry left out of a quadrant's list misses all its pixels,
-// where the update is an exact no-op, so the images and chunk results equal
-// the unculled kernel's bit for bit.  The chunk results are stored by pixel
-// (row-major in the tile), as the other kernels index them.
-__global__ __launch_bounds__(kWave) void raster_fwd_quad_kernel(RasterArgs a)
+// Forward of chunked items with an entry list per 4 x 4 cell of the tile.  An
+// entry's cut-off ellipse usually covers a part of the tile, and a wave that
+// runs it on all its pixels spends most lanes on misses.  Here each wave owns
+// an 8 x 8 part of the tile and lane l covers pixel (4 (q % 2) + r % 4,
+// 4 (q / 2) + r / 4) of it (q = l / 16, r = l % 16), so that each 16-lane row
+// covers one cell; each batch of entries is listed per cell whose pixel
+// centres the ellipse's bounding box reaches (half-widths kappa
+// sqrt(Sigma_xx), kappa sqrt(Sigma_yy) of Sigma = A^-1, widened by 0.1 %, far
+// above the rounding of the per-pixel test), and the wave runs the longest of
+// its four lists, the lanes of each cell taking their own list's entries in
+// depth order (shorter lists are padded with a record that no pixel reaches).
+// An entry left out of a cell's list misses all its pixels, where the update
+// is an exact no-op, so the images and chunk results equal the unculled
+// kernel's bit for bit.  The chunk results are stored by pixel (row-major in
+// the tile), as the other kernels index them.
+//
+// Tiles of several waves stage a batch of one record per pixel together and
+// every wave lists it for its own cells: at 500k Gaussians / 512^2 and 16 x 16
+// tiles 86 us against 140 us for the unculled kernel (which runs every entry
+// on all 256 pixels).
+template <int TW, int TH>
+__global__ __launch_bounds__(TW *TH) void raster_fwd_cells_kernel(RasterArgs a)
 {
-    constexpr int TW = 8, TH = 8, NT = TW * TH, NUL = NT;
-    static_assert(NT == kWave, "one wave per tile");
+    constexpr int NT = TW * TH, NW = NT / kWave, NUL = NT;
+    constexpr int CX = TW / 4, CY = TH / 4;  // cells per row and column of the tile
     // records by entry, s1 first: entry e's pair sits at byte 16 e (s1) and
     // 16 e + S0OFF (s0), so that one register with two immediate offsets
     // reads it; the lists hold these byte places
@@ -304,13 +311,16 @@ __global__ __launch_bounds__(kWave) void raster_fwd_quad_kernel(RasterArgs a)
     __shared__ float4 s10[2 * (NT + 1)];
     float4 *const s1 = s10;
     float4 *const s0 = s10 + (NT + 1);
-    // per quadrant: the byte places of its entries (rows four words apart in
-    // bank, so that the four quadrants' reads of one step do not collide)
-    __shared__ __align__(16) uint32_t ql[4][NT + 4];
+    // per cell: the byte places of its entries (rows four words apart in
+    // bank, so that the four cells' reads of one step do not collide)
+    __shared__ __align__(16) uint32_t ql[4 * NW][NT + 4];
+    __shared__ uint32_t reach[NW > 1 ? NT : 1];  // cell columns (low bits) and rows an entry reaches
     __shared__ int sh_item;
-    const int tid = threadIdx.x;
-    const int qd = tid >> 4, qr = tid & 15;
-    const int lx = 4 * (qd & 1) + (qr & 3), ly = 4 * (qd >> 1) + (qr >> 2);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = NW > 1 ? tid / kWave : 0;
+    const int qd = lane >> 4, qr = lane & 15;
+    // this wave's first cell, this lane's pixel of the tile
+    const int wcx = 2 * (w % (TW / 8)), wcy = 2 * (w / (TW / 8));
+    const int lx = 4 * (wcx + (qd & 1)) + (qr & 3), ly = 4 * (wcy + (qd >> 1)) + (qr >> 2);
     const float k2s = __fmul_rn(a.o.kappa2, kExpScale);
     const float smax = a.o.sigma_max;
     const float kw = a.o.kappa * 1.001f;
@@ -357,7 +367,7 @@ __global__ __launch_bounds__(kWave) void raster_fwd_quad_kernel(RasterArgs a)
         };
         // the longest list in steps of four: four places of the lane's list,
         // then their records
-        const uint32_t *const myl = &ql[qd][0];
+        const uint32_t *const myl = &ql[4 * w + qd][0];
         auto run_lists = [&](int nmax, auto clamp_c) {
             for (int i0 = 0; i0 < nmax; i0 += 4) {
                 const uint4 ev = *reinterpret_cast<const uint4 *>(myl + i0);
@@ -376,43 +386,56 @@ __global__ __launch_bounds__(kWave) void raster_fwd_quad_kernel(RasterArgs a)
             __syncthreads();
             const uint32_t j = b0 + tid;
             bool over = false;  // an opacity above sigma_max / 2 in this batch
-            uint32_t qm = 0u;   // quadrants this lane's entry reaches
+            uint32_t rm = 0u;   // bit i: reaches cell column i; bit CX + i: cell row i
             if (j < I.e) {
                 const uint32_t gid = min(a.tval[j], (uint32_t)a.n - 1u);
                 const size_t idx = vbase + gid;
                 float4 r0 = a.rec[4 * idx], r1 = a.rec[4 * idx + 1];
                 over = r1.y > 0.5f * smax;
-                // bounding box of the cut-off ellipse against the quadrants'
-                // pixel-centre ranges [0.5, 3.5] and [4.5, 7.5] of the tile
+                // bounding box of the cut-off ellipse against the cells'
+                // pixel-centre ranges [4 i + 0.5, 4 i + 3.5] of the tile
                 const float idet = 1.0f / (r0.z * r1.x - r0.w * r0.w);
                 const float hx = kw * sqrtf(r1.x * idet), hy = kw * sqrtf(r0.z * idet);
                 const float ux = r0.x - tx0, uy = r0.y - ty0;
-                const bool xa = ux - hx <= 3.5f && ux + hx >= 0.5f, xb = ux - hx <= 7.5f && ux + hx >= 4.5f;
-                const bool ya = uy - hy <= 3.5f && uy + hy >= 0.5f, yb = uy - hy <= 7.5f && uy + hy >= 4.5f;
-                qm = (xa && ya ? 1u : 0u) | (xb && ya ? 2u : 0u) | (xa && yb ? 4u : 0u) | (xb && yb ? 8u : 0u);
+#pragma unroll
+                for (int i = 0; i < CX; ++i)
+                    rm |= (ux - hx <= 4.0f * i + 3.5f && ux + hx >= 4.0f * i + 0.5f) ? 1u << i : 0u;
+#pragma unroll
+                for (int i = 0; i < CY; ++i)
+                    rm |= (uy - hy <= 4.0f * i + 3.5f && uy + hy >= 4.0f * i + 0.5f) ? 1u << (CX + i) : 0u;
                 scale_conic(r0, r1);
                 s0[tid] = r0;
                 s1[tid] = r1;
             }
+            if constexpr (NW > 1) reach[tid] = rm;
             // lists: every place first holds the padding record, then each
-            // quadrant's entries in batch order
-            reinterpret_cast<uint4 *>(&ql[qd][4 * qr])[0] = make_uint4(16u * NUL, 16u * NUL, 16u * NUL, 16u * NUL);
+            // cell's entries in batch order
+#pragma unroll
+            for (int h = 0; h < NW; ++h)
+                reinterpret_cast<uint4 *>(&ql[4 * w + qd][4 * qr])[16 * h] =
+                    make_uint4(16u * NUL, 16u * NUL, 16u * NUL, 16u * NUL);
+            const bool clamp = __syncthreads_or(over);
+            int len[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int h = 0; h < NW; ++h) {
+                const uint32_t m = NW > 1 ? reach[h * kWave + lane] : rm;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t need = (1u << (wcx + (q & 1))) | (1u << (CX + wcy + (q >> 1)));
+                    const bool in = (m & need) == need;
+                    const uint64_t bal = wave_any_mask(in);
+                    if (in) {
+                        const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+                        ql[4 * w + q][len[q] + pos] = 16u * (uint32_t)(h * kWave + lane);
+                    }
+                    len[q] += (int)__popcll(bal);
+                }
+            }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            int nmax = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const bool in = (qm >> q) & 1u;
-                const uint64_t b = wave_any_mask(in);
-                if (in) {
-                    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32),
-                                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
-                    ql[q][pos] = 16u * (uint32_t)tid;
-                }
-                nmax = max(nmax, (int)__popcll(b));
-            }
-            const bool clamp = __syncthreads_or(over);
+            const int nmax = max(max(len[0], len[1]), max(len[2], len[3]));
             if (clamp) run_lists(nmax, std::true_type{});
             else run_lists(nmax, std::false_type{});
         }
@@ -475,9 +498,9 @@ __global__ __launch_bounds__((TW * TH * merge_tiles_per_block<TW, TH>())) void m
     }
 }
 
-// SPLIT: work items are chunks (every entry of an item lies before the
-// pixel's last contribution).
-template <int TW, int TH, bool SPLIT>
+// Backward of unchunked items (split 0, and t_min > 0, which a lane's stop
+// needs): one workgroup per tile, every entry on all its pixels.
+template <int TW, int TH>
 __global__ __launch_bounds__(TW *TH) void raster_bwd_kernel(RasterArgs a)
 {
     constexpr int NT = TW * TH;
@@ -517,22 +540,17 @@ __global__ __launch_bounds__(TW *TH) void raster_bwd_kernel(RasterArgs a)
         const bool inside = px < V.W && py < V.H;
         const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
         const size_t vbase = (size_t)v * a.n;
-        float g = 0.0f, Cf = 0.0f, T = 1.0f, Cacc = 0.0f;
+        float g = 0.0f, Cf = 0.0f, T = 1.0f;
         uint32_t lastp = I.b;
         if (inside) {
             const size_t p = (size_t)V.pix_base + (size_t)py * V.W + px;
             g = a.dL_dimg[p];
             Cf = a.img_saved[p];
-            lastp = a.split ? I.e : a.nlast[p];
-        }
-        if (a.split) {
-            const float2 pre = a.part[(size_t)it * NT + tid];
-            Cacc = pre.x;
-            T = pre.y;
+            lastp = a.nlast[p];
         }
         // g times the tail S (the saved pixel value minus the colour
         // composited so far), kept up to date entry by entry
-        float Sg = g * (Cf - Cacc);
+        float Sg = g * Cf;
         // end of the longest contributing prefix in the item
         uint32_t m = lastp;
 #pragma unroll
@@ -574,7 +592,7 @@ __global__ __launch_bounds__(TW *TH) void raster_bwd_kernel(RasterArgs a)
                         const float dx = __fsub_rn(fpx, r0.x), dy = __fsub_rn(fpy, r0.y);
                         const float ex = falloff_exponent(dx, dy, r0.z, r0.w, r1.x);
                         bool hit = ex >= k2e;
-                        if constexpr (!SPLIT) hit = hit && (b0 + (uint32_t)q) < lastp;
+                        hit = hit && (b0 + (uint32_t)q) < lastp;
                         // when any lane hits, the whole wave runs the entry:
                         // computed without branches, lanes that miss keep
                         // their state and contribute zeros
@@ -592,17 +610,14 @@ __global__ __launch_bounds__(TW *TH) void raster_bwd_kernel(RasterArgs a)
                             } else {
                                 om = one_minus_alpha_g(r1.y, G);
                             }
-                            if constexpr (!SPLIT) {
-                                // t_min > 0 runs unsplit
-                                if (tmin > 0.0f) {
-                                    const bool stop = hit & (__fmul_rn(T, om) < tmin);
-                                    k2e = stop ? kLaneOff : k2e;
-                                    hit = hit & !stop;
-                                    G = stop ? 0.0f : G;
-                                    sraw = stop ? 0.0f : sraw;
-                                    s = stop ? 0.0f : s;
-                                    om = stop ? 1.0f : om;
-                                }
+                            if (tmin > 0.0f) {
+                                const bool stop = hit & (__fmul_rn(T, om) < tmin);
+                                k2e = stop ? kLaneOff : k2e;
+                                hit = hit & !stop;
+                                G = stop ? 0.0f : G;
+                                sraw = stop ? 0.0f : sraw;
+                                s = stop ? 0.0f : s;
+                                om = stop ? 1.0f : om;
                             }
                             // dL/ds = g (c T - S / (1 - s)) with S the tail
                             // after this entry: g S is updated by -g c s T
@@ -711,61 +726,99 @@ __global__ __launch_bounds__(TW *TH) void raster_bwd_kernel(RasterArgs a)
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// Backward of 8 x 8 tiles in chunks (the tuned shape).  The seven per-entry
-// sums are formed in two parts instead of by a seven-term butterfly per
-// entry.  The per-pair factor q = dL/ds G (zero where a pixel misses the
-// entry) goes to LDS for sixteen entries at a time, and its moments about the
-// mean come from one dense contraction over the 64 pixels on the matrix
-// cores: raw moments M_n = sum_p q(p) P_n(p) of the pixel monomials
-// P = (1, x, y, x^2, x y, y^2) about the tile centre, sixteen steps of
-// v_mfma_f32_16x16x4_f32 with the entries as rows and the monomials as
-// columns, then shifted to each entry's mean.  The colour term g s T is
-// summed by a transposing butterfly over the wave.  The vector ALU keeps the
-// per-pair compositing arithmetic; the matrix cores, which run beside it,
-// take the reductions.
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5))) void raster_bwd_mm_kernel(RasterArgs a)
+// Backward of chunked items.  Each wave owns an 8 x 8 part of the tile, one
+// lane per pixel, and runs the entries of its list (those whose cut-off box
+// reaches the part; with 8 x 8 tiles every entry of the item) in two sweeps
+// over eight at a time:
+//
+//   front to back: G, s and gT = g T (g = dL/dC of the pixel) of every entry,
+//     the colour term g s T, and Sg = g times the tail S behind the eight;
+//   back to front: with B = S / T = the colour seen behind entry j,
+//     dL/ds_j = g T_j (c_j - B), then B <- B + s_j (c_j - B).
+// Only one division per eight entries is left (B behind the last, Sg /
+// gT); per entry it was v_rcp_f32 (8.4 clocks per wave here, against 2.4 of a
+// multiply) and three more operations.  Sg is a difference of colours of
+// order g, so B = Sg / gT is only known to about eps / T; each step back
+// multiplies that error by (1 - s) and gT_j = gT / prod (1 - s), so what
+// reaches dL/ds_j is eps g / (1 - s_j), as with the division per entry.
+//
+// The seven per-entry sums over the pixels: q = dL/ds G (zero where a pixel
+// misses an entry) goes to LDS for sixteen entries, and its moments about the
+// mean come from one dense contraction on the matrix cores: raw moments M_n =
+// sum_p q(p) P_n(p) of the pixel monomials P = (1, x, y, x^2, x y, y^2) about
+// the centre of each 4 x 4 quarter of the part, then shifted to each entry's
+// mean and added (about quarters, since a small Gaussian's moments lose bits in
+// the shift from a distant centre).  v_mfma_f32_4x4x1_16b takes one pixel of
+// four quarters x sixteen entries per step, the pixel's monomials broadcast
+// from one block of the A operand, and leaves lane (entry, quarter) with its
+// own moments in registers: 32 steps of about 10 clocks for the sixteen
+// entries, where sixteen v_mfma_f32_16x16x4 (6 of 16 columns used) took 525 and
+// another trip through LDS.  Matrix and vector instructions of a SIMD do not
+// overlap on this part (measured), so their clocks count like any others.  The
+// colour term is summed by a transposing butterfly over the wave.
+//
+// Tiles of several waves: the waves share the staged records, and every
+// wave's sums go to LDS by entry, where the entry's lane adds the waves that
+// ran it in a fixed order.
+//
+// Measured (500k Gaussians / 512^2, tile sides 16 and 8): 219 and 170 us; the
+// general kernel above took 475 us at 16 x 16, the previous form of this one
+// (per-entry division, v_mfma_f32_16x16x4, 8 x 8 tiles only) 189 us.  Bound by
+// VALU and MFMA issue: about 100 clocks of a SIMD per entry and wave, of which
+// exponent and cut-off 40, compositing 20, contraction 21, colour sum 10.
+// Eight entries per sweep: 170 us, four 177 us.
+template <int TW, int TH>
+__global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TW * TH == 64 ? 5 : 4))) void raster_bwd_mm_kernel(RasterArgs a)
 {
-    // entries per contraction, and entries whose records are read together
-    // (two: 0.2235 ms against 0.2242 for one and 0.2242 for four, at 500k /
-    // 512^2; reading the next batch's records during the current one was
-    // slower, 0.2443 ms, through the registers it holds)
-    constexpr int TW = 8, TH = 8, NT = TW * TH, GRP = 16, PF = 2;
-    static_assert(NT == kWave, "one wave per tile");
-    // s1 first, as in the general kernel (paired reads of alpha and c)
-    __shared__ float4 s10[2 * NT];
+    constexpr int NT = TW * TH, NW = NT / kWave, GRP = 16, SWEEP = 8, PX = TW / 8;
+    constexpr bool MULTI = NW > 1;
+    // entries per batch: with several waves 128 (their per-entry sums fill
+    // LDS: four workgroups of 16 x 16 tiles per CU)
+    constexpr int BATCH = MULTI ? 128 : NT;
+    static_assert(BATCH <= NT, "one lane stages an entry");
+    // records by entry, s1 first: entry e's pair sits at byte 16 e (s1) and
+    // 16 e + S0OFF (s0); place BATCH holds a record no pixel reaches
+    constexpr uint32_t S0OFF = 16u * (BATCH + 1);
+    __shared__ float4 s10[2 * (BATCH + 1)];
     float4 *const s1 = s10;
-    float4 *const s0 = s10 + NT;
-    __shared__ uint32_t se[NT];
-    // q by (entry, pixel), the rows padded so that the operand reads of one
-    // step fall in distinct banks
-    __shared__ float aq[GRP][NT + 1];
-    __shared__ float dm[GRP][8];  // raw moments by (entry, monomial)
-    __shared__ float tsm[GRP];    // the colour term by entry
+    float4 *const s0 = s10 + (BATCH + 1);
+    __shared__ uint32_t se[BATCH];
+    // q by (entry of the group, pixel); rows padded so that the operand reads
+    // fall in distinct banks
+    constexpr int QROW = kWave + 4;
+    __shared__ __align__(16) float aq[NW][GRP][QROW];
+    // several waves: the byte places of a wave's entries, its sums by entry of
+    // the batch, and the waves that run an entry (a bit each)
+    __shared__ __align__(16) uint16_t list[MULTI ? NW : 1][MULTI ? BATCH + GRP : 1];
+    __shared__ float acc_e[MULTI ? NW : 1][MULTI ? BATCH : 1][7];
+    __shared__ uint8_t reach[MULTI ? BATCH : 1];
     __shared__ int sh_item;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int w = MULTI ? __builtin_amdgcn_readfirstlane(tid / kWave) : 0;
+    const int wx = 8 * (w % PX), wy = 8 * (w / PX);  // the wave's part of the tile
     const float k2s = __fmul_rn(a.o.kappa2, kExpScale);
     const float smax = a.o.sigma_max;
-    // matrix operands: lane l supplies A[l % 16][l / 16] = q of entry l % 16 at
-    // pixel p = st + 16 (l / 16) in step st, and B[l / 16][l % 16] = monomial
-    // l % 16 of that pixel (zero past the sixth); D[r][j] comes back in lane
-    // j + 16 (r / 4), item r % 4
-    float bm[GRP];
-    {
-        const int nn = tid & 15, kq = tid >> 4;
-#pragma unroll
-        for (int st = 0; st < GRP; ++st) {
-            const int p = st + 16 * kq;
-            const float x = (float)(p & 7) - 3.5f, y = (float)(p >> 3) - 3.5f;
-            float b = 0.0f;
-            b = nn == 0 ? 1.0f : b;
-            b = nn == 1 ? x : b;
-            b = nn == 2 ? y : b;
-            b = nn == 3 ? x * x : b;
-            b = nn == 4 ? x * y : b;
-            b = nn == 5 ? y * y : b;
-            bm[st] = b;
-        }
+    const float kw = a.o.kappa * 1.001f;
+    const char *const srec = reinterpret_cast<const char *>(s10);
+    if (tid == 0) {
+        // d^T A d = -(dx^2 + dy^2) ~ -2e36, alpha = c = 0
+        s0[BATCH] = make_float4(1e18f, 1e18f, -1.0f, 0.0f);
+        s1[BATCH] = make_float4(-1.0f, 0.0f, 0.0f, 0.0f);
     }
+    // monomials of pixel k of a quarter (k = lane / 4, monomial lane % 4 and
+    // 4 + lane % 4): block k of the A operand
+    float am0, am1;
+    {
+        const int k = lane >> 2, n = lane & 3;
+        const float x = (float)(k & 3) - 1.5f, y = (float)(k >> 2) - 1.5f;
+        am0 = n == 0 ? 1.0f : n == 1 ? x : n == 2 ? y : x * x;
+        am1 = n == 0 ? x * y : n == 1 ? y * y : 0.0f;
+    }
+    auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
     int iter = 0;
     for (;;) {
         const int it = next_item(a, iter, &sh_item);
@@ -775,11 +828,13 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5))) void
         const ViewDev &V = a.views[v];
         const int lt = I.tile - V.tile_base;
         const int ty = lt / V.ntx, tx = lt - ty * V.ntx;
-        const int px = tx * TW + tid % TW, py = ty * TH + tid / TW;
+        // (lane 16 q + k: pixel k, row by row, of quarter q)
+        const int lx = wx + 4 * ((lane >> 4) & 1) + (lane & 3), ly = wy + 4 * (lane >> 5) + ((lane >> 2) & 3);
+        const int px = tx * TW + lx, py = ty * TH + ly;
         const bool inside = px < V.W && py < V.H;
         const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
         // the monomials' origin
-        const float cx = (float)(tx * TW) + 0.5f * TW, cy = (float)(ty * TH) + 0.5f * TH;
+        const float cx = (float)(tx * TW + wx) + 4.0f, cy = (float)(ty * TH + wy) + 4.0f;
         const size_t vbase = (size_t)v * a.n;
         float g = 0.0f, Cf = 0.0f;
         if (inside) {
@@ -787,116 +842,168 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5))) void
             g = a.dL_dimg[p];
             Cf = a.img_saved[p];
         }
-        // (C, T) in front of the chunk, and g times the tail S
-        const float2 pre = a.part[(size_t)it * NT + tid];
-        float T = pre.y;
+        // (C, T) in front of the chunk: g T and g times the tail S
+        const float2 pre = a.part[(size_t)it * NT + ly * TW + lx];
+        float gT = g * pre.y;
         float Sg = g * (Cf - pre.x);
-        float k2e = inside ? k2s : kLaneOff;
-        // slots of group qp (its raw moments in acc, its colour terms in tsm):
-        // the moments go through LDS by (entry, monomial), then lane e < 16
-        // shifts entry qp + e's moments to the mean and stores its slot
-        auto finalize = [&](int qp, int cnt, const floatx4 &acc) {
-            if ((tid & 15) < 6) {
+        const float k2e = inside ? k2s : kLaneOff;
+        // Sums of the group of entries at list place qp, whose q is in aq and
+        // whose colour terms are in tsum (lane 4 e + .: entry e): lane (eg, qt,
+        // j) = 16 eg + 4 qt + j takes quarter qt of entry 4 eg + j, shifts its
+        // moments to the mean and adds the quarters over the lanes of its row;
+        // the lane with qt = j stores.
+        auto finalize = [&](int qp, int cnt, float tsum) {
+            const int el = qp + 4 * (lane >> 4) + (lane & 3), qt = (lane >> 2) & 3;
+            const float *const qrow = &aq[w][4 * (lane >> 4) + (lane & 3)][16 * qt];
+            const float4 x0 = *reinterpret_cast<const float4 *>(qrow), x1 = *reinterpret_cast<const float4 *>(qrow + 4);
+            const float4 x2 = *reinterpret_cast<const float4 *>(qrow + 8), x3 = *reinterpret_cast<const float4 *>(qrow + 12);
+            const int e = MULTI ? (int)(list[w][el] / 16u) : el;
+            const float4 r0 = s0[e];
+            floatx4 A = {0.0f, 0.0f, 0.0f, 0.0f}, B = {0.0f, 0.0f, 0.0f, 0.0f};
+            // (the block of A to broadcast is an immediate)
+#define DDGS_MOMENTS(X, K)                                           \
+    A = __builtin_amdgcn_mfma_f32_4x4x1f32(am0, X, A, 4, K, 0);      \
+    B = __builtin_amdgcn_mfma_f32_4x4x1f32(am1, X, B, 4, K, 0)
+            DDGS_MOMENTS(x0.x, 0); DDGS_MOMENTS(x0.y, 1); DDGS_MOMENTS(x0.z, 2); DDGS_MOMENTS(x0.w, 3);
+            DDGS_MOMENTS(x1.x, 4); DDGS_MOMENTS(x1.y, 5); DDGS_MOMENTS(x1.z, 6); DDGS_MOMENTS(x1.w, 7);
+            DDGS_MOMENTS(x2.x, 8); DDGS_MOMENTS(x2.y, 9); DDGS_MOMENTS(x2.z, 10); DDGS_MOMENTS(x2.w, 11);
+            DDGS_MOMENTS(x3.x, 12); DDGS_MOMENTS(x3.y, 13); DDGS_MOMENTS(x3.z, 14); DDGS_MOMENTS(x3.w, 15);
+#undef DDGS_MOMENTS
+            // moments about the mean: with x = u + (x - u), u the mean's offset
+            // from the quarter's centre
+            const float M0 = A[0], M1 = A[1], M2 = A[2], M3 = A[3], M4 = B[0], M5 = B[1];
+            const float ux = r0.x - (cx + ((qt & 1) ? 2.0f : -2.0f)), uy = r0.y - (cy + ((qt & 2) ? 2.0f : -2.0f));
+            float m[6];
+            m[0] = M1 - ux * M0;
+            m[1] = M2 - uy * M0;
+            m[2] = M3 - ux * (2.0f * M1 - ux * M0);
+            m[3] = M4 - ux * M2 - uy * M1 + ux * uy * M0;
+            m[4] = M5 - uy * (2.0f * M2 - uy * M0);
+            m[5] = M0;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) dm[4 * (tid >> 4) + i][tid & 15] = acc[i];
+            for (int t = 0; t < 6; ++t) {
+                m[t] += dpp_move<0x128>(m[t]);  // row_ror:8
+                m[t] += dpp_move<0x124>(m[t]);  // row_ror:4
             }
-            __syncthreads();
-            if (tid < GRP && qp + tid < cnt) {
-                // moments about the mean: with x = u + (x - u), u the mean's
-                // offset from the tile centre
-                const float M0 = dm[tid][0], M1 = dm[tid][1], M2 = dm[tid][2];
-                const float M3 = dm[tid][3], M4 = dm[tid][4], M5 = dm[tid][5];
-                const float4 r0 = s0[qp + tid];
-                const float ux = r0.x - cx, uy = r0.y - cy;
-                const float m1x = M1 - ux * M0, m1y = M2 - uy * M0;
-                const float mxx = M3 - ux * (2.0f * M1 - ux * M0);
-                const float mxy = M4 - ux * M2 - uy * M1 + ux * uy * M0;
-                const float myy = M5 - uy * (2.0f * M2 - uy * M0);
-                const size_t e = se[qp + tid];
-                if (e < a.slot_cap) {
-                    a.slot[2 * e] = make_float4(m1x, m1y, mxx, mxy);
-                    a.slot[2 * e + 1] = make_float4(myy, M0, tsm[tid], 0.0f);
+            if (qt == (lane & 3) && el < cnt) {
+                if constexpr (MULTI) {
+                    float *const o = &acc_e[w][e][0];
+                    o[0] = m[0]; o[1] = m[1]; o[2] = m[2]; o[3] = m[3]; o[4] = m[4]; o[5] = m[5]; o[6] = tsum;
+                } else {
+                    const size_t sl = se[e];
+                    if (sl < a.slot_cap) {
+                        a.slot[2 * sl] = make_float4(m[0], m[1], m[2], m[3]);
+                        a.slot[2 * sl + 1] = make_float4(m[4], m[5], tsum, 0.0f);
+                    }
                 }
             }
-            __syncthreads();
+            wave_sync();
         };
-        // The batch's groups of 16 entries.  Software-pipelined: group k's
-        // contraction is issued after its entries, and its slots are
-        // finalised after group k + 1's entries, so the matrix cores' latency
-        // is covered by the next group's arithmetic.
+        // The wave's cnt entries in groups of 16 (a partial group ends in the
+        // record no pixel reaches).  Branch-free: lanes that miss an entry run
+        // the same arithmetic with G = 0, which leaves gT and the tail as they
+        // are and makes q and g s T zero.
         auto run_groups = [&](int cnt, auto clamp_c) {
             constexpr bool CLAMP = decltype(clamp_c)::value;
-            floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
             for (int q0 = 0; q0 < cnt; q0 += GRP) {
                 float tv[GRP];
                 // the group's first entry in one vector register (opaque to
                 // the compiler), so that the record reads take immediate offsets
                 int qv = q0;
                 asm volatile("" : "+v"(qv));
-                // PF entries' records read together, then run in order
 #pragma unroll
-                for (int e4 = 0; e4 < GRP; e4 += PF) {
-                    float4 R0[PF], R1[PF];
+                for (int h = 0; h < GRP; h += SWEEP) {
+                    float sv[SWEEP], rv[SWEEP], cv[SWEEP];
 #pragma unroll
-                    for (int u = 0; u < PF; ++u) {
-                        R0[u] = s0[qv + e4 + u];
-                        R1[u] = s1[qv + e4 + u];
-                    }
-#pragma unroll
-                    for (int u = 0; u < PF; ++u) {
-                        const int e = e4 + u;
-                        const float4 r0 = R0[u], r1 = R1[u];
-                        // branch-free: lanes that miss (and the padding record)
-                        // run the same arithmetic with G = 0, which leaves T and
-                        // the tail as they are and makes q and g s T zero, so
-                        // the compiler may interleave the entries of the group
-                        const float dx = __fsub_rn(fpx, r0.x), dy = __fsub_rn(fpy, r0.y);
-                        const float ex = falloff_exponent(dx, dy, r0.z, r0.w, r1.x);
-                        const bool hit = ex >= k2e;
-                        const float G = hit ? __builtin_amdgcn_exp2f(ex) : 0.0f;
-                        const float sraw = __fmul_rn(r1.y, G);
-                        float s = sraw, om;
-                        if constexpr (CLAMP) {
-                            s = clamp_opacity(sraw, smax);
-                            om = __fsub_rn(1.0f, s);
+                    for (int e2 = 0; e2 < SWEEP; e2 += 2) {
+                        float4 R0[2], R1[2];
+                        if constexpr (MULTI) {
+                            const uint32_t pl = *reinterpret_cast<const uint32_t *>(&list[w][qv + h + e2]);
+                            const uint32_t pa = pl & 0xFFFFu, pb = pl >> 16;
+                            R1[0] = *reinterpret_cast<const float4 *>(srec + pa);
+                            R0[0] = *reinterpret_cast<const float4 *>(srec + pa + S0OFF);
+                            R1[1] = *reinterpret_cast<const float4 *>(srec + pb);
+                            R0[1] = *reinterpret_cast<const float4 *>(srec + pb + S0OFF);
                         } else {
-                            om = one_minus_alpha_g(r1.y, G);
+#pragma unroll
+                            for (int u = 0; u < 2; ++u) {
+                                R0[u] = s0[qv + h + e2 + u];
+                                R1[u] = s1[qv + h + e2 + u];
+                            }
                         }
-                        // dL/ds = g (c T - S / (1 - s)), S the tail after this entry
-                        const float gc = g * r1.z;
-                        const float sT = __fmul_rn(s, T);
-                        Sg = __fmaf_rn(-gc, sT, Sg);
-                        const float ds = __fmaf_rn(gc, T, -(Sg * __builtin_amdgcn_rcpf(om)));
-                        float qq = ds * G;
-                        if constexpr (CLAMP) qq = (sraw > smax) ? 0.0f : qq;
-                        T = __fmul_rn(T, om);
-                        aq[e][tid] = qq;
-                        tv[e] = g * sT;
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            const int e = e2 + u;
+                            const float4 r0 = R0[u], r1 = R1[u];
+                            const float dx = __fsub_rn(fpx, r0.x), dy = __fsub_rn(fpy, r0.y);
+                            const float ex = falloff_exponent(dx, dy, r0.z, r0.w, r1.x);
+                            const bool hit = ex >= k2e;
+                            const float G = hit ? __builtin_amdgcn_exp2f(ex) : 0.0f;
+                            const float sraw = __fmul_rn(r1.y, G);
+                            float s = sraw, om;
+                            if constexpr (CLAMP) {
+                                s = clamp_opacity(sraw, smax);
+                                om = __fsub_rn(1.0f, s);
+                            } else {
+                                om = one_minus_alpha_g(r1.y, G);
+                            }
+                            const float t = gT * s;
+                            Sg = __fmaf_rn(-r1.z, t, Sg);
+                            float r = gT * G;
+                            if constexpr (CLAMP) r = (sraw > smax) ? 0.0f : r;
+                            gT = gT * om;
+                            tv[h + e] = t;
+                            sv[e] = s;
+                            rv[e] = r;
+                            cv[e] = r1.z;
+                        }
+                    }
+                    // the colour behind the sweep (0 where nothing of g T is
+                    // left: its products with gT_j vanish then)
+                    const float ig = fabsf(gT) > 1e-37f ? __builtin_amdgcn_rcpf(gT) : 0.0f;
+                    float Bk = Sg * ig;
+                    Bk = __fmaf_rn(__fmaf_rn(-Bk, gT, Sg), ig, Bk);  // (v_rcp_f32 alone is 1 ulp off)
+                    Bk = __builtin_amdgcn_fmed3f(Bk, -1e30f, 1e30f);
+#pragma unroll
+                    for (int e = SWEEP - 1; e >= 0; --e) {
+                        const float d = cv[e] - Bk;
+                        Bk = __fmaf_rn(sv[e], d, Bk);
+                        aq[w][h + e][lane] = rv[e] * d;
                     }
                 }
                 const float tsum = wave_transpose_sum16(tv);
-                if (q0 > 0) finalize(q0 - GRP, cnt, acc);
-                if ((tid & 3) == 0) tsm[tid >> 2] = tsum;
-                __syncthreads();
-                acc = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int st = 0; st < GRP; ++st)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[tid & 15][st + 16 * (tid >> 4)], bm[st], acc, 0, 0, 0);
+                wave_sync();
+                finalize(q0, cnt, tsum);
             }
-            finalize((cnt - 1) / GRP * GRP, cnt, acc);
         };
-        for (uint32_t b0 = I.b; b0 < I.e; b0 += NT) {
-            const int cnt = (int)min((uint32_t)NT, I.e - b0);
+        for (uint32_t b0 = I.b; b0 < I.e; b0 += BATCH) {
+            const int cnt = (int)min((uint32_t)BATCH, I.e - b0);
             __syncthreads();
             const uint32_t j = b0 + tid;
             bool over = false;  // an opacity above sigma_max / 2 in this batch
-            if (j < I.e) {
+            if (tid < BATCH && j < I.e) {
                 const uint32_t gid = min(a.tval[j], (uint32_t)a.n - 1u);
                 const size_t idx = vbase + gid;
                 float4 r0 = a.rec[4 * idx], r1 = a.rec[4 * idx + 1];
                 const float4 r2 = a.rec[4 * idx + 2];
                 const uint32_t place = __float_as_uint(r1.w);
                 over = r1.y > 0.5f * smax;
+                if constexpr (MULTI) {
+                    // the parts of the tile whose pixel centres the bounding
+                    // box of the cut-off ellipse reaches (as in the forward)
+                    const float idet = 1.0f / (r0.z * r1.x - r0.w * r0.w);
+                    const float hx = kw * sqrtf(r1.x * idet), hy = kw * sqrtf(r0.z * idet);
+                    const float ux = r0.x - (float)(tx * TW), uy = r0.y - (float)(ty * TH);
+                    uint32_t m = 0u;
+#pragma unroll
+                    for (int q = 0; q < NW; ++q) {
+                        const float ox = 8.0f * (q % PX), oy = 8.0f * (q / PX);
+                        const bool in = ux - hx <= ox + 7.5f && ux + hx >= ox + 0.5f && uy - hy <= oy + 7.5f &&
+                                        uy + hy >= oy + 0.5f;
+                        m |= in ? 1u << q : 0u;
+                    }
+                    reach[tid] = (uint8_t)m;
+                }
                 scale_conic(r0, r1);
                 s0[tid] = r0;
                 s1[tid] = r1;
@@ -908,17 +1015,56 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5))) void
                 const uint32_t at = (uint32_t)((ty - ty0) * (tx1 - tx0 + 1) + (tx - tx0));
                 se[tid] = first_slot(a.slot_bofs, a.slot_nblk, v, (int)gid, place) +
                           kept_rank(__float_as_uint(r2.z), area, at);
-            } else {
-                // places past the batch's entries hold a record that no pixel
-                // reaches (d^T A d = -(dx^2 + dy^2) ~ -2e36, alpha = c = 0):
-                // every group runs all its entries without a bound check, and
-                // these contribute exact zeros
-                s0[tid] = make_float4(1e18f, 1e18f, -1.0f, 0.0f);
-                s1[tid] = make_float4(-1.0f, 0.0f, 0.0f, 0.0f);
+            } else if (tid < BATCH) {
+                // places past the batch's entries: the record no pixel reaches
+                if constexpr (MULTI) {
+                    reach[tid] = 0u;
+                } else {
+                    s0[tid] = make_float4(1e18f, 1e18f, -1.0f, 0.0f);
+                    s1[tid] = make_float4(-1.0f, 0.0f, 0.0f, 0.0f);
+                }
             }
             const bool clamp = __syncthreads_or(over);
-            if (clamp) run_groups(cnt, std::true_type{});
-            else run_groups(cnt, std::false_type{});
+            int mine = cnt;  // entries this wave runs
+            if constexpr (MULTI) {
+                mine = 0;
+#pragma unroll
+                for (int h = 0; h < BATCH / kWave; ++h) {
+                    const bool in = ((uint32_t)reach[h * kWave + lane] >> w) & 1u;
+                    const uint64_t bal = wave_any_mask(in);
+                    if (in) {
+                        const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+                        list[w][mine + pos] = (uint16_t)(16u * (uint32_t)(h * kWave + lane));
+                    }
+                    mine += (int)__popcll(bal);
+                }
+                if (lane < GRP) list[w][mine + lane] = (uint16_t)(16u * BATCH);
+                wave_sync();
+            }
+            if (mine > 0) {
+                if (clamp) run_groups(mine, std::true_type{});
+                else run_groups(mine, std::false_type{});
+            }
+            if constexpr (MULTI) {
+                __syncthreads();
+                if (tid < cnt) {
+                    const uint32_t m = reach[tid];
+                    float r[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int q = 0; q < NW; ++q) {
+                        if ((m >> q) & 1u) {
+#pragma unroll
+                            for (int t = 0; t < 7; ++t) r[t] += acc_e[q][tid][t];
+                        }
+                    }
+                    const size_t sl = se[tid];
+                    if (sl < a.slot_cap) {
+                        a.slot[2 * sl] = make_float4(r[0], r[1], r[2], r[3]);
+                        a.slot[2 * sl + 1] = make_float4(r[4], r[5], r[6], 0.0f);
+                    }
+                }
+            }
         }
     }
 }
@@ -945,8 +1091,7 @@ hipError_t fwd_inst(const RasterArgs &a, int pb, hipStream_t s)
     if (grid > 0) {
         const bool cnt = a.pair_counts != nullptr;
         if (a.split && cnt) raster_fwd_kernel<TW, TH, true, true><<<grid, TW * TH, 0, s>>>(a);
-        else if (a.split && TW == 8 && TH == 8) raster_fwd_quad_kernel<<<grid, TW * TH, 0, s>>>(a);
-        else if (a.split) raster_fwd_kernel<TW, TH, true, false><<<grid, TW * TH, 0, s>>>(a);
+        else if (a.split) raster_fwd_cells_kernel<TW, TH><<<grid, TW * TH, 0, s>>>(a);
         else if (cnt) raster_fwd_kernel<TW, TH, false, true><<<grid, TW * TH, 0, s>>>(a);
         else raster_fwd_kernel<TW, TH, false, false><<<grid, TW * TH, 0, s>>>(a);
     }
@@ -962,12 +1107,8 @@ hipError_t bwd_inst(const RasterArgs &a, int pb, hipStream_t s)
 {
     const int grid = a.queue_counter ? pb : round_up8(a.split ? a.max_items : a.n_tiles);
     if (grid > 0) {
-        if (a.split && TW == 8 && TH == 8)
-            raster_bwd_mm_kernel<<<grid, TW * TH, 0, s>>>(a);
-        else if (a.split)
-            raster_bwd_kernel<TW, TH, true><<<grid, TW * TH, 0, s>>>(a);
-        else
-            raster_bwd_kernel<TW, TH, false><<<grid, TW * TH, 0, s>>>(a);
+        if (a.split) raster_bwd_mm_kernel<TW, TH><<<grid, TW * TH, 0, s>>>(a);
+        else raster_bwd_kernel<TW, TH><<<grid, TW * TH, 0, s>>>(a);
     }
     return hipGetLastError();
 }
