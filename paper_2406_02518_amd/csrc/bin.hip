@@ -80,10 +80,9 @@ struct ScanArgs {
 
 __device__ __forceinline__ uint32_t is_long(uint32_t cnt) { return cnt > (uint32_t)kSortShort ? 1u : 0u; }
 
-__device__ void slot_block_scan(uint32_t *slot_btot, int64_t slot_nb, uint32_t *wl)
+__device__ void slot_block_scan(uint32_t *slot_btot, int64_t slot_nb, uint32_t carry, uint32_t *wl)
 {
-    // exclusive scan in place, wrapping at 2^32 like the slot indices
-    uint32_t carry = 0;
+    // exclusive scan in place from carry, wrapping at 2^32 like the slot indices
     for (int64_t c0 = 0; c0 < slot_nb; c0 += 4 * kBlock) {
         const int64_t b = c0 + 4 * (int64_t)threadIdx.x;
         uint32_t x[4], s = 0;
@@ -131,7 +130,7 @@ __global__ __launch_bounds__(kBlock) void tile_scan_self_kernel(ScanArgs a)
     __shared__ uint32_t wl[kWaves];
     __shared__ uint64_t red[kWaves];
     __shared__ uint32_t ired[kWaves], lred[kWaves];
-    if (blockIdx.x == 0) slot_block_scan(a.slot_btot, a.slot_nb, wl);
+    if (blockIdx.x == 0) slot_block_scan(a.slot_btot, a.slot_nb, 0u, wl);
     const int base = blockIdx.x * kBlock;
     const uint32_t sp = a.split;
     // entries, long tiles and (with chunks) work items of the tiles before
@@ -201,76 +200,102 @@ __global__ __launch_bounds__(kBlock) void tile_scan_self_kernel(ScanArgs a)
 }
 
 // More tiles: block sums, one block scanning them, then the blocks' scans.
-__global__ __launch_bounds__(kBlock) void tile_sum_kernel(const uint32_t *cnt, int n, uint64_t *bsum, uint32_t *lsum)
+// The slot numbering's block totals go the same way in blocks of their own
+// (kSlotSeg totals each): one block scanning all of them serially took 86 us
+// for the 75008 totals of 64 views x 300k Gaussians.
+constexpr int kSlotSeg = 4 * kBlock;
+
+__global__ __launch_bounds__(kBlock) void tile_sum_kernel(ScanArgs a, int nb, uint64_t *bsum, uint32_t *lsum,
+                                                          uint32_t *ssum)
 {
-    const int t = blockIdx.x * kBlock + threadIdx.x;
-    const uint32_t x = t < n ? cnt[t] : 0u;
-    uint64_t c = x;
-    uint32_t l = is_long(x);
+    __shared__ uint64_t red[kWaves];
+    __shared__ uint32_t lred[kWaves];
+    uint64_t c = 0;
+    uint32_t l = 0;
+    if ((int)blockIdx.x < nb) {
+        const int t = blockIdx.x * kBlock + threadIdx.x;
+        const uint32_t x = t < a.n_tiles ? a.tile_cnt[t] : 0u;
+        c = x;
+        l = is_long(x);
+    } else {
+        const int64_t b = (int64_t)(blockIdx.x - nb) * kSlotSeg + threadIdx.x;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) l += b + q * kBlock < a.slot_nb ? a.slot_btot[b + q * kBlock] : 0u;
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         c += __shfl_xor(c, o, kWave);
         l += __shfl_xor(l, o, kWave);
     }
-    __shared__ uint64_t red[kWaves];
-    __shared__ uint32_t lred[kWaves];
     if ((threadIdx.x & (kWave - 1)) == 0) {
         red[threadIdx.x / kWave] = c;
         lred[threadIdx.x / kWave] = l;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x != 0) return;
+    l = lred[0] + lred[1] + lred[2] + lred[3];
+    if ((int)blockIdx.x < nb) {
         bsum[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
-        lsum[blockIdx.x] = lred[0] + lred[1] + lred[2] + lred[3];
+        lsum[blockIdx.x] = l;
+    } else {
+        ssum[blockIdx.x - nb] = l;  // (wraps at 2^32 like the slot indices)
     }
 }
 
-__global__ __launch_bounds__(1024) void tile_top_kernel(uint64_t *bsum, uint32_t *lsum, int nb, ScanArgs a)
+__global__ __launch_bounds__(1024) void tile_top_kernel(uint64_t *bsum, uint32_t *lsum, int nb, uint32_t *ssum, int ns,
+                                                        ScanArgs a)
 {
     __shared__ uint64_t wt[16];
-    __shared__ uint32_t lwt[16];
+    __shared__ uint32_t lwt[16], swt[16];
     __shared__ uint64_t carry_s;
-    __shared__ uint32_t lcarry_s;
+    __shared__ uint32_t lcarry_s, scarry_s;
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     if (threadIdx.x == 0) {
         carry_s = 0;
         lcarry_s = 0;
+        scarry_s = 0;
     }
     __syncthreads();
-    for (int c0 = 0; c0 < nb; c0 += 1024) {
+    for (int c0 = 0; c0 < max(nb, ns); c0 += 1024) {
         const int idx = c0 + threadIdx.x;
         const uint64_t x = idx < nb ? bsum[idx] : 0;
         const uint32_t lx = idx < nb ? lsum[idx] : 0u;
+        const uint32_t sx = idx < ns ? ssum[idx] : 0u;
         uint64_t inc = x;
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
             const uint64_t y = __shfl_up(inc, o, kWave);
             if (lane >= o) inc += y;
         }
-        const uint32_t linc = wave_incl_scan(lx);
+        const uint32_t linc = wave_incl_scan(lx), sinc = wave_incl_scan(sx);
         if (lane == kWave - 1) {
             wt[w] = inc;
             lwt[w] = linc;
+            swt[w] = sinc;
         }
         __syncthreads();
         uint64_t before = carry_s, tot = 0;
-        uint32_t lbefore = lcarry_s, ltot = 0;
+        uint32_t lbefore = lcarry_s, ltot = 0, sbefore = scarry_s, stot = 0;
         for (int q = 0; q < 16; ++q) {
             if (q < w) {
                 before += wt[q];
                 lbefore += lwt[q];
+                sbefore += swt[q];
             }
             tot += wt[q];
             ltot += lwt[q];
+            stot += swt[q];
         }
         if (idx < nb) {
             bsum[idx] = before + inc - x;
             lsum[idx] = lbefore + linc - lx;
         }
+        if (idx < ns) ssum[idx] = sbefore + sinc - sx;
         __syncthreads();
         if (threadIdx.x == 0) {
             carry_s += tot;
             lcarry_s += ltot;
+            scarry_s += stot;
         }
         __syncthreads();
     }
@@ -280,10 +305,17 @@ __global__ __launch_bounds__(1024) void tile_top_kernel(uint64_t *bsum, uint32_t
     }
 }
 
-__global__ __launch_bounds__(kBlock) void tile_apply_kernel(const uint64_t *bsum, const uint32_t *lsum, ScanArgs a)
+__global__ __launch_bounds__(kBlock) void tile_apply_kernel(const uint64_t *bsum, const uint32_t *lsum, int nb,
+                                                            const uint32_t *ssum, ScanArgs a)
 {
     __shared__ uint32_t wl[kWaves];
-    if (blockIdx.x == gridDim.x - 1) slot_block_scan(a.slot_btot, a.slot_nb, wl);
+    if ((int)blockIdx.x >= nb) {
+        // (the segment of slot_btot this block holds starts with ssum's place)
+        const int sb = blockIdx.x - nb;
+        const int64_t b = (int64_t)sb * kSlotSeg;
+        slot_block_scan(a.slot_btot + b, min((int64_t)kSlotSeg, a.slot_nb - b), ssum[sb], wl);
+        return;
+    }
     const int t = blockIdx.x * kBlock + threadIdx.x;
     const uint32_t v = t < a.n_tiles ? a.tile_cnt[t] : 0u;
     uint32_t tot;
@@ -689,13 +721,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) v
 
 }  // namespace
 
+size_t slot_ssum_words(int64_t slot_nb) { return (size_t)std::max<int64_t>(1, (slot_nb + kSlotSeg - 1) / kSlotSeg); }
 bool tile_scan_makes_items(int n_tiles) { return n_tiles <= kTileScanSelfMax; }
 
 hipError_t launch_tile_scan(const uint32_t *tile_cnt, int n_tiles, uint2 *ranges, uint32_t *cursor,
                             uint32_t capacity, uint64_t *total, uint32_t *m_out, uint32_t *flags,
                             uint32_t *skipped, unsigned long long *need, uint32_t *slot_btot, int64_t slot_nb,
-                            uint64_t *bsum, size_t bsum_words, const TileItems *it, const LongTiles &lt,
-                            hipStream_t s)
+                            uint32_t *slot_ssum, size_t slot_ssum_words, uint64_t *bsum, size_t bsum_words,
+                            const TileItems *it, const LongTiles &lt, hipStream_t s)
 {
     ScanArgs a{tile_cnt, n_tiles, ranges, cursor, capacity, total, m_out, flags, skipped, need, slot_btot, slot_nb,
                0u, nullptr, nullptr, nullptr, 0u, nullptr, nullptr, lt.list, lt.n, lt.bsum};
@@ -716,9 +749,11 @@ hipError_t launch_tile_scan(const uint32_t *tile_cnt, int n_tiles, uint2 *ranges
     }
     if (it) return hipErrorInvalidValue;  // the three-launch scan makes no items
     if (!bsum || (size_t)nb > bsum_words || !lt.bsum || (size_t)nb > lt.bsum_words) return hipErrorInvalidValue;
-    tile_sum_kernel<<<nb, kBlock, 0, s>>>(tile_cnt, n_tiles, bsum, lt.bsum);
-    tile_top_kernel<<<1, 1024, 0, s>>>(bsum, lt.bsum, nb, a);
-    tile_apply_kernel<<<nb, kBlock, 0, s>>>(bsum, lt.bsum, a);
+    const int ns = (int)((slot_nb + kSlotSeg - 1) / kSlotSeg);
+    if (!slot_ssum || (size_t)ns > slot_ssum_words) return hipErrorInvalidValue;
+    tile_sum_kernel<<<nb + ns, kBlock, 0, s>>>(a, nb, bsum, lt.bsum, slot_ssum);
+    tile_top_kernel<<<1, 1024, 0, s>>>(bsum, lt.bsum, nb, slot_ssum, ns, a);
+    tile_apply_kernel<<<nb + ns, kBlock, 0, s>>>(bsum, lt.bsum, nb, slot_ssum, a);
     return hipGetLastError();
 }
 

@@ -417,6 +417,7 @@ ddgs_status ensure_static(ddgs_ctx *c)
     uint64_t *tb;
     DDGS_TRY(ensure_t(c, "tile_bsum", std::max(1, (c->n_tiles + 255) / 256), &tb));
     DDGS_TRY(ensure_t(c, "slot_btot", std::max<int64_t>(1, (int64_t)c->views_h.size() * slot_blocks(n)), &u));
+    DDGS_TRY(ensure_t(c, "slot_ssum", slot_ssum_words(V * slot_blocks(n)), &u));
     DDGS_TRY(ensure_t(c, "ranges", std::max(1, c->n_tiles), &u2));
     DDGS_TRY(ensure_t(c, "long_tiles", std::max(1, c->n_tiles), &u));
     DDGS_TRY(ensure_t(c, "long_bsum", std::max(1, (c->n_tiles + 255) / 256), &u));
@@ -595,7 +596,8 @@ ddgs_status enqueue_front(ddgs_ctx *c, uint32_t capacity, bool captured)
     HIP_TRY(c, launch_tile_scan(buf<uint32_t>(c, "tile_cnt"), c->n_tiles, buf<uint2>(c, "ranges"),
                                 buf<uint32_t>(c, "cursor"), capacity, total_ptr(c), mdev_ptr(c), flags_ptr(c),
                                 captured ? skipped_ptr(c) : nullptr, captured ? need_ptr(c) : nullptr,
-                                buf<uint32_t>(c, "slot_btot"), (int64_t)V * slot_blocks(m.n), buf<uint64_t>(c, "tile_bsum"),
+                                buf<uint32_t>(c, "slot_btot"), (int64_t)V * slot_blocks(m.n),
+                                buf<uint32_t>(c, "slot_ssum"), c->bufs["slot_ssum"].bytes / sizeof(uint32_t), buf<uint64_t>(c, "tile_bsum"),
                                 c->bufs["tile_bsum"].bytes / sizeof(uint64_t), fold ? &ti : nullptr, long_tiles(c), s));
     // the sort stage is timed in two parts: a plain render reads the entry
     // total back to the host between them, and that round trip is not device work
