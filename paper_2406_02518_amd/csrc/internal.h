@@ -268,6 +268,7 @@ struct ProjBwdArgs {
     GaussCache gc;
     const ViewDev *views;
     int V;
+    int views_per_block;  // (set by launch_project_bwd)
     RenderOpts o;
     const uint32_t *cnt;
     const uint32_t *slot_lp, *slot_bofs;  // slot numbering (first_slot)
