@@ -509,6 +509,12 @@ __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const
 constexpr int kSortShortBlock = 512;
 constexpr int kSortLong = 7168, kSortLongBlock = 1024;
 constexpr int kSortLongGrid = 512;  // two workgroups per CU
+// With no more listed tiles than CUs one workgroup per CU is all there is to
+// run, so the launch takes an instance that holds 14336 entries in 131 KB of
+// LDS: ranges between the two sizes then stay out of the global-memory path
+// (100k Gaussians / 251 x 187, 32 listed tiles of up to 7253 entries: 30 ->
+// 15 us).  With more tiles two smaller workgroups per CU are faster.
+constexpr int kSortLongBig = 14336, kSortLongBigGrid = 256;
 constexpr int kBinBits = 11;
 constexpr int kBins = 1 << kBinBits;
 
@@ -706,7 +712,8 @@ __global__ __launch_bounds__(BLOCK) void tile_sort_kernel(const uint2 *ranges, c
 // (a workgroup per tile, with this much LDS each, would spend more on being
 // dispatched for every short or empty tile than on the long ones).
 template <int CAP, int BLOCK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) void tile_sort_long_kernel(
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CAP > kSortLong ? 4 : 8, CAP > kSortLong ? 4 : 8))) void
+tile_sort_long_kernel(
     const uint2 *ranges, const uint2 *ent, uint2 *tmp, uint32_t *tval, const uint32_t *list, const uint32_t *n_list)
 {
     __shared__ SortLds<CAP, BLOCK> S;
@@ -816,8 +823,12 @@ hipError_t launch_tile_sort(const uint2 *ranges, const uint32_t *tile_cnt, int n
     tile_sort_kernel<kSortShort, kSortShortBlock><<<n_tiles, kSortShortBlock, 0, s>>>(ranges, tile_cnt, n_tiles, ent,
                                                                                        tmp, tval, g <= 0 ? 1 : 0);
     if (g <= 0) return hipGetLastError();
-    tile_sort_long_kernel<kSortLong, kSortLongBlock><<<g, kSortLongBlock, 0, s>>>(ranges, ent, tmp, tval, lt.list,
-                                                                                   lt.n);
+    if (g <= kSortLongBigGrid)
+        tile_sort_long_kernel<kSortLongBig, kSortLongBlock><<<g, kSortLongBlock, 0, s>>>(ranges, ent, tmp, tval,
+                                                                                          lt.list, lt.n);
+    else
+        tile_sort_long_kernel<kSortLong, kSortLongBlock><<<g, kSortLongBlock, 0, s>>>(ranges, ent, tmp, tval, lt.list,
+                                                                                       lt.n);
     return hipGetLastError();
 }
 

@@ -583,12 +583,14 @@ ddgs_status enqueue_front(ddgs_ctx *c, uint32_t capacity, bool captured)
     HIP_TRY(c, launch_bin_count(m.n, V, buf<uint32_t>(c, "cnt"), buf<uint2>(c, "rect"), buf<uint32_t>(c, "tmask"),
                                 buf<ViewDev>(c, "views"), c->n_tiles, c->max_view_tiles, buf<uint32_t>(c, "bin_mat"),
                                 buf<uint32_t>(c, "tile_cnt"), s));
-    // a captured step (its buffers are sized already) has the scan write the
-    // chunked raster's work items too
+    // the scan writes the chunked raster's work items too, as far as their
+    // buffer goes (a captured step's is sized for its capacity; a plain render
+    // that turns out to need more entries than its buffers hold lists the
+    // items again once they have grown)
     TileItems ti{};
-    const bool fold = captured && effective_split(c) > 0 && tile_scan_makes_items(c->n_tiles);
+    const bool fold = effective_split(c) > 0 && tile_scan_makes_items(c->n_tiles);
     if (fold) {
-        c->max_items = (int)max_items_for(c, capacity);
+        c->max_items = (int)max_items_for(c, captured ? (int64_t)capacity : c->entry_cap);
         ti = TileItems{effective_split(c), buf<uint32_t>(c, "item_cnt"), buf<uint32_t>(c, "item_base"),
                        buf<uint2>(c, "items"), (uint32_t)c->max_items, n_items_ptr(c), counter_ptr(c)};
     }
@@ -1473,7 +1475,10 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
         ddgs_status st = DDGS_OK;
         if (total >= 0xFFFFFFFFull) st = fail(c, DDGS_ERR_CAPACITY, "more than 2^32-1 tile entries");
         c->M = (int64_t)total;
-        if (st == DDGS_OK && c->M > c->entry_cap) st = ensure_entries(c, c->M);
+        if (st == DDGS_OK && c->M > c->entry_cap) {
+            st = ensure_entries(c, c->M);
+            c->items_folded = false;
+        }
         if (st != DDGS_OK) return st;
         // (the exact total bounds the work items, so the raster grids take
         // no more workgroups than this render can fill; the buffers keep

@@ -91,3 +91,47 @@ def test_gradients_behind_opaque_stacks(R, tw, th):
                 assert torch.isfinite(x).all(), (k, scale)
     finally:
         R.set_options(tile_w=16, tile_h=16, split=256)
+
+
+@pytest.mark.parametrize("n", [1, 2, 2560, 2561, 7168, 7169, 14336, 14337])
+def test_tile_order_around_the_sort_sizes(R, n):
+    """One tile that every Gaussian reaches, at the lengths where the per-tile
+    sort changes its instance: the list is in (depth key, index) order."""
+    sc = synth.random_scene(51, n, k=8, L=1, extent=0.4, std_range=(2.0, 3.0), alpha_range=(0.001, 0.01))
+    sc.mean[:, 1::7] = sc.mean[:, 0::7][:, :sc.mean[:, 1::7].shape[1]]  # equal depths: ties go by index
+    R.set_scene(sc)
+    R.set_views([synth.view(8, 8, 1.0, 1000.0, 600.0, 0.0)])
+    R.render()
+    assert R.num_rendered() == n
+    zk = R.debug(binding.DBG_DEPTH_KEYS, np.uint32, n)
+    vals = R.debug(binding.DBG_TILE_VALS, np.uint32, n)
+    np.testing.assert_array_equal(vals, np.lexsort((np.arange(n), zk)))
+
+
+@pytest.mark.parametrize("split", [16, 256])
+def test_a_render_that_outgrows_its_buffers(split):
+    """The work items are listed by the tile scan as far as the buffers go; a
+    render that needs more lists them again: same image and gradients as a
+    renderer whose buffers were large enough, and the next render too."""
+    small = synth.random_scene(61, 40, k=8, L=1, extent=8.0)
+    large = synth.random_scene(62, 6000, k=8, L=1, extent=10.0, std_range=(0.5, 2.5))
+    v = synth.view(100, 70, 0.4, 1000.0, 600.0, 10.0)
+    dl = torch.randn(100 * 70, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    out = []
+    for warm in ((small,), (large, large)):
+        r = make_renderer(split=split)
+        for s in warm:
+            r.set_scene(s)
+            r.set_views([v])
+            r.render()
+        for _ in range(2):
+            r.set_scene(large)
+            r.set_views([v])
+            img = r.render()
+            g = r.backward(dl)
+            torch.cuda.synchronize()
+            out.append([img.cpu().numpy()] + [g[k].cpu().numpy() for k in sorted(g)])
+        r.close()
+    for o in out[1:]:
+        for x, y in zip(out[0], o):
+            np.testing.assert_array_equal(x, y)
