@@ -30,7 +30,8 @@
  *     never frees them.  ddgs_view arrays are host memory and are copied.
  *   - All device work is enqueued on the context's stream (settable, e.g.
  *     torch's current stream).  Entry points do not synchronise the stream
- *     except where stated (ddgs_render reads the number of tile entries back;
+ *     except where stated (ddgs_render reads the number of tile entries back,
+ *     except for small inputs, where ddgs_num_rendered does if it is asked;
  *     ddgs_check and the debug getters synchronise).
  *   - Every function returns a ddgs_status; on failure nothing is written to
  *     the outputs that the status code does not mention, and the message is
@@ -366,7 +367,8 @@ ddgs_status ddgs_set_allocator(ddgs_ctx *ctx, ddgs_alloc_fn alloc, ddgs_free_fn 
 
 /* Renders every view (Eq. 1 with Eq. 3) into images (device,
  * ddgs_image_size floats).  Reads the number of tile entries back to size
- * the sort (one stream synchronisation).  Keeps what the backward needs
+ * the sort (one stream synchronisation; small inputs, whose buffers hold
+ * every tile of every Gaussian, do without).  Keeps what the backward needs
  * (the sorted tile lists, per-pixel final value and last contributor). */
 ddgs_status ddgs_render(ddgs_ctx *ctx, float *images);
 

@@ -53,7 +53,6 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t x, uint32_t *lds /* >= 4
 // same scan lists, in tile order, the tiles of more than kSortShort entries
 // for the tile sort's long-range launch (a list built with a global atomic
 // per tile would serialise on its counter).
-constexpr int kSortShort = 2560;  // longest range the per-tile sort's first launch takes
 struct ScanArgs {
     const uint32_t *tile_cnt;
     int n_tiles;
@@ -351,14 +350,14 @@ struct BinArgs {
     uint32_t *mat;                // [groups * n_tiles]: view v at groups * tile_base[v]
 };
 
-// Calls f(local tile) for every kept tile of pair r's rectangle inside [t0, t1).
+// Calls f(local tile) for every kept tile of the rectangle rc (mask: a pair's
+// tmask) inside [t0, t1).
 template <class F>
-__device__ __forceinline__ void for_tiles(const BinArgs &a, int64_t r, int ntx, int t0, int t1, F f)
+__device__ __forceinline__ void for_tiles(uint2 rc, uint32_t mask, int ntx, int t0, int t1, F f)
 {
-    const uint2 rc = a.rect[r];
     const int tx0 = rc.x & 0xFFFF, ty0 = rc.x >> 16, tx1 = rc.y & 0xFFFF, ty1 = rc.y >> 16;
     if ((ty1 + 1) * ntx <= t0 || ty0 * ntx >= t1) return;  // no row of the rectangle in the window
-    const uint32_t mask = a.tmask[r], area = (uint32_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
+    const uint32_t area = (uint32_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
     uint32_t place = 0;
     for (int ty = ty0; ty <= ty1; ++ty)
         for (int tx = tx0; tx <= tx1; ++tx, ++place) {
@@ -385,7 +384,7 @@ __global__ __launch_bounds__(kBinBlock) void bin_count_kernel(BinArgs a)
     for (int i = i0 + (int)threadIdx.x; i < i1; i += kBinBlock) {
         const int64_t r = (int64_t)v * a.n + i;
         if (a.cnt[r] == 0u) continue;
-        for_tiles(a, r, V.ntx, t0, t1, [&](int lt) { atomicAdd(&hist[lt - t0], 1u); });
+        for_tiles(a.rect[r], a.tmask[r], V.ntx, t0, t1, [&](int lt) { atomicAdd(&hist[lt - t0], 1u); });
     }
     __syncthreads();
     uint32_t *row = a.mat + (size_t)a.groups * V.tile_base + (size_t)g * Tv + t0;
@@ -482,7 +481,7 @@ __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const
         const int64_t r = (int64_t)v * a.n + i;
         if (a.cnt[r] == 0u) continue;
         const uint32_t key = a.zkey[r];
-        for_tiles(a, r, V.ntx, t0, t1, [&](int lt) {
+        for_tiles(a.rect[r], a.tmask[r], V.ntx, t0, t1, [&](int lt) {
             const uint32_t p = atomicAdd(&cur[lt - t0], 1u);
             if (p < capacity) out[p] = make_uint2(key, (uint32_t)i);
         });
@@ -726,7 +725,131 @@ tile_sort_long_kernel(
     }
 }
 
+// ---------------------------------------------------------- small inputs
+// Up to kSmallPairs pairs and kSmallTiles tiles: the counts stay in one
+// workgroup's LDS from the counting to the scatter, so four launches (five
+// with the work items) become one and no count matrix is written.  At 2000
+// Gaussians / 64^2 each of those launches took 3 to 4 us of the card and about
+// 5 us of host time; this one takes 11 us.  The limit is where one workgroup's
+// two walks over the pairs (eight per thread) still cost less than that.
+constexpr int kSmallBlock = 1024, kSmallPairs = 8192, kSmallTiles = 4096, kSmallSlotBlocks = 1024;
+
+__global__ __launch_bounds__(kSmallBlock) void bin_small_kernel(BinArgs b, ScanArgs a, uint32_t *tile_cnt, uint2 *out)
+{
+    constexpr int PER = kSmallTiles / kSmallBlock;
+    __shared__ uint32_t cell[kSmallTiles];  // counts, then cursors, by global tile
+    __shared__ uint32_t wl[4][kSmallBlock / kWave];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    const int pairs = b.n * b.V;
+    // f(view, pair, kept tile) for every entry; a pair's values are loaded
+    // together (a load at a time, each waiting for the one before, is what
+    // such short walks would be bound by)
+    auto walk = [&](auto f) {
+        for (int r = tid; r < pairs; r += kSmallBlock) {
+            const int v = b.V == 1 ? 0 : r / b.n;
+            const uint32_t cnt = b.cnt[r], mask = b.tmask[r], key = b.zkey[r];
+            const uint2 rc = b.rect[r];
+            const int ntx = b.views[v].ntx, nty = b.views[v].nty, tb = b.views[v].tile_base;
+            if (cnt) for_tiles(rc, mask, ntx, 0, ntx * nty, [&](int lt) { f(tb + lt, key, (uint32_t)(r - v * b.n)); });
+        }
+    };
+    for (int t = tid; t < a.n_tiles; t += kSmallBlock) cell[t] = 0u;
+    __syncthreads();
+    walk([&](int t, uint32_t, uint32_t) { atomicAdd(&cell[t], 1u); });
+    const uint32_t sb = tid < a.slot_nb ? a.slot_btot[tid] : 0u;  // (at most one per thread)
+    __syncthreads();
+    // exclusive scans over the block, together: entries, long tiles, work
+    // items, and the slot numbering's block totals
+    uint32_t c[PER], x[4] = {0u, 0u, 0u, sb}, tot[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int t = tid * PER + q;
+        c[q] = t < a.n_tiles ? cell[t] : 0u;
+        x[0] += c[q];
+        x[1] += is_long(c[q]);
+        if (a.split) x[2] += (c[q] + a.split - 1u) / a.split;
+    }
+    uint32_t pre[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t inc = wave_incl_scan(x[k]);
+        if (lane == kWave - 1) wl[k][w] = inc;
+        pre[k] = inc - x[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSmallBlock / kWave; ++q)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t t = wl[k][q];
+            if (q < w) pre[k] += t;
+            tot[k] += t;
+        }
+    if (tid < a.slot_nb) a.slot_btot[tid] = pre[3];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int t = tid * PER + q;
+        if (t >= a.n_tiles) break;
+        tile_cnt[t] = c[q];
+        write_range(a, t, pre[0], c[q]);
+        cell[t] = pre[0];
+        pre[0] += c[q];
+        if (is_long(c[q])) a.long_list[pre[1]++] = (uint32_t)t;
+        if (a.split) {
+            const uint32_t nv = (c[q] + a.split - 1u) / a.split;
+            a.item_cnt[t] = nv;
+            a.item_base[t] = pre[2];
+            for (uint32_t k = 0; k < nv && pre[2] + k < a.max_items; ++k)
+                a.items[pre[2] + k] = make_uint2((uint32_t)t, k);
+            pre[2] += nv;
+        }
+    }
+    if (tid == 0) {
+        finish_scan(a, tot[0]);
+        *a.long_n = tot[1];
+        if (a.split) {
+            *a.n_items = tot[2] > a.max_items ? a.max_items : tot[2];
+            a.counter[0] = 0u;
+            a.counter[1] = 0u;
+        }
+    }
+    __syncthreads();
+    walk([&](int t, uint32_t key, uint32_t i) {
+        const uint32_t p = atomicAdd(&cell[t], 1u);
+        if (p < a.capacity) out[p] = make_uint2(key, i);
+    });
+}
+
 }  // namespace
+
+bool bin_small(int64_t n, int64_t V, int64_t n_tiles)
+{
+    return n > 0 && V > 0 && n <= kSmallPairs && V <= kSmallPairs / n && n_tiles > 0 && n_tiles <= kSmallTiles &&
+           V * slot_blocks(n) <= kSmallSlotBlocks;
+}
+
+hipError_t launch_bin_small(int n, int V, const uint32_t *cnt, const uint2 *rect, const uint32_t *tmask,
+                            const uint32_t *zkey, const ViewDev *views, int n_tiles, uint32_t *tile_cnt,
+                            uint2 *ranges, uint32_t *cursor, uint32_t capacity, uint64_t *total, uint32_t *m_out,
+                            uint32_t *flags, uint32_t *skipped, unsigned long long *need, uint32_t *slot_btot,
+                            int64_t slot_nb, const TileItems *it, const LongTiles &lt, uint2 *out, hipStream_t s)
+{
+    if (!bin_small(n, V, n_tiles) || slot_nb > kSmallSlotBlocks || !lt.list || !lt.n) return hipErrorInvalidValue;
+    const BinArgs b{n, V, 1, n, cnt, rect, tmask, zkey, views, nullptr};
+    ScanArgs a{tile_cnt, n_tiles, ranges, cursor, capacity, total, m_out, flags, skipped, need, slot_btot, slot_nb,
+               0u, nullptr, nullptr, nullptr, 0u, nullptr, nullptr, lt.list, lt.n, lt.bsum};
+    if (it && it->split > 0) {
+        a.split = (uint32_t)it->split;
+        a.item_cnt = it->cnt;
+        a.item_base = it->base;
+        a.items = it->items;
+        a.max_items = it->max_items;
+        a.n_items = it->n_items;
+        a.counter = it->counter;
+    }
+    bin_small_kernel<<<1, kSmallBlock, 0, s>>>(b, a, tile_cnt, out);
+    return hipGetLastError();
+}
 
 size_t slot_ssum_words(int64_t slot_nb) { return (size_t)std::max<int64_t>(1, (slot_nb + kSlotSeg - 1) / kSlotSeg); }
 bool tile_scan_makes_items(int n_tiles) { return n_tiles <= kTileScanSelfMax; }

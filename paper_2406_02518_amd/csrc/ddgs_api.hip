@@ -100,7 +100,9 @@ struct ddgs_ctx {
     bool rendered = false;
     uint64_t model_gen = 0, views_gen = 0, opt_gen = 0;
     uint64_t r_model_gen = ~0ull, r_views_gen = ~0ull, r_opt_gen = ~0ull;
-    int64_t M = 0;             // entries of the last render
+    int64_t M = 0;             // entries of the last render (-1: on the device only)
+    bool total_pending = false;  // M is read back when it is asked for (a small plain render)
+    hipStream_t total_stream = nullptr;  // the stream that render ran on
     uint32_t *queue = nullptr;
     int64_t entry_cap = 0;     // capacity of the entry buffers
     bool keep_unsorted = false;
@@ -112,7 +114,8 @@ struct ddgs_ctx {
     int64_t step_cap = 0;
     int64_t last_skipped = 0, last_need = 0;  // found by the last ddgs_check
     int max_items = 0;         // work items the raster grids are sized for
-    bool items_folded = false; // the tile scan wrote the work items (captured step)
+    bool items_folded = false; // the tile scan wrote the work items
+    bool binned = false;       // the entries are in their ranges already (bin_small)
     // workgroups of the long-range tile sort: a plain render reads the number
     // of long tiles with the entry total and launches one per long tile (no
     // launch if there are none); a captured step takes twice the most that
@@ -227,9 +230,13 @@ ddgs_status ensure(ddgs_ctx *c, const char *name, size_t bytes, void **out)
     return DDGS_OK;
 }
 
+ddgs_status resolve_total(ddgs_ctx *c);
+
 // Releases every workspace buffer (library-owned ones are freed).
 void release_buffers(ddgs_ctx *c)
 {
+    (void)resolve_total(c);  // (the entry total is in one of them)
+    c->total_pending = false;
     (void)hipStreamSynchronize(c->stream);
     if (!c->ws_base)
         for (auto &kv : c->bufs) {
@@ -451,6 +458,7 @@ int effective_split(const ddgs_ctx *c) { return c->opt.t_min > 0.0f ? 0 : std::m
 // long-range sort grid of a captured step (see ddgs_ctx::long_grid)
 int captured_long_grid(const ddgs_ctx *c)
 {
+    if (c->model.n <= kSortShort) return 0;  // (no tile can hold more)
     const bool seen = c->long_seen >= 0 && c->long_seen_n == c->model.n && c->long_seen_tiles == c->n_tiles;
     if (!seen) return 1 << 30;
     if (c->long_seen == 0) return 0;
@@ -561,12 +569,33 @@ void set_items(ddgs_ctx *c, RasterArgs &ra, bool backward)
     ra.queue_counter = c->opt.persistent ? counter_ptr(c) + (backward ? 1 : 0) : nullptr;
 }
 
+// Reads the entry total of a small plain render, which did not wait for it.
+ddgs_status resolve_total(ddgs_ctx *c)
+{
+    if (!c->total_pending) return DDGS_OK;
+    uint64_t t = 0;
+    HIP_TRY(c, hipSetDevice(c->device));
+    if (c->stream != c->total_stream) HIP_TRY(c, hipDeviceSynchronize());  // (the old stream may be gone)
+    HIP_TRY(c, hipMemcpyAsync(&t, total_ptr(c), sizeof(t), hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->M = (int64_t)t;
+    c->total_pending = false;
+    return DDGS_OK;
+}
+
+// Entries a small plain render may take room for without asking: 54 bytes
+// each, and the raster grids cover all of them (up to 4096 workgroups at chunks
+// of 64, most of which find no work).
+constexpr int64_t kSmallEntries = (int64_t)1 << 18;
+
 // Projection (which also counts every tile's entries) and the scan of the
 // tile counts into the tile ranges (stages shared by the plain and the
 // captured paths).  capacity: entries the tile lists may hold (the plain path
 // passes 2^32 - 1 and sizes its buffers from the total afterwards); captured:
 // the step counters (skipped replays, largest need) are kept.
-ddgs_status enqueue_front(ddgs_ctx *c, uint32_t capacity, bool captured)
+// small: the one-workgroup binning, which scatters the entries too (the entry
+// buffers hold `capacity`).
+ddgs_status enqueue_front(ddgs_ctx *c, uint32_t capacity, bool captured, bool small)
 {
     hipStream_t s = c->stream;
     const ModelDev m = model_dev(c->model, c->c_override);
@@ -580,9 +609,6 @@ ddgs_status enqueue_front(ddgs_ctx *c, uint32_t capacity, bool captured)
     HIP_TRY(c, launch_prep_project(m, gc, buf<ViewDev>(c, "views"), V, ro, po, s));
     stage_end(c, DDGS_T_PROJECT);
     stage_begin(c, DDGS_T_SORT);
-    HIP_TRY(c, launch_bin_count(m.n, V, buf<uint32_t>(c, "cnt"), buf<uint2>(c, "rect"), buf<uint32_t>(c, "tmask"),
-                                buf<ViewDev>(c, "views"), c->n_tiles, c->max_view_tiles, buf<uint32_t>(c, "bin_mat"),
-                                buf<uint32_t>(c, "tile_cnt"), s));
     // the scan writes the chunked raster's work items too, as far as their
     // buffer goes (a captured step's is sized for its capacity; a plain render
     // that turns out to need more entries than its buffers hold lists the
@@ -595,6 +621,21 @@ ddgs_status enqueue_front(ddgs_ctx *c, uint32_t capacity, bool captured)
                        buf<uint2>(c, "items"), (uint32_t)c->max_items, n_items_ptr(c), counter_ptr(c)};
     }
     c->items_folded = fold;
+    c->binned = small;
+    if (small) {
+        HIP_TRY(c, launch_bin_small(m.n, V, buf<uint32_t>(c, "cnt"), buf<uint2>(c, "rect"), buf<uint32_t>(c, "tmask"),
+                                    buf<uint32_t>(c, "zkey"), buf<ViewDev>(c, "views"), c->n_tiles,
+                                    buf<uint32_t>(c, "tile_cnt"), buf<uint2>(c, "ranges"), buf<uint32_t>(c, "cursor"),
+                                    capacity, total_ptr(c), mdev_ptr(c), flags_ptr(c),
+                                    captured ? skipped_ptr(c) : nullptr, captured ? need_ptr(c) : nullptr,
+                                    buf<uint32_t>(c, "slot_btot"), (int64_t)V * slot_blocks(m.n),
+                                    fold ? &ti : nullptr, long_tiles(c), buf<uint2>(c, "bin_ent"), s));
+        stage_end(c, DDGS_T_SORT);
+        return DDGS_OK;
+    }
+    HIP_TRY(c, launch_bin_count(m.n, V, buf<uint32_t>(c, "cnt"), buf<uint2>(c, "rect"), buf<uint32_t>(c, "tmask"),
+                                buf<ViewDev>(c, "views"), c->n_tiles, c->max_view_tiles, buf<uint32_t>(c, "bin_mat"),
+                                buf<uint32_t>(c, "tile_cnt"), s));
     HIP_TRY(c, launch_tile_scan(buf<uint32_t>(c, "tile_cnt"), c->n_tiles, buf<uint2>(c, "ranges"),
                                 buf<uint32_t>(c, "cursor"), capacity, total_ptr(c), mdev_ptr(c), flags_ptr(c),
                                 captured ? skipped_ptr(c) : nullptr, captured ? need_ptr(c) : nullptr,
@@ -616,9 +657,11 @@ ddgs_status enqueue_back(ddgs_ctx *c, int64_t cap, float *images)
     const int n = (int)c->model.n;
     uint2 *ent = buf<uint2>(c, "bin_ent");
     if (c->timing) (void)hipEventRecord(c->ev_sort_tail_s, c->stream);
-    HIP_TRY(c, launch_bin_scatter(n, V, buf<uint32_t>(c, "cnt"), buf<uint2>(c, "rect"), buf<uint32_t>(c, "tmask"),
-                                  buf<uint32_t>(c, "zkey"), buf<ViewDev>(c, "views"), c->n_tiles, c->max_view_tiles,
-                                  buf<uint32_t>(c, "bin_mat"), buf<uint32_t>(c, "cursor"), (uint32_t)cap, ent, s));
+    if (!c->binned)
+        HIP_TRY(c, launch_bin_scatter(n, V, buf<uint32_t>(c, "cnt"), buf<uint2>(c, "rect"), buf<uint32_t>(c, "tmask"),
+                                      buf<uint32_t>(c, "zkey"), buf<ViewDev>(c, "views"), c->n_tiles,
+                                      c->max_view_tiles, buf<uint32_t>(c, "bin_mat"), buf<uint32_t>(c, "cursor"),
+                                      (uint32_t)cap, ent, s));
     if (c->keep_unsorted)
         HIP_TRY(c, launch_copy_u32((uint32_t *)buf<uint2>(c, "ubin"), (const uint32_t *)ent, nullptr, 2 * cap, s));
     HIP_TRY(c, launch_tile_sort(buf<uint2>(c, "ranges"), buf<uint32_t>(c, "tile_cnt"), c->n_tiles, ent,
@@ -1459,8 +1502,25 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
     DDGS_TRY(ensure_static(c));
     DDGS_TRY(ensure_entries(c, std::max<int64_t>(c->entry_cap, 1)));
     const int64_t VN = c->model.n * (int64_t)c->views_h.size();
-    if (VN > 0) {
-        DDGS_TRY(enqueue_front(c, 0xFFFFFFFFu, false));
+    c->total_pending = false;
+    // A small input is binned by one workgroup, into entry buffers that hold
+    // every tile of every Gaussian: such a render needs no total from the
+    // device and does not wait for it (the stream synchronisation and the
+    // launches it held back cost about 30 us of a 2000-Gaussian call).  A
+    // caller region is not grown for it.
+    const int64_t worst = c->model.n * (int64_t)c->n_tiles;
+    const bool small = VN > 0 && bin_small(c->model.n, (int64_t)c->views_h.size(), c->n_tiles) &&
+                       worst <= kSmallEntries && (c->entry_cap >= worst || !c->ws_base);
+    if (small) {
+        DDGS_TRY(ensure_entries(c, std::max(worst, c->entry_cap)));
+        DDGS_TRY(enqueue_front(c, (uint32_t)std::min<int64_t>(c->entry_cap, 0xFFFFFFFFll), false, true));
+        c->M = -1;
+        c->total_pending = true;
+        c->total_stream = c->stream;
+        c->long_grid = c->model.n > kSortShort ? 1 << 30 : 0;
+        DDGS_TRY(enqueue_back(c, worst, images));
+    } else if (VN > 0) {
+        DDGS_TRY(enqueue_front(c, 0xFFFFFFFFu, false, false));
         // entry total ([0..1]) and number of long tiles ([12])
         uint32_t sc[13] = {};
         HIP_TRY(c, hipMemcpyAsync(sc, total_ptr(c), sizeof(sc), hipMemcpyDeviceToHost, c->stream));
@@ -1587,6 +1647,7 @@ ddgs_status ddgs_step_capture(ddgs_ctx *c, int kind, const float *target, float 
         float *tmp_img;
         DDGS_TRY(ensure_t(c, "capture_probe_img", c->total_pix, &tmp_img));
         DDGS_TRY(ddgs_render(c, tmp_img));
+        DDGS_TRY(resolve_total(c));
         cap = std::max<int64_t>(2 * c->M, 1024);
     }
     cap = std::min<int64_t>(cap, 0xFFFFFFF0ll);
@@ -1596,7 +1657,7 @@ ddgs_status ddgs_step_capture(ddgs_ctx *c, int kind, const float *target, float 
     c->timing = false;
     HIP_TRY(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
     c->long_grid = captured_long_grid(c);
-    ddgs_status st = enqueue_front(c, (uint32_t)c->step_cap, true);
+    ddgs_status st = enqueue_front(c, (uint32_t)c->step_cap, true, bin_small(c->model.n, (int64_t)c->views_h.size(), c->n_tiles));
     if (st == DDGS_OK) st = enqueue_back(c, c->step_cap, images);
     if (st == DDGS_OK) st = enqueue_loss(c, kind, images, target, lambda, loss_out, dL, true);
     if (st == DDGS_OK) st = enqueue_backward(c, dL, g, c->step_cap, true);
@@ -1660,6 +1721,7 @@ ddgs_status ddgs_step_launch(ddgs_ctx *c)
     DDGS_TRY(prepare_views(c));
     HIP_TRY(c, hipGraphLaunch(c->exec, c->stream));
     c->M = -1;  // unknown until ddgs_check
+    c->total_pending = false;
     c->rendered = true;
     c->r_model_gen = c->model_gen;
     c->r_views_gen = c->views_gen;
@@ -1685,6 +1747,7 @@ ddgs_status ddgs_check(ddgs_ctx *c, uint32_t *flags)
     if (!c) return DDGS_ERR_INVALID_ARG;
     HIP_TRY(c, hipSetDevice(c->device));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    DDGS_TRY(resolve_total(c));
     uint32_t sc[12] = {};
     if (buf<uint32_t>(c, "scalars"))
         HIP_TRY(c, hipMemcpy(sc, buf<uint32_t>(c, "scalars"), sizeof(sc), hipMemcpyDeviceToHost));
@@ -1778,6 +1841,7 @@ ddgs_status ddgs_param_count(int k, int L, int64_t n, int64_t *per, int64_t *sha
 ddgs_status ddgs_num_rendered(const ddgs_ctx *c, int64_t *n)
 {
     if (!c || !n) return DDGS_ERR_INVALID_ARG;
+    DDGS_TRY(resolve_total(const_cast<ddgs_ctx *>(c)));
     *n = c->M;
     return DDGS_OK;
 }
@@ -1833,6 +1897,7 @@ ddgs_status ddgs_debug_copy(ddgs_ctx *c, int what, void *host, size_t bytes)
     HIP_TRY(c, hipSetDevice(c->device));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     const int64_t VN = c->model.n * (int64_t)c->views_h.size();
+    DDGS_TRY(resolve_total(c));
     if (c->M < 0) {
         uint32_t fl = 0;
         ddgs_check(c, &fl);
@@ -2102,6 +2167,7 @@ ddgs_status ddgs_autotune(ddgs_ctx *c, const char *cache_path, int repeats, floa
         const ddgs_status st1 = ddgs_set_options(c, &base);
         if (st0 != DDGS_OK) return st0;
         if (st1 != DDGS_OK) return st1;
+        DDGS_TRY(resolve_total(c));
         if (n > 0 && V > 0) epp = (double)c->M / (double)(n * V);
     }
     const std::string sig = tune_signature(c, epp);
@@ -2190,8 +2256,9 @@ ddgs_status ddgs_autotune(ddgs_ctx *c, const char *cache_path, int repeats, floa
                 ts.push_back(t);
             }
         }
+        if (st == DDGS_OK) st = resolve_total(c);
         const int64_t cap = std::min<int64_t>(std::max<int64_t>(2 * c->M, 1024), 0xFFFFFFF0ll);
-        if (c->stream) st = ensure_entries(c, cap);
+        if (st == DDGS_OK && c->stream) st = ensure_entries(c, cap);
         if (st != DDGS_OK || !c->stream) {
             if (st == DDGS_OK) record(ts);
             return;
@@ -2205,7 +2272,7 @@ ddgs_status ddgs_autotune(ddgs_ctx *c, const char *cache_path, int repeats, floa
             st = fail(c, DDGS_ERR_HIP, "tuner: hipStreamBeginCapture failed");
             return;
         }
-        st = enqueue_front(c, (uint32_t)cap, true);
+        st = enqueue_front(c, (uint32_t)cap, true, bin_small(n, V, c->n_tiles));
         if (st == DDGS_OK) st = enqueue_back(c, cap, img);
         if (st == DDGS_OK) st = enqueue_backward(c, dL, &g, cap, true);
         const hipError_t ec = hipStreamEndCapture(c->stream, &graph);

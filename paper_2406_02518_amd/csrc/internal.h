@@ -349,6 +349,7 @@ hipError_t launch_ranges(const uint32_t *keys, const uint32_t *m_dev, int64_t m_
 // same launch also writes the work items of `split` entries per tile (what
 // launch_items writes).
 constexpr int kTileScanSelfMax = 16384;
+constexpr int kSortShort = 2560;  // longest range the per-tile sort's first launch takes
 struct TileItems {
     int split;
     uint32_t *cnt, *base;
@@ -387,6 +388,15 @@ hipError_t launch_bin_scatter(int n, int V, const uint32_t *cnt, const uint2 *re
                               const uint32_t *zkey, const ViewDev *views, int n_tiles, int max_view_tiles,
                               const uint32_t *mat, const uint32_t *start, uint32_t capacity, uint2 *out,
                               hipStream_t s);
+// Count, scan, work items and scatter of a small input in one launch of one
+// workgroup (where bin_small says so), with the results of launch_bin_count,
+// launch_tile_scan and launch_bin_scatter.
+bool bin_small(int64_t n, int64_t V, int64_t n_tiles);
+hipError_t launch_bin_small(int n, int V, const uint32_t *cnt, const uint2 *rect, const uint32_t *tmask,
+                            const uint32_t *zkey, const ViewDev *views, int n_tiles, uint32_t *tile_cnt,
+                            uint2 *ranges, uint32_t *cursor, uint32_t capacity, uint64_t *total, uint32_t *m_out,
+                            uint32_t *flags, uint32_t *skipped, unsigned long long *need, uint32_t *slot_btot,
+                            int64_t slot_nb, const TileItems *items, const LongTiles &lt, uint2 *out, hipStream_t s);
 // Sorts every tile's range of ent by (depth key, index) and writes the
 // indices to tval; tmp (same layout as ent) is scratch for ranges longer than
 // the LDS holds.  tile_cnt and lt are those the tile scan of the same step

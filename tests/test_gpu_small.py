@@ -1,0 +1,103 @@
+"""Small inputs, which one workgroup bins and whose plain render does not wait
+for its entry total: the same lists, images and gradients as the general
+binning gives, around the limits of the rule that selects it."""
+import numpy as np
+import pytest
+
+from gpu_common import make_renderer
+from paper_2406_02518_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _views(V, w, h):
+    return [synth.view(w - (3 * j) % 4, h, 0.9, 1000.0, 600.0, 25.0 * j) for j in range(V)]
+
+
+def _lists(r, sc, views, opts):
+    r.set_options(**opts)
+    r.set_scene(sc)
+    r.set_views(views)
+    img = r.render()
+    dl = torch.sin(torch.arange(img.numel(), device="cuda", dtype=torch.float32))
+    g = r.backward(dl)
+    torch.cuda.synchronize()
+    M = r.num_rendered()
+    base = r.debug(binding.DBG_TILE_BASE, np.int32, len(views) + 1)
+    return [img.cpu().numpy(), r.debug(binding.DBG_TILE_VALS, np.uint32, M),
+            r.debug(binding.DBG_RANGES, np.uint32, 2 * int(base[-1]))] + [g[k].cpu().numpy() for k in sorted(g)]
+
+
+# (the rule: n V <= 8192, up to 4096 tiles, n x tiles <= 2^18; the pairs of
+# sizes sit on both sides of it, the last is beyond the entry limit)
+@pytest.mark.parametrize("n,V,w,h", [(1, 1, 5, 4), (255, 3, 40, 33), (2000, 1, 64, 64), (257, 31, 24, 16),
+                                     (8192, 1, 80, 80), (8193, 1, 80, 80), (2731, 3, 64, 48), (3000, 1, 300, 290)])
+@pytest.mark.parametrize("opts", [dict(tile_w=16, tile_h=16, split=256), dict(tile_w=8, tile_h=8, split=64),
+                                  dict(tile_w=32, tile_h=8, split=0), dict(tile_w=16, tile_h=8, split=0, persistent=1)])
+def test_small_binning_equals_the_general_one(n, V, w, h, opts):
+    sc = synth.random_scene(71 + n, n, k=8, L=1, extent=18.0, std_range=(0.3, 2.0))
+    views = _views(V, w, h)
+    a, b = make_renderer(), make_renderer()
+    try:
+        got = _lists(a, sc, views, opts)
+        # a caller region is not grown for the small path: the general binning
+        b.set_options(**opts)
+        b.set_scene(sc)
+        b.set_views(views)
+        ws = torch.empty(b.workspace_size(max(1, got[1].size)) + (1 << 20), dtype=torch.uint8, device="cuda")
+        b.set_workspace(ws)
+        exp = _lists(b, sc, views, opts)
+        for x, y in zip(got, exp):
+            np.testing.assert_array_equal(x, y)
+    finally:
+        a.close()
+        b.close()
+
+
+@pytest.mark.parametrize("n", [900, 3000])
+def test_small_captured_step_equals_the_plain_path(n):
+    """Replays (with eager work between them) against the plain calls, and an
+    overflow of the captured capacity."""
+    sc = synth.random_scene(91, n, k=8, L=1, extent=18.0)
+    views = _views(2, 48, 40)
+    r = binding.Renderer(0, stream=torch.cuda.Stream())
+    try:
+        r.set_scene(sc)
+        r.set_views(views)
+        P = r.image_size()
+        img, dl = torch.empty(P, device="cuda"), torch.empty(P, device="cuda")
+        loss = torch.empty(2, device="cuda")
+        w = torch.sin(torch.arange(P, device="cuda", dtype=torch.float32))
+        grads = r.alloc_grads()
+
+        def capture():
+            with torch.cuda.stream(r.stream):
+                binding.ddgs_step_capture(r.ctx, binding.LOSS_LINEAR, w.data_ptr(), 0.0, img.data_ptr(), dl.data_ptr(),
+                                          loss.data_ptr(), r.grads_struct(grads))
+
+        torch.cuda.synchronize()
+        exp_img = r.render().clone()
+        exp_g = {k: v.clone() for k, v in r.backward(w).items()}
+        torch.cuda.synchronize()
+        need = r.num_rendered()
+        capture()
+        for _ in range(3):
+            binding.ddgs_step_launch(r.ctx)
+            assert r.check_step() == 0
+            torch.cuda.synchronize()
+            assert torch.equal(img, exp_img)
+            for k in exp_g:
+                assert torch.equal(grads[k], exp_g[k]), k
+            (w * 2.0).sum().item()
+        r.set_options(capacity=need - 1)
+        capture()
+        binding.ddgs_step_launch(r.ctx)
+        assert r.check_step() == 1
+        capture()
+        binding.ddgs_step_launch(r.ctx)
+        assert r.check_step() == 0
+        assert torch.equal(img, exp_img)
+    finally:
+        r.close()
