@@ -20,8 +20,8 @@
 //
 // Backward: the tail S_j = sum_{m>j} c_m s_m T_m is the saved pixel value
 // minus the running sum.  Per-pair image-plane gradients are summed over the
-// wave (on the matrix cores for chunked items, with DPP row operations for
-// unchunked ones), over the waves of the workgroup in LDS in a fixed order,
+// wave (through LDS for chunked items, with DPP row operations for unchunked
+// ones), over the waves of the workgroup in LDS in a fixed order,
 // and written once per tile entry into its own slot (the pair's first slot plus the tile's row-major
 // place in the pair's rectangle) -- no float atomics, so the gradients are
 // run-to-run deterministic.
@@ -724,8 +724,6 @@ __global__ __launch_bounds__(TW *TH) void raster_bwd_kernel(RasterArgs a)
     }
 }
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
 // Backward of chunked items.  Each wave owns an 8 x 8 part of the tile, one
 // lane per pixel, and runs the entries of its list (those whose cut-off box
 // reaches the part; with 8 x 8 tiles every entry of the item) in two sweeps
@@ -734,7 +732,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 //   front to back: G, s and gT = g T (g = dL/dC of the pixel) of every entry,
 //     the colour term g s T, and Sg = g times the tail S behind the eight;
 //   back to front: with B = S / T = the colour seen behind entry j,
-//     dL/ds_j = g T_j (c_j - B), then B <- B + s_j (c_j - B).
+//     dL/ds_j = g T_j (c_j - B), then B <- c_j - (1 - s_j) (c_j - B).
 // Only one division per eight entries is left (B behind the last, Sg /
 // gT); per entry it was v_rcp_f32 (8.4 clocks per wave here, against 2.4 of a
 // multiply) and three more operations.  Sg is a difference of colours of
@@ -743,32 +741,29 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // reaches dL/ds_j is eps g / (1 - s_j), as with the division per entry.
 //
 // The seven per-entry sums over the pixels: q = dL/ds G (zero where a pixel
-// misses an entry) goes to LDS for sixteen entries, and its moments about the
-// mean come from one dense contraction on the matrix cores: raw moments M_n =
-// sum_p q(p) P_n(p) of the pixel monomials P = (1, x, y, x^2, x y, y^2) about
-// the centre of each 4 x 4 quarter of the part, then shifted to each entry's
-// mean and added (about quarters, since a small Gaussian's moments lose bits in
-// the shift from a distant centre).  v_mfma_f32_4x4x1_16b takes one pixel of
-// four quarters x sixteen entries per step, the pixel's monomials broadcast
-// from one block of the A operand, and leaves lane (entry, quarter) with its
-// own moments in registers: 32 steps of about 10 clocks for the sixteen
-// entries, where sixteen v_mfma_f32_16x16x4 (6 of 16 columns used) took 525 and
-// another trip through LDS.  Matrix and vector instructions of a SIMD do not
-// overlap on this part (measured), so their clocks count like any others.  The
-// colour term is summed by a transposing butterfly over the wave.
+// misses an entry) goes to LDS for sixteen entries, and comes back with one
+// lane per (entry, 4 x 4 quarter of the part), which forms the quarter's
+// moments about its centre from its sixteen values in registers (43 additions
+// and multiply-adds), shifts them to the entry's mean and adds the quarters
+// over its lane row.  (About quarters, since a small Gaussian's moments lose
+// bits in the shift from a distant centre.)  The same moments as a dense
+// contraction on the matrix cores cost more: the monomials fill 6 of 8 columns
+// of v_mfma_f32_4x4x1 (32 steps of about 10 clocks; 169 us) or 6 of 16 of
+// v_mfma_f32_16x16x4 (525 clocks), matrix and vector instructions of a SIMD do
+// not overlap on this part (measured), and float32 split into three bf16 terms
+// spends on the split what the faster steps save (169 us).  The colour term is
+// summed by a transposing butterfly over the wave.
 //
 // Tiles of several waves: the waves share the staged records, and every
 // wave's sums go to LDS by entry, where the entry's lane adds the waves that
 // ran it in a fixed order.
 //
-// Measured (500k Gaussians / 512^2, tile sides 16 and 8): 219 and 170 us; the
-// general kernel above took 475 us at 16 x 16, the previous form of this one
-// (per-entry division, v_mfma_f32_16x16x4, 8 x 8 tiles only) 189 us.  Bound by
-// VALU and MFMA issue: about 100 clocks of a SIMD per entry and wave, of which
-// exponent and cut-off 40, compositing 20, contraction 21, colour sum 10.
-// Eight entries per sweep: 170 us, four 177 us.
+// Measured (500k Gaussians / 512^2, tile sides 16 and 8): 197 and 151 us; the
+// general kernel above took 475 us at 16 x 16, a former one with a division
+// per entry and v_mfma_f32_16x16x4 for 8 x 8 tiles 189 us.  Bound by VALU
+// issue.
 template <int TW, int TH>
-__global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TW * TH == 64 ? 5 : 4))) void raster_bwd_mm_kernel(RasterArgs a)
+__global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TW * TH == 64 ? 5 : 4))) void raster_bwd_parts_kernel(RasterArgs a)
 {
     constexpr int NT = TW * TH, NW = NT / kWave, GRP = 16, SWEEP = 8, PX = TW / 8;
     constexpr bool MULTI = NW > 1;
@@ -804,15 +799,6 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TW * TH 
         // d^T A d = -(dx^2 + dy^2) ~ -2e36, alpha = c = 0
         s0[BATCH] = make_float4(1e18f, 1e18f, -1.0f, 0.0f);
         s1[BATCH] = make_float4(-1.0f, 0.0f, 0.0f, 0.0f);
-    }
-    // monomials of pixel k of a quarter (k = lane / 4, monomial lane % 4 and
-    // 4 + lane % 4): block k of the A operand
-    float am0, am1;
-    {
-        const int k = lane >> 2, n = lane & 3;
-        const float x = (float)(k & 3) - 1.5f, y = (float)(k >> 2) - 1.5f;
-        am0 = n == 0 ? 1.0f : n == 1 ? x : n == 2 ? y : x * x;
-        am1 = n == 0 ? x * y : n == 1 ? y * y : 0.0f;
     }
     auto wave_sync = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -859,20 +845,28 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TW * TH 
             const float4 x2 = *reinterpret_cast<const float4 *>(qrow + 8), x3 = *reinterpret_cast<const float4 *>(qrow + 12);
             const int e = MULTI ? (int)(list[w][el] / 16u) : el;
             const float4 r0 = s0[e];
-            floatx4 A = {0.0f, 0.0f, 0.0f, 0.0f}, B = {0.0f, 0.0f, 0.0f, 0.0f};
-            // (the block of A to broadcast is an immediate)
-#define DDGS_MOMENTS(X, K)                                           \
-    A = __builtin_amdgcn_mfma_f32_4x4x1f32(am0, X, A, 4, K, 0);      \
-    B = __builtin_amdgcn_mfma_f32_4x4x1f32(am1, X, B, 4, K, 0)
-            DDGS_MOMENTS(x0.x, 0); DDGS_MOMENTS(x0.y, 1); DDGS_MOMENTS(x0.z, 2); DDGS_MOMENTS(x0.w, 3);
-            DDGS_MOMENTS(x1.x, 4); DDGS_MOMENTS(x1.y, 5); DDGS_MOMENTS(x1.z, 6); DDGS_MOMENTS(x1.w, 7);
-            DDGS_MOMENTS(x2.x, 8); DDGS_MOMENTS(x2.y, 9); DDGS_MOMENTS(x2.z, 10); DDGS_MOMENTS(x2.w, 11);
-            DDGS_MOMENTS(x3.x, 12); DDGS_MOMENTS(x3.y, 13); DDGS_MOMENTS(x3.z, 14); DDGS_MOMENTS(x3.w, 15);
-#undef DDGS_MOMENTS
-            // moments about the mean: with x = u + (x - u), u the mean's offset
+            // raw moments of the quarter's 4 x 4 pixels about its centre, in half
+            // pixels (X, Y = -3, -1, 1, 3): per pixel row the sums of q, q X and q
+            // X^2, then over the rows
+            float S[4], P[4], Q[4];
+            auto row = [](const float4 x, float &s_, float &p_, float &q_) {
+                const float o = x.x + x.w, i = x.y + x.z;
+                s_ = o + i;
+                p_ = __fmaf_rn(3.0f, x.w - x.x, x.z - x.y);
+                q_ = __fmaf_rn(9.0f, o, i);
+            };
+            row(x0, S[0], P[0], Q[0]);
+            row(x1, S[1], P[1], Q[1]);
+            row(x2, S[2], P[2], Q[2]);
+            row(x3, S[3], P[3], Q[3]);
+            const float so = S[0] + S[3], si = S[1] + S[2];
+            const float M0 = so + si, M1 = (P[0] + P[3]) + (P[1] + P[2]), M2 = __fmaf_rn(3.0f, S[3] - S[0], S[2] - S[1]);
+            const float M3 = (Q[0] + Q[3]) + (Q[1] + Q[2]), M4 = __fmaf_rn(3.0f, P[3] - P[0], P[2] - P[1]);
+            const float M5 = __fmaf_rn(9.0f, so, si);
+            // moments about the mean: with X = U + (X - U), U the mean's offset
             // from the quarter's centre
-            const float M0 = A[0], M1 = A[1], M2 = A[2], M3 = A[3], M4 = B[0], M5 = B[1];
-            const float ux = r0.x - (cx + ((qt & 1) ? 2.0f : -2.0f)), uy = r0.y - (cy + ((qt & 2) ? 2.0f : -2.0f));
+            const float ux = 2.0f * (r0.x - (cx + ((qt & 1) ? 2.0f : -2.0f)));
+            const float uy = 2.0f * (r0.y - (cy + ((qt & 2) ? 2.0f : -2.0f)));
             float m[6];
             m[0] = M1 - ux * M0;
             m[1] = M2 - uy * M0;
@@ -885,6 +879,11 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TW * TH 
                 m[t] += dpp_move<0x128>(m[t]);  // row_ror:8
                 m[t] += dpp_move<0x124>(m[t]);  // row_ror:4
             }
+            m[0] *= 0.5f;  // (from half pixels)
+            m[1] *= 0.5f;
+            m[2] *= 0.25f;
+            m[3] *= 0.25f;
+            m[4] *= 0.25f;
             if (qt == (lane & 3) && el < cnt) {
                 if constexpr (MULTI) {
                     float *const o = &acc_e[w][e][0];
@@ -913,7 +912,7 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TW * TH 
                 asm volatile("" : "+v"(qv));
 #pragma unroll
                 for (int h = 0; h < GRP; h += SWEEP) {
-                    float sv[SWEEP], rv[SWEEP], cv[SWEEP];
+                    float ov[SWEEP], rv[SWEEP], cv[SWEEP];
 #pragma unroll
                     for (int e2 = 0; e2 < SWEEP; e2 += 2) {
                         float4 R0[2], R1[2];
@@ -939,21 +938,20 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TW * TH 
                             const float ex = falloff_exponent(dx, dy, r0.z, r0.w, r1.x);
                             const bool hit = ex >= k2e;
                             const float G = hit ? __builtin_amdgcn_exp2f(ex) : 0.0f;
-                            const float sraw = __fmul_rn(r1.y, G);
-                            float s = sraw, om;
+                            float r = gT * G, t, om;
                             if constexpr (CLAMP) {
-                                s = clamp_opacity(sraw, smax);
+                                const float sraw = __fmul_rn(r1.y, G), s = clamp_opacity(sraw, smax);
                                 om = __fsub_rn(1.0f, s);
+                                t = gT * s;
+                                r = (sraw > smax) ? 0.0f : r;
                             } else {
                                 om = one_minus_alpha_g(r1.y, G);
+                                t = r1.y * r;
                             }
-                            const float t = gT * s;
                             Sg = __fmaf_rn(-r1.z, t, Sg);
-                            float r = gT * G;
-                            if constexpr (CLAMP) r = (sraw > smax) ? 0.0f : r;
                             gT = gT * om;
                             tv[h + e] = t;
-                            sv[e] = s;
+                            ov[e] = om;
                             rv[e] = r;
                             cv[e] = r1.z;
                         }
@@ -967,7 +965,7 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TW * TH 
 #pragma unroll
                     for (int e = SWEEP - 1; e >= 0; --e) {
                         const float d = cv[e] - Bk;
-                        Bk = __fmaf_rn(sv[e], d, Bk);
+                        Bk = __fmaf_rn(-ov[e], d, cv[e]);
                         aq[w][h + e][lane] = rv[e] * d;
                     }
                 }
@@ -1107,7 +1105,7 @@ hipError_t bwd_inst(const RasterArgs &a, int pb, hipStream_t s)
 {
     const int grid = a.queue_counter ? pb : round_up8(a.split ? a.max_items : a.n_tiles);
     if (grid > 0) {
-        if (a.split) raster_bwd_mm_kernel<TW, TH><<<grid, TW * TH, 0, s>>>(a);
+        if (a.split) raster_bwd_parts_kernel<TW, TH><<<grid, TW * TH, 0, s>>>(a);
         else raster_bwd_kernel<TW, TH><<<grid, TW * TH, 0, s>>>(a);
     }
     return hipGetLastError();
