@@ -494,7 +494,8 @@ __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const
 // order is that of the integer C = k 2^bi + i (bi = bits of the index span),
 // which is unique per entry.  The entries are bucketed by the top kBinBits
 // bits of C (a counting pass with LDS atomics; the order inside a bucket
-// does not matter), and each entry's final place is its bucket's start plus
+// does not matter), and each entry's final place is its bucket's start (the
+// cursor the bucket before it was left with) plus
 // the number of entries of its bucket with a smaller C.  Buckets hold a few
 // entries on average, so the ranking costs a few comparisons per entry (and
 // stays correct, if quadratic, for any distribution).  Ranges that fit the
@@ -502,7 +503,7 @@ __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const
 // second global buffer.
 // Two instances: ranges of up to 2560 entries with 512 threads per tile (the
 // per-tile phases are latency-bound: 512 measured 0.037 ms at 500k / 8x8
-// tiles, 256 0.045, 1024 0.053; four workgroups of 37 KB LDS per CU), and
+// tiles, 256 0.045, 1024 0.053; four workgroups of 29 KB LDS per CU), and
 // longer ranges, up to 7168 in LDS (two workgroups of 74 KB per CU), with
 // 1024 threads in a second launch.  Each launch leaves the other's tiles.
 constexpr int kSortShortBlock = 512;
@@ -514,14 +515,20 @@ constexpr int kSortLongGrid = 512;  // two workgroups per CU
 // (100k Gaussians / 251 x 187, 32 listed tiles of up to 7253 entries: 30 ->
 // 15 us).  With more tiles two smaller workgroups per CU are faster.
 constexpr int kSortLongBig = 14336, kSortLongBigGrid = 256;
-constexpr int kBinBits = 11;
-constexpr int kBins = 1 << kBinBits;
+// Buckets: 2048 for the short ranges, 4096 beyond: the LDS that a second array
+// of bucket starts took ranks longer ranges against half as many entries.
+// With both, and the block scans by DPP: short ranges 27 -> 23 us at 500k /
+// 512^2 and 254 -> 220 us at 64 views x 300k; long ranges 277 -> 236 us there
+// and 400 -> 341 us at 16 uneven views x 1M.
+template <int CAP>
+constexpr int kBinBits = CAP > kSortShort ? 12 : 11;
 
 template <int CAP, int BLOCK>
 struct SortLds {
     uint2 e[CAP];               // (key, index) in bucket order
-    uint32_t start[kBins];      // bucket starts
-    uint32_t cur[kBins];        // counts, then cursors (bucket ends at the last step)
+    // counts, then cursors: a bucket's entries placed, its cursor is its end
+    // and the next bucket's start
+    uint32_t cur[1 << kBinBits<CAP>];
     uint32_t wl[BLOCK / kWave];
     uint32_t red[4 * (BLOCK / kWave)];
 };
@@ -557,7 +564,7 @@ template <int CAP, int BLOCK>
 __device__ __forceinline__ void sort_tile(SortLds<CAP, BLOCK> &S, uint2 rg, const uint2 *ent, uint2 *tmp,
                                           uint32_t *tval)
 {
-    constexpr int kSortLds = CAP, kSortBlock = BLOCK, kSortWaves = BLOCK / kWave;
+    constexpr int kSortLds = CAP, kSortBlock = BLOCK, kSortWaves = BLOCK / kWave, kBins = 1 << kBinBits<CAP>;
     constexpr int kSortRegs = CAP / BLOCK;  // entries per thread held in registers
     const int len = (int)(rg.y - rg.x);
     const uint2 *g = ent + rg.x;
@@ -594,13 +601,10 @@ __device__ __forceinline__ void sort_tile(SortLds<CAP, BLOCK> &S, uint2 rg, cons
             imax = max(imax, y.y);
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, kWave));
-        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, kWave));
-        imin = min(imin, (uint32_t)__shfl_xor((int)imin, o, kWave));
-        imax = max(imax, (uint32_t)__shfl_xor((int)imax, o, kWave));
-    }
+    kmin = wave_min(kmin);
+    kmax = wave_max(kmax);
+    imin = wave_min(imin);
+    imax = wave_max(imax);
     const int lane = tid & (kWave - 1), w = tid / kWave;
     if (lane == 0) {
         S.red[w] = kmin;
@@ -619,7 +623,7 @@ __device__ __forceinline__ void sort_tile(SortLds<CAP, BLOCK> &S, uint2 rg, cons
     }
     const int bi = bit_length(imax - imin);
     const int total_bits = bit_length(kmax - kmin) + bi;
-    const int sh = total_bits > kBinBits ? total_bits - kBinBits : 0;
+    const int sh = total_bits > kBinBits<CAP> ? total_bits - kBinBits<CAP> : 0;
     auto code = [&](uint2 y) -> uint64_t {
         return ((uint64_t)(y.x - kmin) << bi) | (uint64_t)(y.y - imin);
     };
@@ -645,7 +649,6 @@ __device__ __forceinline__ void sort_tile(SortLds<CAP, BLOCK> &S, uint2 rg, cons
         uint32_t pre = sort_block_scan<BLOCK>(sum, S.wl, tot);
 #pragma unroll
         for (int q = 0; q < B; ++q) {
-            S.start[tid * B + q] = pre;
             S.cur[tid * B + q] = pre;
             pre += c[q];
         }
@@ -663,7 +666,7 @@ __device__ __forceinline__ void sort_tile(SortLds<CAP, BLOCK> &S, uint2 rg, cons
             if (tid + q * kSortBlock >= len) continue;
             const uint64_t cx = code(x[q]);
             const uint32_t b = (uint32_t)(cx >> sh);
-            const uint32_t s0 = S.start[b], e0 = S.cur[b];
+            const uint32_t s0 = b ? S.cur[b - 1] : 0u, e0 = S.cur[b];
             uint32_t r = s0;
             for (uint32_t p = s0; p < e0; ++p) r += code(S.e[p]) < cx ? 1u : 0u;
             tval[rg.x + r] = x[q].y;
@@ -680,7 +683,7 @@ __device__ __forceinline__ void sort_tile(SortLds<CAP, BLOCK> &S, uint2 rg, cons
             const uint2 y = buf[p];
             const uint64_t cy = code(y);
             const uint32_t b = (uint32_t)(cy >> sh);
-            const uint32_t s0 = S.start[b], e0 = S.cur[b];
+            const uint32_t s0 = b ? S.cur[b - 1] : 0u, e0 = S.cur[b];
             uint32_t r = s0;
             for (uint32_t q = s0; q < e0; ++q) r += code(buf[q]) < cy ? 1u : 0u;
             tval[rg.x + r] = y.y;

@@ -237,15 +237,48 @@ __device__ __forceinline__ float wave_transpose_sum16(float (&v)[16])
     return x;
 }
 
+// DPP move of a word: lanes without a source (or outside ROW_MASK) get `old`
+template <int CTRL, int ROW_MASK = 0xF>
+__device__ __forceinline__ uint32_t dpp_word(uint32_t old, uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROW_MASK, 0xF, false);
+}
+
+// Inclusive prefix sum over the wave's lanes: inside the rows of 16, then the
+// rows' totals into the rows behind.  Six VALU moves in a chain of about 50
+// clocks; through LDS (ds_bpermute) each step costs about 100, which the short
+// scan kernels and the per-tile sort waited for.
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
 {
-    const int lane = (int)__lane_id();
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        uint32_t y = __shfl_up(x, o, kWave);
-        if (lane >= o) x += y;
-    }
+    x += dpp_word<0x111>(0u, x);        // row_shr:1
+    x += dpp_word<0x112>(0u, x);        // row_shr:2
+    x += dpp_word<0x114>(0u, x);        // row_shr:4
+    x += dpp_word<0x118>(0u, x);        // row_shr:8
+    x += dpp_word<0x142, 0xA>(0u, x);   // row_bcast:15 into rows 1 and 3
+    x += dpp_word<0x143, 0xC>(0u, x);   // row_bcast:31 into rows 2 and 3
     return x;
+}
+
+// Smallest / largest value over the wave's lanes (the same in every lane).
+// Every lane of the wave must be active.
+template <class OP>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t x, OP op)
+{
+    x = op(x, dpp_word<0x111>(x, x));
+    x = op(x, dpp_word<0x112>(x, x));
+    x = op(x, dpp_word<0x114>(x, x));
+    x = op(x, dpp_word<0x118>(x, x));
+    x = op(x, dpp_word<0x142, 0xA>(x, x));
+    x = op(x, dpp_word<0x143, 0xC>(x, x));
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t x)
+{
+    return wave_reduce(x, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t x)
+{
+    return wave_reduce(x, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
 }
 
 // ---------------------------------------------------------------- launches
