@@ -75,6 +75,9 @@ struct ScanArgs {
     // long tiles (count > kSortShort): the list, its length, and per-block
     // counts of the three-launch scan
     uint32_t *long_list, *long_n, *long_bsum;
+    // pinned host words (null: none): the entry total (low, high word) and the
+    // number of long tiles, for a host that waits for this launch's end
+    uint32_t *host;
 };
 
 __device__ __forceinline__ uint32_t is_long(uint32_t cnt) { return cnt > (uint32_t)kSortShort ? 1u : 0u; }
@@ -113,6 +116,16 @@ __device__ void finish_scan(const ScanArgs &a, uint64_t t)
         // flags are cleared skips its optimiser updates
         if (f & 1u) *a.skipped = *a.skipped + 1u;
         if ((unsigned long long)t > *a.need) *a.need = (unsigned long long)t;
+    }
+}
+
+__device__ void finish_long(const ScanArgs &a, uint64_t t, uint32_t n_long)
+{
+    *a.long_n = n_long;
+    if (a.host) {
+        a.host[0] = (uint32_t)t;
+        a.host[1] = (uint32_t)(t >> 32);
+        a.host[2] = n_long;
     }
 }
 
@@ -188,7 +201,7 @@ __global__ __launch_bounds__(kBlock) void tile_scan_self_kernel(ScanArgs a)
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
         finish_scan(a, carry + tot);
-        *a.long_n = lcarry + ltot;
+        finish_long(a, carry + tot, lcarry + ltot);
         if (sp) {
             const uint32_t ni = icarry + itot;
             *a.n_items = ni > a.max_items ? a.max_items : ni;
@@ -300,7 +313,7 @@ __global__ __launch_bounds__(1024) void tile_top_kernel(uint64_t *bsum, uint32_t
     }
     if (threadIdx.x == 0) {
         finish_scan(a, carry_s);
-        *a.long_n = lcarry_s;
+        finish_long(a, carry_s, lcarry_s);
     }
 }
 
@@ -701,7 +714,8 @@ __device__ __forceinline__ void sort_tile(SortLds<CAP, BLOCK> &S, uint2 rg, cons
 // bucketed in global memory by this launch's workgroup).
 template <int CAP, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void tile_sort_kernel(const uint2 *ranges, const uint32_t *tile_cnt, int n_tiles,
-                                                          const uint2 *ent, uint2 *tmp, uint32_t *tval, int take_long)
+                                                          const uint2 *ent, uint2 *tmp, uint32_t *tval,
+                                                          uint32_t capacity, int take_long)
 {
     static_assert(CAP >= kSortShort, "short ranges are sorted in LDS");
     __shared__ SortLds<CAP, BLOCK> S;
@@ -709,7 +723,7 @@ __global__ __launch_bounds__(BLOCK) void tile_sort_kernel(const uint2 *ranges, c
     if (tile >= n_tiles) return;
     const uint32_t cnt = tile_cnt[tile];  // (both loads in flight together)
     const uint2 rg = ranges[tile];
-    if ((is_long(cnt) && !take_long) || rg.y <= rg.x) return;
+    if ((is_long(cnt) && !take_long) || rg.y <= rg.x || rg.y > capacity) return;
     sort_tile<CAP, BLOCK>(S, rg, ent, tmp, tval);
 }
 
@@ -844,7 +858,7 @@ hipError_t launch_bin_small(int n, int V, const uint32_t *cnt, const uint2 *rect
     if (!bin_small(n, V, n_tiles) || slot_nb > kSmallSlotBlocks || !lt.list || !lt.n) return hipErrorInvalidValue;
     const BinArgs b{n, V, 1, n, cnt, rect, tmask, zkey, views, nullptr};
     ScanArgs a{tile_cnt, n_tiles, ranges, cursor, capacity, total, m_out, flags, skipped, need, slot_btot, slot_nb,
-               0u, nullptr, nullptr, nullptr, 0u, nullptr, nullptr, lt.list, lt.n, lt.bsum};
+               0u, nullptr, nullptr, nullptr, 0u, nullptr, nullptr, lt.list, lt.n, lt.bsum, nullptr};
     if (it && it->split > 0) {
         a.split = (uint32_t)it->split;
         a.item_cnt = it->cnt;
@@ -865,10 +879,10 @@ hipError_t launch_tile_scan(const uint32_t *tile_cnt, int n_tiles, uint2 *ranges
                             uint32_t capacity, uint64_t *total, uint32_t *m_out, uint32_t *flags,
                             uint32_t *skipped, unsigned long long *need, uint32_t *slot_btot, int64_t slot_nb,
                             uint32_t *slot_ssum, size_t slot_ssum_words, uint64_t *bsum, size_t bsum_words,
-                            const TileItems *it, const LongTiles &lt, hipStream_t s)
+                            const TileItems *it, const LongTiles &lt, uint32_t *host, hipStream_t s)
 {
     ScanArgs a{tile_cnt, n_tiles, ranges, cursor, capacity, total, m_out, flags, skipped, need, slot_btot, slot_nb,
-               0u, nullptr, nullptr, nullptr, 0u, nullptr, nullptr, lt.list, lt.n, lt.bsum};
+               0u, nullptr, nullptr, nullptr, 0u, nullptr, nullptr, lt.list, lt.n, lt.bsum, host};
     if (!lt.list || !lt.n) return hipErrorInvalidValue;
     const int nb = (n_tiles + kBlock - 1) / kBlock;
     if (n_tiles <= kTileScanSelfMax) {
@@ -946,13 +960,19 @@ hipError_t launch_bin_scatter(int n, int V, const uint32_t *cnt, const uint2 *re
 }
 
 hipError_t launch_tile_sort(const uint2 *ranges, const uint32_t *tile_cnt, int n_tiles, const uint2 *ent, uint2 *tmp,
-                            uint32_t *tval, const LongTiles &lt, int long_grid, hipStream_t s)
+                            uint32_t *tval, uint32_t capacity, bool take_long, hipStream_t s)
 {
     if (n_tiles <= 0) return hipSuccess;
+    tile_sort_kernel<kSortShort, kSortShortBlock><<<n_tiles, kSortShortBlock, 0, s>>>(
+        ranges, tile_cnt, n_tiles, ent, tmp, tval, capacity, take_long ? 1 : 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_tile_sort_long(const uint2 *ranges, int n_tiles, const uint2 *ent, uint2 *tmp, uint32_t *tval,
+                                 const LongTiles &lt, int long_grid, hipStream_t s)
+{
     const int g = std::min(std::min(n_tiles, kSortLongGrid), long_grid);
-    tile_sort_kernel<kSortShort, kSortShortBlock><<<n_tiles, kSortShortBlock, 0, s>>>(ranges, tile_cnt, n_tiles, ent,
-                                                                                       tmp, tval, g <= 0 ? 1 : 0);
-    if (g <= 0) return hipGetLastError();
+    if (g <= 0) return hipSuccess;
     if (g <= kSortLongBigGrid)
         tile_sort_long_kernel<kSortLongBig, kSortLongBlock><<<g, kSortLongBlock, 0, s>>>(ranges, ent, tmp, tval,
                                                                                           lt.list, lt.n);

@@ -131,6 +131,11 @@ struct ddgs_ctx {
     // target image of the captured step's loss (uploaded with the view table)
     const float *step_target = nullptr;
 
+    // entry total and number of long tiles of a plain render, written by its tile
+    // scan to pinned host memory, and the event behind that launch
+    uint32_t *total_host = nullptr;
+    hipEvent_t total_event = nullptr;
+
     // pinned staging of the view table uploads
     void *stage_host = nullptr;
     size_t stage_bytes = 0;
@@ -641,31 +646,45 @@ ddgs_status enqueue_front(ddgs_ctx *c, uint32_t capacity, bool captured, bool sm
                                 captured ? skipped_ptr(c) : nullptr, captured ? need_ptr(c) : nullptr,
                                 buf<uint32_t>(c, "slot_btot"), (int64_t)V * slot_blocks(m.n),
                                 buf<uint32_t>(c, "slot_ssum"), c->bufs["slot_ssum"].bytes / sizeof(uint32_t), buf<uint64_t>(c, "tile_bsum"),
-                                c->bufs["tile_bsum"].bytes / sizeof(uint64_t), fold ? &ti : nullptr, long_tiles(c), s));
+                                c->bufs["tile_bsum"].bytes / sizeof(uint64_t), fold ? &ti : nullptr, long_tiles(c),
+                                captured ? nullptr : c->total_host, s));
     // the sort stage is timed in two parts: a plain render reads the entry
     // total back to the host between them, and that round trip is not device work
     stage_end(c, DDGS_T_SORT);
     return DDGS_OK;
 }
 
-// Scatter of the entries into their tile ranges, the per-tile sort, the
+// Scatter of the entries into their tile ranges and the per-tile sort of all
+// but the long tiles (with take_long: of those too).  cap: what the entry
+// buffers hold; entries and ranges beyond it are left out.
+ddgs_status enqueue_sort_head(ddgs_ctx *c, int64_t cap, bool take_long)
+{
+    hipStream_t s = c->stream;
+    const uint32_t cap32 = (uint32_t)std::min<int64_t>(cap, 0xFFFFFFFFll);
+    uint2 *ent = buf<uint2>(c, "bin_ent");
+    if (!c->binned)
+        HIP_TRY(c, launch_bin_scatter((int)c->model.n, (int)c->views_h.size(), buf<uint32_t>(c, "cnt"),
+                                      buf<uint2>(c, "rect"), buf<uint32_t>(c, "tmask"), buf<uint32_t>(c, "zkey"),
+                                      buf<ViewDev>(c, "views"), c->n_tiles, c->max_view_tiles,
+                                      buf<uint32_t>(c, "bin_mat"), buf<uint32_t>(c, "cursor"), cap32, ent, s));
+    if (c->keep_unsorted)
+        HIP_TRY(c, launch_copy_u32((uint32_t *)buf<uint2>(c, "ubin"), (const uint32_t *)ent, nullptr, 2 * cap, s));
+    HIP_TRY(c, launch_tile_sort(buf<uint2>(c, "ranges"), buf<uint32_t>(c, "tile_cnt"), c->n_tiles, ent,
+                                buf<uint2>(c, "bin_tmp"), buf<uint32_t>(c, "tval"), cap32, take_long, s));
+    return DDGS_OK;
+}
+
+// The scatter and sort (head: not enqueued yet), the long tiles' sort, the
 // optional work items or queue, and the forward raster.
-ddgs_status enqueue_back(ddgs_ctx *c, int64_t cap, float *images)
+ddgs_status enqueue_back(ddgs_ctx *c, int64_t cap, float *images, bool head = true)
 {
     hipStream_t s = c->stream;
     const int V = (int)c->views_h.size();
     const int n = (int)c->model.n;
-    uint2 *ent = buf<uint2>(c, "bin_ent");
     if (c->timing) (void)hipEventRecord(c->ev_sort_tail_s, c->stream);
-    if (!c->binned)
-        HIP_TRY(c, launch_bin_scatter(n, V, buf<uint32_t>(c, "cnt"), buf<uint2>(c, "rect"), buf<uint32_t>(c, "tmask"),
-                                      buf<uint32_t>(c, "zkey"), buf<ViewDev>(c, "views"), c->n_tiles,
-                                      c->max_view_tiles, buf<uint32_t>(c, "bin_mat"), buf<uint32_t>(c, "cursor"),
-                                      (uint32_t)cap, ent, s));
-    if (c->keep_unsorted)
-        HIP_TRY(c, launch_copy_u32((uint32_t *)buf<uint2>(c, "ubin"), (const uint32_t *)ent, nullptr, 2 * cap, s));
-    HIP_TRY(c, launch_tile_sort(buf<uint2>(c, "ranges"), buf<uint32_t>(c, "tile_cnt"), c->n_tiles, ent,
-                                buf<uint2>(c, "bin_tmp"), buf<uint32_t>(c, "tval"), long_tiles(c), c->long_grid, s));
+    if (head) DDGS_TRY(enqueue_sort_head(c, cap, c->long_grid <= 0));
+    HIP_TRY(c, launch_tile_sort_long(buf<uint2>(c, "ranges"), c->n_tiles, buf<uint2>(c, "bin_ent"),
+                                     buf<uint2>(c, "bin_tmp"), buf<uint32_t>(c, "tval"), long_tiles(c), c->long_grid, s));
     c->queue = nullptr;
     const int split = effective_split(c);
     c->max_items = (int)max_items_for(c, cap);
@@ -948,7 +967,8 @@ ddgs_status ddgs_create(ddgs_ctx **out, int device, void *hip_stream)
         ddgs_destroy(c);
         return DDGS_ERR_HIP;
     }
-    if (hipEventCreateWithFlags(&c->stage_event, hipEventDisableTiming) != hipSuccess) {
+    if (hipEventCreateWithFlags(&c->stage_event, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&c->total_event, hipEventDisableTiming) != hipSuccess) {
         ddgs_destroy(c);
         return DDGS_ERR_HIP;
     }
@@ -973,7 +993,9 @@ void ddgs_destroy(ddgs_ctx *c)
     if (c->ev_sort_tail_s) (void)hipEventDestroy(c->ev_sort_tail_s);
     if (c->ev_sort_tail_e) (void)hipEventDestroy(c->ev_sort_tail_e);
     if (c->stage_event) (void)hipEventDestroy(c->stage_event);
+    if (c->total_event) (void)hipEventDestroy(c->total_event);
     if (c->stage_host) (void)hipHostFree(c->stage_host);
+    if (c->total_host) (void)hipHostFree(c->total_host);
     delete c;
 }
 
@@ -1520,13 +1542,26 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
         c->long_grid = c->model.n > kSortShort ? 1 << 30 : 0;
         DDGS_TRY(enqueue_back(c, worst, images));
     } else if (VN > 0) {
+        if (!c->total_host)
+            HIP_TRY(c, hipHostMalloc((void **)&c->total_host, 4 * sizeof(uint32_t), hipHostMallocCoherent));
         DDGS_TRY(enqueue_front(c, 0xFFFFFFFFu, false, false));
-        // entry total ([0..1]) and number of long tiles ([12])
-        uint32_t sc[13] = {};
-        HIP_TRY(c, hipMemcpyAsync(sc, total_ptr(c), sizeof(sc), hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        HIP_TRY(c, hipEventRecord(c->total_event, c->stream));
+        // While the host waits for the entry total, the card scatters and sorts
+        // into the buffers that an earlier render sized (what lies beyond
+        // them is left out); only a render that needs larger ones runs both again.
+        // (Waiting first left the card idle for the copy, the round trip and the
+        // launches behind it: 500k Gaussians / 512^2 205 -> 172 us, 100k /
+        // 251 x 187 through autograd 325 -> 266 us.)  Not with stage timing,
+        // whose stages hold device work only.
+        const int64_t held = std::min<int64_t>({(int64_t)(c->bufs["bin_ent"].bytes / sizeof(uint2)),
+                                                (int64_t)(c->bufs["bin_tmp"].bytes / sizeof(uint2)),
+                                                (int64_t)(c->bufs["tval"].bytes / sizeof(uint32_t)), 0xFFFFFFFEll});
+        bool ahead = c->entry_cap > 1 && !c->timing && !c->keep_unsorted;
+        if (ahead) DDGS_TRY(enqueue_sort_head(c, held, false));
+        HIP_TRY(c, hipEventSynchronize(c->total_event));
+        const uint32_t *const sc = c->total_host;
         const uint64_t total = (uint64_t)sc[0] | ((uint64_t)sc[1] << 32);
-        const int64_t n_long = sc[12];
+        const int64_t n_long = sc[2];
         if (c->long_seen_n != c->model.n || c->long_seen_tiles != c->n_tiles) c->long_seen = -1;
         c->long_seen = std::max(c->long_seen, n_long);
         c->long_seen_n = c->model.n;
@@ -1543,7 +1578,8 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
         // (the exact total bounds the work items, so the raster grids take
         // no more workgroups than this render can fill; the buffers keep
         // entry_cap)
-        DDGS_TRY(enqueue_back(c, std::max<int64_t>(c->M, 1), images));
+        if (c->M > held) ahead = false;
+        DDGS_TRY(enqueue_back(c, std::max<int64_t>(c->M, 1), images, !ahead));
     } else {
         // no Gaussians: empty lists everywhere
         c->M = 0;

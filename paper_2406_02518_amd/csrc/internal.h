@@ -380,7 +380,8 @@ hipError_t launch_ranges(const uint32_t *keys, const uint32_t *m_dev, int64_t m_
 // [slot_ssum_words(slot_nb)] scratch).
 // With `items` (only where tile_scan_makes_items: the one-launch scan), the
 // same launch also writes the work items of `split` entries per tile (what
-// launch_items writes).
+// launch_items writes).  host (or NULL): three pinned host words for the entry
+// total and the number of long tiles, valid once the launch has ended.
 constexpr int kTileScanSelfMax = 16384;
 constexpr int kSortShort = 2560;  // longest range the per-tile sort's first launch takes
 struct TileItems {
@@ -404,7 +405,7 @@ hipError_t launch_tile_scan(const uint32_t *tile_cnt, int n_tiles, uint2 *ranges
                             uint32_t capacity, uint64_t *total, uint32_t *m_out, uint32_t *flags,
                             uint32_t *skipped, unsigned long long *need, uint32_t *slot_btot, int64_t slot_nb,
                             uint32_t *slot_ssum, size_t slot_ssum_words, uint64_t *bsum, size_t bsum_words,
-                            const TileItems *items, const LongTiles &lt, hipStream_t s);
+                            const TileItems *items, const LongTiles &lt, uint32_t *host, hipStream_t s);
 // Per-tile entry counts without global atomics: groups of Gaussians of each
 // view count their entries per tile in LDS into a count matrix mat
 // ([bin_matrix_words] u32), whose columns are then scanned into every
@@ -432,13 +433,17 @@ hipError_t launch_bin_small(int n, int V, const uint32_t *cnt, const uint2 *rect
                             int64_t slot_nb, const TileItems *items, const LongTiles &lt, uint2 *out, hipStream_t s);
 // Sorts every tile's range of ent by (depth key, index) and writes the
 // indices to tval; tmp (same layout as ent) is scratch for ranges longer than
-// the LDS holds.  tile_cnt and lt are those the tile scan of the same step
-// used (the long tiles go to a second launch of at most long_grid
-// workgroups, each taking the listed tiles round-robin; with long_grid 0
-// there is no second launch and the first one sorts the long tiles too,
-// through global memory: meant for steps that rarely or never have any).
+// the LDS holds.  tile_cnt is the tile scan's of the same step.  Ranges that
+// end beyond capacity are left alone.  Long tiles (lt, listed by the tile scan)
+// are left to launch_tile_sort_long unless take_long is set: then this launch
+// sorts them too, through global memory (meant for steps that rarely or never
+// have any).
 hipError_t launch_tile_sort(const uint2 *ranges, const uint32_t *tile_cnt, int n_tiles, const uint2 *ent, uint2 *tmp,
-                            uint32_t *tval, const LongTiles &lt, int long_grid, hipStream_t s);
+                            uint32_t *tval, uint32_t capacity, bool take_long, hipStream_t s);
+// The listed long tiles, taken round-robin by at most long_grid workgroups
+// (none: no launch).
+hipError_t launch_tile_sort_long(const uint2 *ranges, int n_tiles, const uint2 *ent, uint2 *tmp, uint32_t *tval,
+                                 const LongTiles &lt, int long_grid, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_zero_u64(uint64_t *p, hipStream_t s);
 hipError_t launch_copy_u32(uint32_t *dst, const uint32_t *src, const uint32_t *n_dev, int64_t n_cap,

@@ -101,3 +101,25 @@ def test_small_captured_step_equals_the_plain_path(n):
         assert torch.equal(img, exp_img)
     finally:
         r.close()
+
+
+@pytest.mark.parametrize("opts", [dict(tile_w=16, tile_h=16, split=256), dict(tile_w=8, tile_h=8, split=64),
+                                  dict(tile_w=16, tile_h=8, split=0, persistent=1)])
+def test_renders_after_smaller_and_larger_ones(opts):
+    """A plain render scatters and sorts into the buffers that earlier renders
+    sized before it knows its entry total: totals within their spare room,
+    beyond it, and smaller ones again, ranges of long tiles, and more tiles than
+    the one-launch scan takes, each equal to a fresh renderer's first render."""
+    a = make_renderer()
+    try:
+        for n, w, h, V in [(9000, 60, 52, 1), (9900, 60, 52, 1), (40000, 60, 52, 1), (9000, 60, 52, 2),
+                           (60000, 33, 20, 1), (60000, 1100, 1000, 1), (9000, 17, 16, 1)]:
+            sc = synth.random_scene(17, n, k=4, L=1, extent=18.0, std_range=(0.3, 1.5))
+            views = _views(V, w, h)
+            b = make_renderer()
+            got, exp = _lists(a, sc, views, opts), _lists(b, sc, views, opts)
+            b.close()
+            for x, y in zip(got, exp):
+                np.testing.assert_array_equal(x, y)
+    finally:
+        a.close()
