@@ -477,6 +477,11 @@ __global__ __launch_bounds__(kColTiles *kColBlocks) void bin_colscan_kernel(BinA
 // g - 1, so XCD x takes the x-th contiguous eighth of the groups: the
 // partial cache lines that consecutive groups write into one range are then
 // completed in one L2 instead of across XCDs.  gridDim.x is a multiple of 8.
+// What is read is read once and passes the L2 by (non-temporal loads), which
+// leaves it to those lines: 743 -> 703 us at 16 uneven views x 1M (40 M writes
+// to memory for 65 M entries), 387 -> 375 us at 64 views x 300k.  Windows of
+// 2048 tiles bring the writes to 24 M there, but the passes over the pairs
+// they add cost more (785 us).
 __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const uint32_t *start, uint32_t capacity,
                                                                 uint2 *out)
 {
@@ -491,14 +496,16 @@ __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const
     const int t1 = min(Tv, t0 + kWin), nt = t1 - t0;
     const uint32_t *row = a.mat + (size_t)a.groups * V.tile_base + (size_t)g * Tv + t0;
     const uint32_t *st = start + V.tile_base + t0;
-    for (int j = threadIdx.x; j < nt; j += kBinBlock) cur[j] = st[j] + row[j];
+    for (int j = threadIdx.x; j < nt; j += kBinBlock) cur[j] = st[j] + __builtin_nontemporal_load(row + j);
     __syncthreads();
     const int i0 = g * a.per, i1 = min(a.n, i0 + a.per);
     for (int i = i0 + (int)threadIdx.x; i < i1; i += kBinBlock) {
         const int64_t r = (int64_t)v * a.n + i;
-        if (a.cnt[r] == 0u) continue;
-        const uint32_t key = a.zkey[r];
-        for_tiles(a.rect[r], a.tmask[r], V.ntx, t0, t1, [&](int lt) {
+        if (__builtin_nontemporal_load(a.cnt + r) == 0u) continue;
+        const uint32_t key = __builtin_nontemporal_load(a.zkey + r);
+        const uint64_t rc = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(a.rect) + r);
+        const uint32_t mask = __builtin_nontemporal_load(a.tmask + r);
+        for_tiles(make_uint2((uint32_t)rc, (uint32_t)(rc >> 32)), mask, V.ntx, t0, t1, [&](int lt) {
             const uint32_t p = atomicAdd(&cur[lt - t0], 1u);
             if (p < capacity) out[p] = make_uint2(key, (uint32_t)i);
         });
