@@ -383,6 +383,8 @@ __device__ __forceinline__ void for_tiles(uint2 rc, uint32_t mask, int ntx, int 
 // in flight to hide the latency of its reads and LDS atomics)
 constexpr int kBinBlock = 1024;
 
+// U: a thread's pairs loaded together.
+template <int U>
 __global__ __launch_bounds__(kBinBlock) void bin_count_kernel(BinArgs a)
 {
     extern __shared__ uint32_t hist[];
@@ -394,10 +396,20 @@ __global__ __launch_bounds__(kBinBlock) void bin_count_kernel(BinArgs a)
     for (int j = threadIdx.x; j < nt; j += kBinBlock) hist[j] = 0u;
     __syncthreads();
     const int i0 = g * a.per, i1 = min(a.n, i0 + a.per);
-    for (int i = i0 + (int)threadIdx.x; i < i1; i += kBinBlock) {
-        const int64_t r = (int64_t)v * a.n + i;
-        if (a.cnt[r] == 0u) continue;
-        for_tiles(a.rect[r], a.tmask[r], V.ntx, t0, t1, [&](int lt) { atomicAdd(&hist[lt - t0], 1u); });
+    for (int i = i0 + (int)threadIdx.x; i < i1; i += U * kBinBlock) {
+        uint32_t cnt[U], mask[U];
+        uint2 rc[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t r = (int64_t)v * a.n + min(i + u * kBinBlock, i1 - 1);
+            cnt[u] = i + u * kBinBlock < i1 ? a.cnt[r] : 0u;
+            rc[u] = a.rect[r];
+            mask[u] = a.tmask[r];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (cnt[u] != 0u)
+                for_tiles(rc[u], mask[u], V.ntx, t0, t1, [&](int lt) { atomicAdd(&hist[lt - t0], 1u); });
     }
     __syncthreads();
     uint32_t *row = a.mat + (size_t)a.groups * V.tile_base + (size_t)g * Tv + t0;
@@ -478,10 +490,11 @@ __global__ __launch_bounds__(kColTiles *kColBlocks) void bin_colscan_kernel(BinA
 // partial cache lines that consecutive groups write into one range are then
 // completed in one L2 instead of across XCDs.  gridDim.x is a multiple of 8.
 // What is read is read once and passes the L2 by (non-temporal loads), which
-// leaves it to those lines: 743 -> 703 us at 16 uneven views x 1M (40 M writes
+// leaves it to those lines: 743 -> 703 us at 16 uneven views x 1M (37 M writes
 // to memory for 65 M entries), 387 -> 375 us at 64 views x 300k.  Windows of
 // 2048 tiles bring the writes to 24 M there, but the passes over the pairs
 // they add cost more (785 us).
+template <int U>
 __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const uint32_t *start, uint32_t capacity,
                                                                 uint2 *out)
 {
@@ -499,16 +512,26 @@ __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const
     for (int j = threadIdx.x; j < nt; j += kBinBlock) cur[j] = st[j] + __builtin_nontemporal_load(row + j);
     __syncthreads();
     const int i0 = g * a.per, i1 = min(a.n, i0 + a.per);
-    for (int i = i0 + (int)threadIdx.x; i < i1; i += kBinBlock) {
-        const int64_t r = (int64_t)v * a.n + i;
-        if (__builtin_nontemporal_load(a.cnt + r) == 0u) continue;
-        const uint32_t key = __builtin_nontemporal_load(a.zkey + r);
-        const uint64_t rc = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(a.rect) + r);
-        const uint32_t mask = __builtin_nontemporal_load(a.tmask + r);
-        for_tiles(make_uint2((uint32_t)rc, (uint32_t)(rc >> 32)), mask, V.ntx, t0, t1, [&](int lt) {
-            const uint32_t p = atomicAdd(&cur[lt - t0], 1u);
-            if (p < capacity) out[p] = make_uint2(key, (uint32_t)i);
-        });
+    for (int i = i0 + (int)threadIdx.x; i < i1; i += U * kBinBlock) {
+        uint32_t cnt[U], mask[U], key[U];
+        uint64_t rc[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t r = (int64_t)v * a.n + min(i + u * kBinBlock, i1 - 1);
+            cnt[u] = i + u * kBinBlock < i1 ? __builtin_nontemporal_load(a.cnt + r) : 0u;
+            key[u] = __builtin_nontemporal_load(a.zkey + r);
+            rc[u] = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(a.rect) + r);
+            mask[u] = __builtin_nontemporal_load(a.tmask + r);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (cnt[u] == 0u) continue;
+            const uint2 rect = make_uint2((uint32_t)rc[u], (uint32_t)(rc[u] >> 32));
+            for_tiles(rect, mask[u], V.ntx, t0, t1, [&](int lt) {
+                const uint32_t p = atomicAdd(&cur[lt - t0], 1u);
+                if (p < capacity) out[p] = make_uint2(key[u], (uint32_t)(i + u * kBinBlock));
+            });
+        }
     }
 }
 
@@ -915,18 +938,23 @@ hipError_t launch_tile_scan(const uint32_t *tile_cnt, int n_tiles, uint2 *ranges
     return hipGetLastError();
 }
 
-// Gaussians per group: at least 1024 (one per thread of the count and
-// scatter workgroups; with the XCD-ordered groups 1024 measured 0.024 ms for
-// the scatter at 500k Gaussians / 8x8 tiles against 0.036 ms for 2048), and
-// few enough groups that the count matrix stays within kMatWords words
-// (256 MB; with many views the cap sets the group size: at 1M Gaussians and
-// 96256 tiles a cap of 8M words made groups of 16k and the scatter took
-// 1.21 ms, 64M words 0.96 ms, the 64-pose batch 8.33 -> 8.10 ms per step).
+// Gaussians per group: 1024 (one per thread of the count and scatter
+// workgroups; with the XCD-ordered groups 1024 measured 0.024 ms for the
+// scatter at 500k Gaussians / 8x8 tiles against 0.036 ms for 2048, and 376
+// against 518 us at 64 views x 300k) as long as the count matrix stays within
+// kMatWords words (256 MB); with more tiles 4096, four pairs in flight per
+// thread (16 uneven views x 1M, 90k tiles: count, column scan and scatter 117 +
+// 56 + 663 us, against 155 + 120 + 703 us for 2048 one at a time: the matrix
+// is half as large), and beyond that as many as the limit takes (groups of 16k
+// there: the scatter alone 1.21 ms).
 constexpr int64_t kMatWords = (int64_t)64 << 20;
+constexpr int kPerLarge = 4 * kBinBlock;
 int bin_per_group(int64_t n, int64_t n_tiles)
 {
-    int64_t per = 1024;
-    while (per < n && ((n + per - 1) / per) * std::max<int64_t>(n_tiles, 1) > kMatWords) per *= 2;
+    auto fits = [&](int64_t per) { return ((n + per - 1) / per) * std::max<int64_t>(n_tiles, 1) <= kMatWords; };
+    if (n <= kBinBlock || fits(kBinBlock)) return kBinBlock;
+    int64_t per = kPerLarge;
+    while (per < n && !fits(per)) per *= 2;
     return (int)per;
 }
 
@@ -946,7 +974,9 @@ hipError_t launch_bin_count(int n, int V, const uint32_t *cnt, const uint2 *rect
     BinArgs a{n, V, (n + per - 1) / per, per, cnt, rect, tmask, nullptr, views, mat};
     const int wins = (max_view_tiles + kWin - 1) / kWin;
     const size_t lds = sizeof(uint32_t) * std::min(max_view_tiles, kWin);
-    bin_count_kernel<<<dim3(a.groups, V, wins), kBinBlock, lds, s>>>(a);
+    const dim3 grid(a.groups, V, wins);
+    if (per >= kPerLarge) bin_count_kernel<4><<<grid, kBinBlock, lds, s>>>(a);
+    else bin_count_kernel<1><<<grid, kBinBlock, lds, s>>>(a);
     bin_colscan_kernel<<<(n_tiles + kColTiles - 1) / kColTiles, kColTiles * kColBlocks, 0, s>>>(a, n_tiles, tile_cnt);
     return hipGetLastError();
 }
@@ -962,7 +992,9 @@ hipError_t launch_bin_scatter(int n, int V, const uint32_t *cnt, const uint2 *re
     BinArgs a{n, V, (n + per - 1) / per, per, cnt, rect, tmask, zkey, views, const_cast<uint32_t *>(mat)};
     const int wins = (max_view_tiles + kWin - 1) / kWin;
     const size_t lds = sizeof(uint32_t) * std::min(max_view_tiles, kWin);
-    bin_scatter_kernel<<<dim3((a.groups + 7) / 8 * 8, V, wins), kBinBlock, lds, s>>>(a, start, capacity, out);
+    const dim3 grid((a.groups + 7) / 8 * 8, V, wins);
+    if (per >= kPerLarge) bin_scatter_kernel<4><<<grid, kBinBlock, lds, s>>>(a, start, capacity, out);
+    else bin_scatter_kernel<1><<<grid, kBinBlock, lds, s>>>(a, start, capacity, out);
     return hipGetLastError();
 }
 

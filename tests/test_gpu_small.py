@@ -123,3 +123,32 @@ def test_renders_after_smaller_and_larger_ones(opts):
                 np.testing.assert_array_equal(x, y)
     finally:
         a.close()
+
+
+def test_groups_of_many_tiles_equal_single_views():
+    """Gaussians x tiles beyond the count matrix of 1024-Gaussian groups: the
+    batch's larger groups (with a partial last one) give every view the image
+    and the lists that it gets alone, where the groups are the smaller ones."""
+    n, opts = 200001, dict(tile_w=8, tile_h=8, split=256)
+    sc = synth.random_scene(23, n, k=4, L=1, extent=60.0, std_range=(0.05, 0.3))
+    views = [synth.view(1900 - 3 * j, 1880, 0.12, 1000.0, 600.0, 25.0 * j) for j in range(7)]
+    tiles = [-(-v.W // 8) * -(-v.H // 8) for v in views]
+    assert -(-n // 1024) * sum(tiles) > 64 << 20 > -(-n // 1024) * max(tiles)
+    r = make_renderer()
+    try:
+        r.set_options(**opts)
+        r.set_scene(sc)
+        r.set_views(views)
+        imgs = [x.clone() for x in r.split(r.render())]
+        M = r.num_rendered()
+        vals = r.debug(binding.DBG_TILE_VALS, np.uint32, M)
+        at = 0
+        for v, img in zip(views, imgs):
+            r.set_views([v])
+            assert torch.equal(r.split(r.render())[0], img)
+            m = r.num_rendered()
+            np.testing.assert_array_equal(r.debug(binding.DBG_TILE_VALS, np.uint32, m), vals[at:at + m])
+            at += m
+        assert at == M and M > n
+    finally:
+        r.close()
