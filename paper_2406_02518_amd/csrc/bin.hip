@@ -383,7 +383,9 @@ __device__ __forceinline__ void for_tiles(uint2 rc, uint32_t mask, int ntx, int 
 // in flight to hide the latency of its reads and LDS atomics)
 constexpr int kBinBlock = 1024;
 
-// U: a thread's pairs loaded together.
+// U: a thread's pairs loaded together; the first ones before the counters are
+// cleared (a workgroup lives for a few memory latencies: 151 -> 115 us at
+// 64 views x 300k).
 template <int U>
 __global__ __launch_bounds__(kBinBlock) void bin_count_kernel(BinArgs a)
 {
@@ -393,12 +395,10 @@ __global__ __launch_bounds__(kBinBlock) void bin_count_kernel(BinArgs a)
     const int Tv = V.ntx * V.nty, t0 = w * kWin;
     if (t0 >= Tv) return;
     const int t1 = min(Tv, t0 + kWin), nt = t1 - t0;
-    for (int j = threadIdx.x; j < nt; j += kBinBlock) hist[j] = 0u;
-    __syncthreads();
     const int i0 = g * a.per, i1 = min(a.n, i0 + a.per);
-    for (int i = i0 + (int)threadIdx.x; i < i1; i += U * kBinBlock) {
-        uint32_t cnt[U], mask[U];
-        uint2 rc[U];
+    uint32_t cnt[U], mask[U];
+    uint2 rc[U];
+    auto load = [&](int i) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t r = (int64_t)v * a.n + min(i + u * kBinBlock, i1 - 1);
@@ -406,10 +406,18 @@ __global__ __launch_bounds__(kBinBlock) void bin_count_kernel(BinArgs a)
             rc[u] = a.rect[r];
             mask[u] = a.tmask[r];
         }
+    };
+    int i = i0 + (int)threadIdx.x;
+    load(i);  // (in flight while the counters are cleared)
+    for (int j = threadIdx.x; j < nt; j += kBinBlock) hist[j] = 0u;
+    __syncthreads();
+    while (i < i1) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (cnt[u] != 0u)
                 for_tiles(rc[u], mask[u], V.ntx, t0, t1, [&](int lt) { atomicAdd(&hist[lt - t0], 1u); });
+        i += U * kBinBlock;
+        if (i < i1) load(i);
     }
     __syncthreads();
     uint32_t *row = a.mat + (size_t)a.groups * V.tile_base + (size_t)g * Tv + t0;
@@ -493,7 +501,10 @@ __global__ __launch_bounds__(kColTiles *kColBlocks) void bin_colscan_kernel(BinA
 // leaves it to those lines: 743 -> 703 us at 16 uneven views x 1M (37 M writes
 // to memory for 65 M entries), 387 -> 375 us at 64 views x 300k.  Windows of
 // 2048 tiles bring the writes to 24 M there, but the passes over the pairs
-// they add cost more (785 us).
+// they add cost more (785 us).  A thread's first pairs are loaded before the
+// cursors are set (376 -> 326 us at 64 views x 300k).  Bound by the L2's rate of
+// 8-byte writes there (56 M; at one a clock and channel 210 us), by partial
+// lines to memory at the uneven views (631 us).
 template <int U>
 __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const uint32_t *start, uint32_t capacity,
                                                                 uint2 *out)
@@ -509,12 +520,10 @@ __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const
     const int t1 = min(Tv, t0 + kWin), nt = t1 - t0;
     const uint32_t *row = a.mat + (size_t)a.groups * V.tile_base + (size_t)g * Tv + t0;
     const uint32_t *st = start + V.tile_base + t0;
-    for (int j = threadIdx.x; j < nt; j += kBinBlock) cur[j] = st[j] + __builtin_nontemporal_load(row + j);
-    __syncthreads();
     const int i0 = g * a.per, i1 = min(a.n, i0 + a.per);
-    for (int i = i0 + (int)threadIdx.x; i < i1; i += U * kBinBlock) {
-        uint32_t cnt[U], mask[U], key[U];
-        uint64_t rc[U];
+    uint32_t cnt[U], mask[U], key[U];
+    uint64_t rc[U];
+    auto load = [&](int i) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t r = (int64_t)v * a.n + min(i + u * kBinBlock, i1 - 1);
@@ -523,6 +532,12 @@ __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const
             rc[u] = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(a.rect) + r);
             mask[u] = __builtin_nontemporal_load(a.tmask + r);
         }
+    };
+    int i = i0 + (int)threadIdx.x;
+    load(i);  // (in flight while the cursors are set)
+    for (int j = threadIdx.x; j < nt; j += kBinBlock) cur[j] = st[j] + __builtin_nontemporal_load(row + j);
+    __syncthreads();
+    while (i < i1) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (cnt[u] == 0u) continue;
@@ -532,6 +547,8 @@ __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const
                 if (p < capacity) out[p] = make_uint2(key[u], (uint32_t)(i + u * kBinBlock));
             });
         }
+        i += U * kBinBlock;
+        if (i < i1) load(i);
     }
 }
 
@@ -945,7 +962,7 @@ hipError_t launch_tile_scan(const uint32_t *tile_cnt, int n_tiles, uint2 *ranges
 // kMatWords words (256 MB); with more tiles 4096, four pairs in flight per
 // thread (16 uneven views x 1M, 90k tiles: count, column scan and scatter 117 +
 // 56 + 663 us, against 155 + 120 + 703 us for 2048 one at a time: the matrix
-// is half as large), and beyond that as many as the limit takes (groups of 16k
+// is half as large; 111 + 55 + 631 us with the first loads ahead), and beyond that as many as the limit takes (groups of 16k
 // there: the scatter alone 1.21 ms).
 constexpr int64_t kMatWords = (int64_t)64 << 20;
 constexpr int kPerLarge = 4 * kBinBlock;
