@@ -1433,11 +1433,16 @@ ddgs_status ddgs_rads_sample(ddgs_ctx *c, int64_t n1, const uint32_t *mc_keys, i
         DDGS_TRY(ensure_t(c, "rads_v1", (size_t)M, &v1));
         SortWs ws;
         DDGS_TRY(aux_sort_ws(c, M, &ws));
-        HIP_TRY(c, hipMemcpyAsync(k0, mc_keys, sizeof(uint32_t) * M, hipMemcpyDeviceToDevice, s));
-        HIP_TRY(c, launch_iota(v0, M, s));
-        bool in_k1 = false;
-        HIP_TRY(c, radix_sort_pairs(k0, v0, k1, v1, M, nullptr, 32, ws, &in_k1, s));
-        HIP_TRY(c, launch_rads_gather(buf<float>(c, "rads_pts"), M, in_k1 ? v1 : v0, n1e, points, N, s));
+        if (M <= kPickMax) {
+            HIP_TRY(c, radix_top_pass(mc_keys, M, k1, v1, ws, s));
+            HIP_TRY(c, launch_rads_pick(ws.tot, k1, v1, k0, v0, n1e, buf<float>(c, "rads_pts"), M, points, N, s));
+        } else {
+            HIP_TRY(c, hipMemcpyAsync(k0, mc_keys, sizeof(uint32_t) * M, hipMemcpyDeviceToDevice, s));
+            HIP_TRY(c, launch_iota(v0, M, s));
+            bool in_k1 = false;
+            HIP_TRY(c, radix_sort_pairs(k0, v0, k1, v1, M, nullptr, 32, ws, &in_k1, s));
+            HIP_TRY(c, launch_rads_gather(buf<float>(c, "rads_pts"), M, in_k1 ? v1 : v0, n1e, points, N, s));
+        }
     }
     HIP_TRY(c, launch_rads_draws(c->rads_vol, buf<uint64_t>(c, "rads_swt"), buf<uint16_t>(c, "rads_w16"), dw_draws, n2,
                                  points, N, n1e, s));

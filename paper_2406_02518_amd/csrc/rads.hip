@@ -295,6 +295,133 @@ __global__ __launch_bounds__(kRadsBlock) void gather_kernel(const float *src, in
     out[2 * N + j] = src[2 * M + i];
 }
 
+// The n1 smallest of M keys, ties by index, without sorting all of them: a
+// stable pass by the keys' top bits (radix_top_pass) leaves buckets of a few
+// hundred random keys, and one workgroup per bucket orders its own and writes
+// their points; the buckets behind the n1-th key are left alone.  Four launches
+// instead of the fifteen of a whole sort, each of which lasted a launch's few
+// microseconds (126k keys, n1 = 15000: 63 -> 26 us of the card).  In a bucket of up to
+// kPickLds keys an entry's place is the number of smaller ones, counted over
+// the bucket in LDS; a longer one (keys that are not random) is sorted by its
+// workgroup with three stable 8-bit passes through memory.
+constexpr int kPickBlock = 512, kPickLds = 1024, kPickWaves = kPickBlock / kWave;
+__global__ __launch_bounds__(kPickBlock) void pick_kernel(const uint32_t *tot, uint32_t *ka, uint32_t *va, uint32_t *kb,
+                                                          uint32_t *vb, int64_t n1, const float *src, int64_t M,
+                                                          float *out, int64_t N)
+{
+    static_assert(kPickBlock == 1 << kTopBits, "one thread per bucket total");
+    __shared__ __align__(16) uint32_t key[kPickLds];
+    __shared__ uint32_t wh[kPickWaves][256], cur[256], wl[kPickWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    uint32_t start = 0;
+    {
+        const uint32_t inc = wave_incl_scan(tid < (int)blockIdx.x ? tot[tid] : 0u);
+        if (lane == kWave - 1) wl[w] = inc;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kPickWaves; ++q) start += wl[q];
+    }
+    const int len = (int)tot[blockIdx.x];
+    if (len == 0 || (int64_t)start >= n1) return;  // uniform over the block
+    auto put = [&](int rank, uint32_t i) {
+        const int64_t o = (int64_t)start + rank;
+        if (o >= n1) return;
+        out[o] = src[i];
+        out[N + o] = src[M + i];
+        out[2 * N + o] = src[2 * M + i];
+    };
+    ka += start;
+    va += start;
+    if (len <= kPickLds) {
+        uint32_t k[kPickLds / kPickBlock], v[kPickLds / kPickBlock];
+#pragma unroll
+        for (int q = 0; q < kPickLds / kPickBlock; ++q) {
+            const int j = tid + q * kPickBlock;
+            k[q] = j < len ? ka[j] : 0xFFFFFFFFu;
+            v[q] = j < len ? va[j] : 0u;
+            key[j] = k[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kPickLds / kPickBlock; ++q) {
+            const int j = tid + q * kPickBlock;
+            // the keys in front of this wave's, its own, and those behind
+            const int jw = w * kWave + q * kPickBlock;
+            if (jw >= len) break;
+            const uint32_t x = k[q];
+            int r = 0;
+            for (int p = 0; p < jw; p += 4) {
+                const uint4 y = *reinterpret_cast<const uint4 *>(&key[p]);
+                r += (y.x <= x) + (y.y <= x) + (y.z <= x) + (y.w <= x);
+            }
+#pragma unroll 4
+            for (int p = jw; p < jw + kWave; ++p) r += key[p] < x || (key[p] == x && p < j);
+            for (int p = jw + kWave; p < len; p += 4) {
+                const uint4 y = *reinterpret_cast<const uint4 *>(&key[p]);
+                r += (y.x < x) + (y.y < x) + (y.z < x) + (y.w < x);
+            }
+            if (j < len) put(r, v[q]);
+        }
+        return;
+    }
+    kb += start;
+    vb += start;
+    for (int shift = 0; shift < 24; shift += 8) {
+        if (tid < 256) cur[tid] = 0u;
+        __syncthreads();
+        for (int j = tid; j < len; j += kPickBlock) atomicAdd(&cur[(ka[j] >> shift) & 255u], 1u);
+        __syncthreads();
+        const uint32_t c = tid < 256 ? cur[tid] : 0u, inc = wave_incl_scan(c);
+        if (lane == kWave - 1) wl[w] = inc;
+        __syncthreads();
+        uint32_t pre = inc - c;
+        for (int q = 0; q < w; ++q) pre += wl[q];
+        if (tid < 256) cur[tid] = pre;
+        for (int c0 = 0; c0 < len; c0 += kPickBlock) {
+            for (int q = tid; q < kPickWaves * 256; q += kPickBlock) wh[q / 256][q % 256] = 0u;
+            __syncthreads();
+            const int j = c0 + tid;
+            const bool ok = j < len;
+            const uint32_t kk = ok ? ka[j] : 0u, vv = ok ? va[j] : 0u, d = (kk >> shift) & 255u;
+            uint64_t peers = __ballot(ok);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const bool bit = (d >> b) & 1u;
+                const uint64_t bal = __ballot(bit);
+                peers &= bit ? bal : ~bal;
+            }
+            const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
+            if (ok && below == 0u) wh[w][d] = (uint32_t)__popcll(peers);
+            __syncthreads();
+            if (tid < 256) {
+                uint32_t run = cur[tid];
+#pragma unroll
+                for (int q = 0; q < kPickWaves; ++q) {
+                    const uint32_t t = wh[q][tid];
+                    wh[q][tid] = run;
+                    run += t;
+                }
+                cur[tid] = run;
+            }
+            __syncthreads();
+            if (ok) {
+                const uint32_t o = wh[w][d] + below;
+                kb[o] = kk;
+                vb[o] = vv;
+            }
+            __syncthreads();
+        }
+        uint32_t *t = ka;
+        ka = kb;
+        kb = t;
+        t = va;
+        va = vb;
+        vb = t;
+    }
+    for (int j = tid; j < len; j += kPickBlock) put(j, va[j]);
+}
+
 // draw j: the first voxel whose inclusive weight sum exceeds draws[j] (the
 // last voxel if none does), one wave per draw: a 64-way search of the
 // segments' running sums, then the segment's words, 16 consecutive ones per
@@ -612,6 +739,15 @@ hipError_t launch_rads_gather(const float *src, int64_t M, const uint32_t *idx, 
 {
     if (n1 == 0) return hipSuccess;
     gather_kernel<<<(unsigned)blocks(n1, kRadsBlock), kRadsBlock, 0, s>>>(src, M, idx, n1, out, N);
+    return hipGetLastError();
+}
+
+hipError_t launch_rads_pick(const uint32_t *tot, uint32_t *ka, uint32_t *va, uint32_t *kb, uint32_t *vb, int64_t n1,
+                            const float *src, int64_t M, float *out, int64_t N, hipStream_t s)
+{
+    if (n1 == 0 || M == 0) return hipSuccess;
+    if (M > kPickMax) return hipErrorInvalidValue;
+    pick_kernel<<<1 << kTopBits, kPickBlock, 0, s>>>(tot, ka, va, kb, vb, n1, src, M, out, N);
     return hipGetLastError();
 }
 

@@ -353,7 +353,7 @@ __global__ __launch_bounds__(kBlock) void radix_scatter_kernel(const uint32_t *k
     for (int r = 0; r < IPT; ++r) {
         const int64_t li = min(wbase + r * kWave + lane, n - 1);
         key[r] = kin[li];
-        val[r] = vin[li];
+        val[r] = vin ? vin[li] : (uint32_t)li;  // (no values: the indices)
     }
 #pragma unroll
     for (int r = 0; r < IPT; ++r) {
@@ -625,6 +625,22 @@ hipError_t radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *
         std::swap(va, vb);
         *in_k1 = !*in_k1;
     }
+    return hipGetLastError();
+}
+
+hipError_t radix_top_pass(const uint32_t *keys, int64_t n, uint32_t *kout, uint32_t *vout, const SortWs &ws,
+                          hipStream_t s)
+{
+    if (n <= 0) return hipSuccess;
+    if (!ws.counts || !ws.tot || sort_counts_words(n) > ws.counts_words || n >= kRadixSmallN) return hipErrorInvalidValue;
+    constexpr int NB = 1 << kTopBits;
+    static_assert(NB <= kRadixMaxDigits, "digit totals");
+    const int nblocks = (int)blocks_for(n, (int64_t)kBlock * kRadixIPTSmall);
+    radix_count_kernel<kRadixIPTSmall, NB><<<(unsigned)nblocks, kBlock, 0, s>>>(keys, n, nullptr, 32 - kTopBits, NB - 1u,
+                                                                               ws.counts, nblocks);
+    radix_prefix_kernel<<<NB, kBlock, 0, s>>>(ws.counts, nblocks, ws.tot);
+    radix_scatter_kernel<kRadixIPTSmall, NB><<<(unsigned)nblocks, kBlock, 0, s>>>(
+        keys, nullptr, kout, vout, n, nullptr, 32 - kTopBits, kTopBits, ws.counts, ws.tot, nblocks, nullptr, nullptr);
     return hipGetLastError();
 }
 

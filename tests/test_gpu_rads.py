@@ -156,3 +156,46 @@ def test_volume_segments(R, shape):
     rng = np.random.default_rng(shape[2])
     hu = rng.uniform(-1000.0, 1500.0, shape).astype(np.float32)
     _run(R, hu, (1.0, 1.0, 1.0), (0.0, 0.0, 0.0), 200, 300, seed=1)
+
+
+def _keys(kind, M, rng):
+    k = rng.integers(0, 1 << 32, M, dtype=np.uint64)
+    if kind == "one bucket":  # of the top bits, with ties
+        k >>= 10
+        k //= 3
+    elif kind == "limits":  # buckets of 1024 and 1025 keys, the rest above
+        k = (1 << 24) + k * 255 // 256
+        k[:1024] >>= 10
+        k[1024:2049] = (k[1024:2049] >> 10) | (1 << 23)
+        k = rng.permutation(k)
+    elif kind == "equal":
+        k[:] = 0xFFFFFFFF
+    elif kind == "ends":  # 0 and the largest key, many times
+        k[::3] = 0xFFFFFFFF
+        k[1::3] = 0
+    return k.astype(np.uint32)
+
+
+@pytest.mark.parametrize("kind", ["random", "one bucket", "limits", "equal", "ends"])
+@pytest.mark.parametrize("shape", [(3, 4, 5), (12, 13, 14), (45, 46, 47), (57, 58, 59)])
+def test_key_subsample(R, kind, shape):
+    """The interface points of the smallest keys, in key order with ties by edge
+    order, for few, some and many crossings (the last volume has more than the
+    bucketed selection takes) and keys that fill its buckets unevenly."""
+    rng = np.random.default_rng(sum(shape))
+    hu = rng.uniform(-1000.0, 1500.0, shape).astype(np.float32)
+    vol, keep = _volume(hu, (1.0, 1.0, 1.0), (0.0, 0.0, 0.0))
+    level, M, W = binding.ddgs_rads_prepare(R.ctx, vol)
+    pmc, _ = rads_ref.crossings(hu, level, (1.0, 1.0, 1.0), (0.0, 0.0, 0.0))
+    assert M == len(pmc) and (M > 1 << 18) == (shape == (57, 58, 59))
+    if kind == "limits" and M < 4000:
+        pytest.skip("needs 2049 keys in two buckets")
+    keys = _keys(kind, M, rng)
+    order = np.lexsort((np.arange(M), keys))
+    kd = torch.from_numpy(keys.view(np.int32)).cuda()
+    for n1 in (1, 1700, 15000, M):
+        n = min(n1, M)
+        pts = torch.empty((3, n), device="cuda")
+        assert binding.ddgs_rads_sample(R.ctx, n1, kd.data_ptr(), 0, None, pts.data_ptr(), None) == n
+        torch.cuda.synchronize()
+        np.testing.assert_allclose(pts.cpu().numpy().T, pmc[order[:n]], rtol=0, atol=2e-4)
