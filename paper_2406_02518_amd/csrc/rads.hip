@@ -232,20 +232,29 @@ __global__ __launch_bounds__(kSegScanBlock) void seg_scan_kernel(uint32_t *scnt,
 }
 
 // the crossing points, [3][M], in edge order (voxel, then axis): the volume is
-// read only where the kept words have a bit
+// read only where the kept words have a bit.  A wave walks its rounds one after
+// another, each a chain of loads, so a segment's 16 rounds go to the four waves
+// of a workgroup (256^3 volume, 126k crossings: 28 us with a wave per segment,
+// 20 us; 23 us with eight waves).
 __global__ __launch_bounds__(kRadsBlock) void mc_emit_kernel(RadsVol v, const float *mm, int64_t nseg,
                                                              const uint64_t *edge, const uint32_t *scnt, float *pts,
                                                              int64_t M)
 {
+    constexpr int PART = 3 * kRadsRounds / (kRadsBlock / kWave);  // words per wave
+    static_assert(PART % 3 == 0, "whole rounds");
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t seg = (int64_t)blockIdx.x * (kRadsBlock / kWave) + threadIdx.x / kWave;
+    const int64_t seg = blockIdx.x;
+    const int w0 = (int)(threadIdx.x / kWave) * PART;
     if (seg >= nseg) return;
     uint32_t base = scnt[seg];
     if (base == scnt[seg + 1]) return;
     const float iso = mm[2];
     const uint64_t mine = lane < 3 * kRadsRounds ? edge[seg * (3 * kRadsRounds) + lane] : 0ull;
     const uint32_t step[3] = {1u, (uint32_t)v.nx, (uint32_t)v.nx * (uint32_t)v.ny};
-    uint64_t left = __builtin_amdgcn_ballot_w64(mine != 0ull);
+    // the crossings of the waves before
+    const uint32_t inc = wave_incl_scan(lane < w0 ? (uint32_t)__popcll(mine) : 0u);
+    base += (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+    uint64_t left = __builtin_amdgcn_ballot_w64(mine != 0ull && lane >= w0 && lane < w0 + PART);
     while (left) {
         const int r = __builtin_ctzll(left) / 3;
         left &= ~(7ull << (3 * r));
@@ -723,7 +732,7 @@ hipError_t launch_mc_emit(const RadsVol &v, const float *mm, const uint64_t *edg
 {
     const int64_t n = (int64_t)v.nx * v.ny * v.nz, nseg = rads_segments(n);
     if (M == 0) return hipSuccess;
-    mc_emit_kernel<<<(unsigned)blocks(nseg, kRadsBlock / kWave), kRadsBlock, 0, s>>>(v, mm, nseg, edge, scnt, pts, M);
+    mc_emit_kernel<<<(unsigned)nseg, kRadsBlock, 0, s>>>(v, mm, nseg, edge, scnt, pts, M);
     return hipGetLastError();
 }
 
