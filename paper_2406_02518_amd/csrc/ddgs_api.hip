@@ -131,10 +131,15 @@ struct ddgs_ctx {
     // target image of the captured step's loss (uploaded with the view table)
     const float *step_target = nullptr;
 
-    // entry total and number of long tiles of a plain render, written by its tile
-    // scan to pinned host memory, and the event behind that launch
-    uint32_t *total_host = nullptr;
-    hipEvent_t total_event = nullptr;
+    // pinned host words that a kernel writes for a call that waits for them
+    // (host_event: behind that kernel): the entry total and the number of long
+    // tiles of a plain render; the totals of a volume.  (A copy to pageable
+    // memory instead: 254 -> 217 us for a 256^3 volume's dual sampling.)
+    struct HostWords {
+        uint32_t total[3];
+        RadsTotals rads;
+    } *host = nullptr;
+    hipEvent_t host_event = nullptr;
 
     // pinned staging of the view table uploads
     void *stage_host = nullptr;
@@ -232,6 +237,12 @@ ddgs_status ensure(ddgs_ctx *c, const char *name, size_t bytes, void **out)
         b.bytes = nb;
     }
     *out = b.p;
+    return DDGS_OK;
+}
+
+ddgs_status ensure_host(ddgs_ctx *c)
+{
+    if (!c->host) HIP_TRY(c, hipHostMalloc((void **)&c->host, sizeof(*c->host), hipHostMallocCoherent));
     return DDGS_OK;
 }
 
@@ -647,7 +658,7 @@ ddgs_status enqueue_front(ddgs_ctx *c, uint32_t capacity, bool captured, bool sm
                                 buf<uint32_t>(c, "slot_btot"), (int64_t)V * slot_blocks(m.n),
                                 buf<uint32_t>(c, "slot_ssum"), c->bufs["slot_ssum"].bytes / sizeof(uint32_t), buf<uint64_t>(c, "tile_bsum"),
                                 c->bufs["tile_bsum"].bytes / sizeof(uint64_t), fold ? &ti : nullptr, long_tiles(c),
-                                captured ? nullptr : c->total_host, s));
+                                captured ? nullptr : c->host->total, s));
     // the sort stage is timed in two parts: a plain render reads the entry
     // total back to the host between them, and that round trip is not device work
     stage_end(c, DDGS_T_SORT);
@@ -968,7 +979,7 @@ ddgs_status ddgs_create(ddgs_ctx **out, int device, void *hip_stream)
         return DDGS_ERR_HIP;
     }
     if (hipEventCreateWithFlags(&c->stage_event, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->total_event, hipEventDisableTiming) != hipSuccess) {
+        hipEventCreateWithFlags(&c->host_event, hipEventDisableTiming) != hipSuccess) {
         ddgs_destroy(c);
         return DDGS_ERR_HIP;
     }
@@ -993,9 +1004,9 @@ void ddgs_destroy(ddgs_ctx *c)
     if (c->ev_sort_tail_s) (void)hipEventDestroy(c->ev_sort_tail_s);
     if (c->ev_sort_tail_e) (void)hipEventDestroy(c->ev_sort_tail_e);
     if (c->stage_event) (void)hipEventDestroy(c->stage_event);
-    if (c->total_event) (void)hipEventDestroy(c->total_event);
+    if (c->host_event) (void)hipEventDestroy(c->host_event);
     if (c->stage_host) (void)hipHostFree(c->stage_host);
-    if (c->total_host) (void)hipHostFree(c->total_host);
+    if (c->host) (void)hipHostFree(c->host);
     delete c;
 }
 
@@ -1379,35 +1390,33 @@ ddgs_status ddgs_rads_prepare(ddgs_ctx *c, const ddgs_volume *vol, float *level,
               vol->origin[0], vol->origin[1], vol->origin[2], vol->hu};
     const int64_t nb = rads_minmax_blocks(n, c->num_cu), nseg = rads_segments(n);
     float2 *part;
-    uint64_t *tot, *swt, *edge;
+    uint64_t *swt, *edge;
+    float *mm;
     uint32_t *scnt;
     uint16_t *w16;
     DDGS_TRY(ensure_t(c, "rads_part", (size_t)nb, &part));
-    DDGS_TRY(ensure_t(c, "rads_tot", 4, &tot));  // crossings, weight; min, max, level
+    DDGS_TRY(ensure_t(c, "rads_mm", 4, &mm));  // min, max, level
     DDGS_TRY(ensure_t(c, "rads_scnt", (size_t)nseg + 1, &scnt));
     DDGS_TRY(ensure_t(c, "rads_swt", (size_t)nseg + 1, &swt));
     DDGS_TRY(ensure_t(c, "rads_w16", rads_weight_words(n), &w16));
     DDGS_TRY(ensure_t(c, "rads_edge", rads_edge_words(n), &edge));
-    float *mm = (float *)(tot + 2);
+    DDGS_TRY(ensure_host(c));
+    RadsTotals *const h = &c->host->rads;
     HIP_TRY(c, launch_rads_level(v, part, nb, mm, s));
-    HIP_TRY(c, launch_rads_segments(v, mm, w16, edge, scnt, swt, tot, s));
-    struct {
-        uint64_t m, w;
-        float mm[4];
-    } h{};
-    HIP_TRY(c, hipMemcpyAsync(&h, tot, sizeof(h), hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipStreamSynchronize(s));
+    HIP_TRY(c, launch_rads_segments(v, mm, w16, edge, scnt, swt, h, s));
+    HIP_TRY(c, hipEventRecord(c->host_event, s));
+    HIP_TRY(c, hipEventSynchronize(c->host_event));
     float *pts;
-    DDGS_TRY(ensure_t(c, "rads_pts", (size_t)std::max<uint64_t>(3 * h.m, 1), &pts));
-    HIP_TRY(c, launch_mc_emit(v, mm, edge, scnt, pts, (int64_t)h.m, s));
+    DDGS_TRY(ensure_t(c, "rads_pts", (size_t)std::max<uint64_t>(3 * h->crossings, 1), &pts));
+    HIP_TRY(c, launch_mc_emit(v, mm, edge, scnt, pts, (int64_t)h->crossings, s));
     v.hu = nullptr;  // not read after this call
     c->rads_vol = v;
-    c->rads_m = (int64_t)h.m;
-    c->rads_w = h.w;
+    c->rads_m = (int64_t)h->crossings;
+    c->rads_w = h->weight;
     c->rads_ok = true;
-    *level = h.mm[2];
-    *n_crossings = (int64_t)h.m;
-    *total_weight = h.w;
+    *level = h->level;
+    *n_crossings = (int64_t)h->crossings;
+    *total_weight = h->weight;
     return DDGS_OK;
 }
 
@@ -1547,10 +1556,9 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
         c->long_grid = c->model.n > kSortShort ? 1 << 30 : 0;
         DDGS_TRY(enqueue_back(c, worst, images));
     } else if (VN > 0) {
-        if (!c->total_host)
-            HIP_TRY(c, hipHostMalloc((void **)&c->total_host, 4 * sizeof(uint32_t), hipHostMallocCoherent));
+        DDGS_TRY(ensure_host(c));
         DDGS_TRY(enqueue_front(c, 0xFFFFFFFFu, false, false));
-        HIP_TRY(c, hipEventRecord(c->total_event, c->stream));
+        HIP_TRY(c, hipEventRecord(c->host_event, c->stream));
         // While the host waits for the entry total, the card scatters and sorts
         // into the buffers that an earlier render sized (what lies beyond
         // them is left out); only a render that needs larger ones runs both again.
@@ -1563,8 +1571,8 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
                                                 (int64_t)(c->bufs["tval"].bytes / sizeof(uint32_t)), 0xFFFFFFFEll});
         bool ahead = c->entry_cap > 1 && !c->timing && !c->keep_unsorted;
         if (ahead) DDGS_TRY(enqueue_sort_head(c, held, false));
-        HIP_TRY(c, hipEventSynchronize(c->total_event));
-        const uint32_t *const sc = c->total_host;
+        HIP_TRY(c, hipEventSynchronize(c->host_event));
+        const uint32_t *const sc = c->host->total;
         const uint64_t total = (uint64_t)sc[0] | ((uint64_t)sc[1] << 32);
         const int64_t n_long = sc[2];
         if (c->long_seen_n != c->model.n || c->long_seen_tiles != c->n_tiles) c->long_seen = -1;

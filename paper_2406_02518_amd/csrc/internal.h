@@ -569,12 +569,17 @@ hipError_t launch_rads_level(const RadsVol &v, float2 *part, int64_t nb, float *
 // Segments of consecutive voxels: running crossing counts scnt and weight
 // sums swt before each ([rads_segments + 1], the last entry the total), the
 // voxels' 16-bit weights w16 [rads_weight_words] and crossing edges
-// [rads_edge_words], and tot = (crossings, weight)
+// [rads_edge_words], and the totals for the host
 int64_t rads_segments(int64_t n);
 size_t rads_edge_words(int64_t n);
 size_t rads_weight_words(int64_t n);
+// (host: pinned, valid once the launch has ended)
+struct RadsTotals {
+    uint64_t crossings, weight;
+    float level;
+};
 hipError_t launch_rads_segments(const RadsVol &v, const float *mm, uint16_t *w16, uint64_t *edge, uint32_t *scnt,
-                                uint64_t *swt, uint64_t *tot, hipStream_t s);
+                                uint64_t *swt, RadsTotals *host, hipStream_t s);
 hipError_t launch_mc_emit(const RadsVol &v, const float *mm, const uint64_t *edge, const uint32_t *scnt, float *pts,
                           int64_t M, hipStream_t s);
 hipError_t launch_iota(uint32_t *p, int64_t n, hipStream_t s);

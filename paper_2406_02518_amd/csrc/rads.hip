@@ -165,12 +165,12 @@ __global__ __launch_bounds__(kRadsBlock) void seg_count_kernel(RadsVol v, uint32
 }
 
 // Exclusive scans of the segment totals in place, by one block; entry nseg of
-// each receives the total, and tot both (crossings, weight).  A wave takes 16
+// each receives the total, and the pinned host words both.  A wave takes 16
 // rounds of 64 consecutive segments (coalesced loads, all in flight together;
 // one thread per 16 segments instead took 46 us for 16384 of them).
 constexpr int kSegScanBlock = 1024;
 __global__ __launch_bounds__(kSegScanBlock) void seg_scan_kernel(uint32_t *scnt, uint64_t *swt, int64_t nseg,
-                                                                 uint64_t *tot)
+                                                                 const float *mm, RadsTotals *host)
 {
     constexpr int NW = kSegScanBlock / kWave, PER = 16;
     // (64 segments weigh at most 64 x 1024 x 65535 < 2^32)
@@ -226,8 +226,9 @@ __global__ __launch_bounds__(kSegScanBlock) void seg_scan_kernel(uint32_t *scnt,
     if (threadIdx.x == 0) {
         scnt[nseg] = (uint32_t)cc;
         swt[nseg] = cw;
-        tot[0] = cc;
-        tot[1] = cw;
+        host->crossings = cc;
+        host->weight = cw;
+        host->level = mm[2];
     }
 }
 
@@ -718,12 +719,12 @@ hipError_t launch_rads_level(const RadsVol &v, float2 *part, int64_t nb, float *
 }
 
 hipError_t launch_rads_segments(const RadsVol &v, const float *mm, uint16_t *w16, uint64_t *edge, uint32_t *scnt,
-                                uint64_t *swt, uint64_t *tot, hipStream_t s)
+                                uint64_t *swt, RadsTotals *host, hipStream_t s)
 {
     const int64_t n = (int64_t)v.nx * v.ny * v.nz, nseg = rads_segments(n);
     seg_count_kernel<<<(unsigned)blocks(nseg, kRadsBlock / kWave), kRadsBlock, 0, s>>>(v, (uint32_t)n, mm, nseg, w16,
                                                                                         edge, scnt, swt);
-    seg_scan_kernel<<<1, kSegScanBlock, 0, s>>>(scnt, swt, nseg, tot);
+    seg_scan_kernel<<<1, kSegScanBlock, 0, s>>>(scnt, swt, nseg, mm, host);
     return hipGetLastError();
 }
 
