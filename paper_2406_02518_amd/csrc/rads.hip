@@ -8,6 +8,8 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 namespace ddgs {
 
@@ -81,10 +83,9 @@ __device__ __forceinline__ uint32_t weight_of(float hu, float mn, float mx)
 // keeps them as 16-bit words; a scan of the segment totals places crossings
 // and draws, a second launch writes the points from the kept bits, and a draw
 // searches the segments and then the words of one.  The pass over the volume
-// is bound by HBM and the arithmetic of the weights: per voxel 4 B read, 2.4 B
-// written (the running sums per voxel this replaces moved 60 B: the eight
-// launches from the counts to the points of a 256^3 volume took 324 us, these
-// three take 90).
+// is bound by VALU issue and HBM: per voxel 4 B read, 2.4 B written (the running
+// sums per voxel this replaces moved 60 B: the eight launches from the counts
+// to the points of a 256^3 volume took 324 us, these three take 59).
 struct RadsVoxel {
     int x, y, z;
 };
@@ -93,36 +94,39 @@ __device__ __forceinline__ RadsVoxel voxel_of(const RadsVol &v, uint32_t i)
     const uint32_t row = i / (uint32_t)v.nx, z = row / (uint32_t)v.ny;
     return RadsVoxel{(int)(i - row * (uint32_t)v.nx), (int)(row - z * (uint32_t)v.ny), (int)z};
 }
-// kWave voxels on (the divisions are done once per segment); step64 is
-// voxel_of(kWave)
-__device__ __forceinline__ void next_round(const RadsVol &v, const RadsVoxel &step64, RadsVoxel &c)
+
+// hu / d for d in [2^-60, 2^100], 0 <= hu <= d, given r = 1 / d rounded: two
+// residual steps, of which the first leaves an error below one unit in the last
+// place and the second rounds correctly (Markstein's theorem), so the quotient
+// is the division's; a quotient small enough for a residual to underflow
+// weighs nothing either way.  Five operations for the division's eleven.
+__device__ __forceinline__ float quotient(float hu, float d, float r)
 {
-    c.x += step64.x;
-    const int cx = c.x >= v.nx ? 1 : 0;
-    c.x -= cx ? v.nx : 0;
-    c.y += step64.y + cx;
-    const int cy = c.y >= v.ny ? 1 : 0;
-    c.y -= cy ? v.ny : 0;
-    c.z += step64.z + cy;
+    float q = __fmul_rn(hu, r);
+    q = __fmaf_rn(__fmaf_rn(-q, d, hu), r, q);
+    return __fmaf_rn(__fmaf_rn(-q, d, hu), r, q);
 }
-// which of the three edges leaving voxel i (at c) cross the level, and their
-// far ends
-__device__ __forceinline__ uint32_t crossing_edges(const RadsVol &v, uint32_t i, const RadsVoxel &c, float a, float iso,
-                                                   float (&far_end)[3])
+
+// lane LANE of (lo, hi) = the (uniform) word b
+template <int LANE>
+__device__ __forceinline__ void keep_word(uint32_t &lo, uint32_t &hi, uint64_t b)
 {
-    const uint32_t step[3] = {1u, (uint32_t)v.nx, (uint32_t)v.nx * (uint32_t)v.ny};
-    const bool in[3] = {c.x + 1 < v.nx, c.y + 1 < v.ny, c.z + 1 < v.nz};
-    uint32_t m = 0u;
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-        far_end[ax] = in[ax] ? v.hu[i + step[ax]] : a;
-        m |= below(far_end[ax], iso) != below(a, iso) ? 1u << ax : 0u;
-    }
-    return m;
+    asm("v_writelane_b32 %0, %1, %2" : "+v"(lo) : "s"((uint32_t)b), "n"(LANE));
+    asm("v_writelane_b32 %0, %1, %2" : "+v"(hi) : "s"((uint32_t)(b >> 32)), "n"(LANE));
+}
+template <class F, int... R>
+__device__ __forceinline__ void each_round(F f, std::integer_sequence<int, R...>)
+{
+    (f(std::integral_constant<int, R>{}), ...);
 }
 
 // edge: per segment the crossing edges of its 16 rounds of 64 voxels, one word
-// per round and axis (word 3 round + axis, bit = lane)
+// per round and axis (word 3 round + axis, bit = lane).  Bound by VALU issue:
+// the words are formed from compare masks in scalar registers, and segments
+// whose far ends all lie in the volume (all but the last plane's) read the four
+// voxels of a lane at one offset from four scalar bases, without a test
+// (256^3: 88 VALU instructions a round and 43 us with a branch per far end and
+// a division per voxel, 31 instructions and 28 us).
 __global__ __launch_bounds__(kRadsBlock) void seg_count_kernel(RadsVol v, uint32_t n, const float *mm, int64_t nseg,
                                                                uint16_t *w16, uint64_t *edge, uint32_t *scnt,
                                                                uint64_t *swt)
@@ -131,28 +135,66 @@ __global__ __launch_bounds__(kRadsBlock) void seg_count_kernel(RadsVol v, uint32
     const int64_t seg = (int64_t)blockIdx.x * (kRadsBlock / kWave) + threadIdx.x / kWave;
     if (seg >= nseg) return;
     const float mn = mm[0], mx = mm[1], iso = mm[2];
+    const float d = mx - mn, rd = 1.0f / d;
     uint32_t cnt = 0, wt = 0;  // (at most 3 and 65535 per voxel)
     uint64_t mine = 0;         // lane 3 round + axis keeps that word
-    RadsVoxel c = voxel_of(v, (uint32_t)(seg * kRadsSeg) + (uint32_t)lane);
-    const RadsVoxel step64 = voxel_of(v, kWave);
-#pragma unroll 4
-    for (int r = 0; r < kRadsRounds; ++r) {
-        const uint32_t i = (uint32_t)(seg * kRadsSeg) + (uint32_t)(r * kWave + lane);
-        uint32_t w = 0u, m = 0u;
-        if (i < n) {
-            const float a = v.hu[i];
-            w = weight_of(a, mn, mx);
-            float far_end[3];
-            m = crossing_edges(v, i, c, a, iso, far_end);
-        }
-        next_round(v, step64, c);
-        w16[i] = (uint16_t)w;  // (zero up to the segment's end)
-        wt += w;
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(seg * kRadsSeg));
+    const RadsVoxel c0 = voxel_of(v, first + (uint32_t)lane), step64 = voxel_of(v, kWave);
+    int x = c0.x, y = c0.y;
+    const uint32_t plane = (uint32_t)v.nx * (uint32_t)v.ny;
+    const uint32_t step[3] = {1u, (uint32_t)v.nx, plane};
+    // kWave voxels on
+    auto next = [&] {
+        x += step64.x;
+        const int cx = x >= v.nx ? 1 : 0;
+        x -= cx ? v.nx : 0;
+        y += step64.y + cx;
+        y -= y >= v.ny ? v.ny : 0;
+    };
+    // (uniform over the wave)
+    if (first + (uint32_t)kRadsSeg + plane <= n && d >= 0x1p-60f && d <= 0x1p100f) {
+        const float *const p = v.hu + first, *const px = p + step[0], *const py = p + step[1], *const pz = p + step[2];
+        uint16_t *const pw = w16 + first;
+        uint32_t lo = 0, hi = 0;
+        auto round = [&](auto rc) {
+            constexpr int r = decltype(rc)::value;
+            const uint32_t o = (uint32_t)(r * kWave + lane);
+            const float a = p[o], fx = px[o], fy = py[o], fz = pz[o];
+            const uint32_t w = (uint32_t)floorf(quotient(a - mn, d, rd) * 65535.0f);
+            pw[o] = (uint16_t)w;
+            wt += w;
+            const uint64_t ba = __builtin_amdgcn_ballot_w64(below(a, iso));
+            const uint64_t b0 = (__builtin_amdgcn_ballot_w64(below(fx, iso)) ^ ba) &
+                                __builtin_amdgcn_ballot_w64(x < v.nx - 1);
+            const uint64_t b1 = (__builtin_amdgcn_ballot_w64(below(fy, iso)) ^ ba) &
+                                __builtin_amdgcn_ballot_w64(y < v.ny - 1);
+            const uint64_t b2 = __builtin_amdgcn_ballot_w64(below(fz, iso)) ^ ba;
+            cnt += (uint32_t)(__popcll(b0) + __popcll(b1) + __popcll(b2));
+            keep_word<3 * r>(lo, hi, b0);
+            keep_word<3 * r + 1>(lo, hi, b1);
+            keep_word<3 * r + 2>(lo, hi, b2);
+            next();
+        };
+        each_round(round, std::make_integer_sequence<int, kRadsRounds>{});
+        mine = ((uint64_t)hi << 32) | lo;
+    } else {
+#pragma unroll 1
+        for (int r = 0; r < kRadsRounds; ++r) {
+            const uint32_t i = first + (uint32_t)(r * kWave + lane);
+            const bool ok = i < n;
+            const float a = ok ? v.hu[i] : 0.0f;
+            const bool in[3] = {ok && x < v.nx - 1, ok && y < v.ny - 1, i + plane < n};
+            const uint32_t w = ok ? weight_of(a, mn, mx) : 0u;
+            w16[i] = (uint16_t)w;  // (zero up to the segment's end)
+            wt += w;
 #pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            const uint64_t b = __builtin_amdgcn_ballot_w64((m >> ax) & 1u);
-            cnt += (uint32_t)__popcll(b);
-            mine = lane == 3 * r + ax ? b : mine;
+            for (int ax = 0; ax < 3; ++ax) {
+                const float far_end = in[ax] ? v.hu[i + step[ax]] : a;
+                const uint64_t b = __builtin_amdgcn_ballot_w64(below(far_end, iso) != below(a, iso));
+                cnt += (uint32_t)__popcll(b);
+                mine = lane == 3 * r + ax ? b : mine;
+            }
+            next();
         }
     }
 #pragma unroll

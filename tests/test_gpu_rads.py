@@ -199,3 +199,17 @@ def test_key_subsample(R, kind, shape):
         assert binding.ddgs_rads_sample(R.ctx, n1, kd.data_ptr(), 0, None, pts.data_ptr(), None) == n
         torch.cuda.synchronize()
         np.testing.assert_allclose(pts.cpu().numpy().T, pmc[order[:n]], rtol=0, atol=2e-4)
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-18, 1.0, 1e27, 1e33])
+def test_volume_value_ranges(R, scale):
+    """Level, crossings and weights exactly, for values on both sides of the range
+    in which the weights' quotient needs no division (2^-60 to 2^100), in a
+    volume with segments that lie inside it and segments of its last plane."""
+    rng = np.random.default_rng(5)
+    hu = (rng.uniform(-1000.0, 1500.0, (9, 20, 30)) * scale).astype(np.float32)
+    vol, keep = _volume(hu, (1.0, 1.0, 1.0), (0.0, 0.0, 0.0))
+    level, M, W = binding.ddgs_rads_prepare(R.ctx, vol)
+    assert level == rads_ref.iso_level(hu)
+    assert M == len(rads_ref.crossings(hu, level, (1.0, 1.0, 1.0), (0.0, 0.0, 0.0))[0])
+    assert W == int(rads_ref.weights(hu).astype(np.uint64).sum())
