@@ -577,7 +577,10 @@ constexpr int kSortLongGrid = 512;  // two workgroups per CU
 // run, so the launch takes an instance that holds 14336 entries in 131 KB of
 // LDS: ranges between the two sizes then stay out of the global-memory path
 // (100k Gaussians / 251 x 187, 32 listed tiles of up to 7253 entries: 30 ->
-// 15 us).  With more tiles two smaller workgroups per CU are faster.
+// 15 us).  With more tiles two smaller workgroups per CU are faster.  With no
+// more tiles at all than CUs that instance takes every tile in one launch: the
+// short ranges are sorted beside the long ones (100k Gaussians / 256^2, 256
+// tiles: 7.5 + 12.9 -> 12.6 us).
 constexpr int kSortLongBig = 14336, kSortLongBigGrid = 256;
 // Buckets: 2048 for the short ranges, 4096 beyond: the LDS that a second array
 // of bucket starts took ranks longer ranges against half as many entries.
@@ -760,7 +763,8 @@ __device__ __forceinline__ void sort_tile(SortLds<CAP, BLOCK> &S, uint2 rg, cons
 // take_long is set (then there is no second launch, and a long tile is
 // bucketed in global memory by this launch's workgroup).
 template <int CAP, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void tile_sort_kernel(const uint2 *ranges, const uint32_t *tile_cnt, int n_tiles,
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CAP > kSortLong ? 4 : 8, CAP > kSortLong ? 4 : 8))) void
+tile_sort_kernel(const uint2 *ranges, const uint32_t *tile_cnt, int n_tiles,
                                                           const uint2 *ent, uint2 *tmp, uint32_t *tval,
                                                           uint32_t capacity, int take_long)
 {
@@ -1015,12 +1019,19 @@ hipError_t launch_bin_scatter(int n, int V, const uint32_t *cnt, const uint2 *re
     return hipGetLastError();
 }
 
+bool tile_sort_one_launch(int n_tiles) { return n_tiles <= kSortLongBigGrid; }
+
 hipError_t launch_tile_sort(const uint2 *ranges, const uint32_t *tile_cnt, int n_tiles, const uint2 *ent, uint2 *tmp,
-                            uint32_t *tval, uint32_t capacity, bool take_long, hipStream_t s)
+                            uint32_t *tval, uint32_t capacity, TileSort how, hipStream_t s)
 {
     if (n_tiles <= 0) return hipSuccess;
-    tile_sort_kernel<kSortShort, kSortShortBlock><<<n_tiles, kSortShortBlock, 0, s>>>(
-        ranges, tile_cnt, n_tiles, ent, tmp, tval, capacity, take_long ? 1 : 0);
+    const int take_long = how == TileSort::kShort ? 0 : 1;
+    if (how == TileSort::kWide)
+        tile_sort_kernel<kSortLongBig, kSortLongBlock><<<n_tiles, kSortLongBlock, 0, s>>>(
+            ranges, tile_cnt, n_tiles, ent, tmp, tval, capacity, take_long);
+    else
+        tile_sort_kernel<kSortShort, kSortShortBlock><<<n_tiles, kSortShortBlock, 0, s>>>(
+            ranges, tile_cnt, n_tiles, ent, tmp, tval, capacity, take_long);
     return hipGetLastError();
 }
 

@@ -471,12 +471,18 @@ ddgs_status ensure_static(ddgs_ctx *c)
 // t_min > 0 each tile is walked by one workgroup.
 int effective_split(const ddgs_ctx *c) { return c->opt.t_min > 0.0f ? 0 : std::max(0, (int)c->opt.split); }
 
+// most long tiles that plain renders of this Gaussian count and tile layout had
+// (-1: none rendered)
+int64_t long_tiles_seen(const ddgs_ctx *c)
+{
+    return c->long_seen_n == c->model.n && c->long_seen_tiles == c->n_tiles ? c->long_seen : -1;
+}
+
 // long-range sort grid of a captured step (see ddgs_ctx::long_grid)
 int captured_long_grid(const ddgs_ctx *c)
 {
     if (c->model.n <= kSortShort) return 0;  // (no tile can hold more)
-    const bool seen = c->long_seen >= 0 && c->long_seen_n == c->model.n && c->long_seen_tiles == c->n_tiles;
-    if (!seen) return 1 << 30;
+    if (long_tiles_seen(c) < 0) return 1 << 30;
     if (c->long_seen == 0) return 0;
     return (int)std::max<int64_t>(16, std::min<int64_t>(2 * c->long_seen, 1 << 30));
 }
@@ -665,10 +671,10 @@ ddgs_status enqueue_front(ddgs_ctx *c, uint32_t capacity, bool captured, bool sm
     return DDGS_OK;
 }
 
-// Scatter of the entries into their tile ranges and the per-tile sort of all
-// but the long tiles (with take_long: of those too).  cap: what the entry
+// Scatter of the entries into their tile ranges and the first launch of the
+// per-tile sort (how: what it does with long tiles).  cap: what the entry
 // buffers hold; entries and ranges beyond it are left out.
-ddgs_status enqueue_sort_head(ddgs_ctx *c, int64_t cap, bool take_long)
+ddgs_status enqueue_sort_head(ddgs_ctx *c, int64_t cap, TileSort how)
 {
     hipStream_t s = c->stream;
     const uint32_t cap32 = (uint32_t)std::min<int64_t>(cap, 0xFFFFFFFFll);
@@ -681,21 +687,25 @@ ddgs_status enqueue_sort_head(ddgs_ctx *c, int64_t cap, bool take_long)
     if (c->keep_unsorted)
         HIP_TRY(c, launch_copy_u32((uint32_t *)buf<uint2>(c, "ubin"), (const uint32_t *)ent, nullptr, 2 * cap, s));
     HIP_TRY(c, launch_tile_sort(buf<uint2>(c, "ranges"), buf<uint32_t>(c, "tile_cnt"), c->n_tiles, ent,
-                                buf<uint2>(c, "bin_tmp"), buf<uint32_t>(c, "tval"), cap32, take_long, s));
+                                buf<uint2>(c, "bin_tmp"), buf<uint32_t>(c, "tval"), cap32, how, s));
     return DDGS_OK;
 }
 
-// The scatter and sort (head: not enqueued yet), the long tiles' sort, the
-// optional work items or queue, and the forward raster.
-ddgs_status enqueue_back(ddgs_ctx *c, int64_t cap, float *images, bool head = true)
+// The scatter and the sort's first launch (unless `ahead`: that one is enqueued),
+// the long tiles' sort, the optional work items or queue, and the forward raster.
+ddgs_status enqueue_back(ddgs_ctx *c, int64_t cap, float *images, const TileSort *ahead = nullptr)
 {
     hipStream_t s = c->stream;
     const int V = (int)c->views_h.size();
     const int n = (int)c->model.n;
     if (c->timing) (void)hipEventRecord(c->ev_sort_tail_s, c->stream);
-    if (head) DDGS_TRY(enqueue_sort_head(c, cap, c->long_grid <= 0));
-    HIP_TRY(c, launch_tile_sort_long(buf<uint2>(c, "ranges"), c->n_tiles, buf<uint2>(c, "bin_ent"),
-                                     buf<uint2>(c, "bin_tmp"), buf<uint32_t>(c, "tval"), long_tiles(c), c->long_grid, s));
+    const TileSort how = ahead ? *ahead : c->long_grid <= 0 ? TileSort::kAll
+                         : tile_sort_one_launch(c->n_tiles) ? TileSort::kWide : TileSort::kShort;
+    if (!ahead) DDGS_TRY(enqueue_sort_head(c, cap, how));
+    if (how == TileSort::kShort)
+        HIP_TRY(c, launch_tile_sort_long(buf<uint2>(c, "ranges"), c->n_tiles, buf<uint2>(c, "bin_ent"),
+                                         buf<uint2>(c, "bin_tmp"), buf<uint32_t>(c, "tval"), long_tiles(c),
+                                         c->long_grid, s));
     c->queue = nullptr;
     const int split = effective_split(c);
     c->max_items = (int)max_items_for(c, cap);
@@ -1570,7 +1580,11 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
                                                 (int64_t)(c->bufs["bin_tmp"].bytes / sizeof(uint2)),
                                                 (int64_t)(c->bufs["tval"].bytes / sizeof(uint32_t)), 0xFFFFFFFEll});
         bool ahead = c->entry_cap > 1 && !c->timing && !c->keep_unsorted;
-        if (ahead) DDGS_TRY(enqueue_sort_head(c, held, false));
+        // (long tiles, if an earlier render of this layout had some and there
+        // are few tiles, in the same launch; else in a second one, if there are any)
+        const TileSort how = tile_sort_one_launch(c->n_tiles) && long_tiles_seen(c) > 0 ? TileSort::kWide
+                                                                                         : TileSort::kShort;
+        if (ahead) DDGS_TRY(enqueue_sort_head(c, held, how));
         HIP_TRY(c, hipEventSynchronize(c->host_event));
         const uint32_t *const sc = c->host->total;
         const uint64_t total = (uint64_t)sc[0] | ((uint64_t)sc[1] << 32);
@@ -1592,7 +1606,7 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
         // no more workgroups than this render can fill; the buffers keep
         // entry_cap)
         if (c->M > held) ahead = false;
-        DDGS_TRY(enqueue_back(c, std::max<int64_t>(c->M, 1), images, !ahead));
+        DDGS_TRY(enqueue_back(c, std::max<int64_t>(c->M, 1), images, ahead ? &how : nullptr));
     } else {
         // no Gaussians: empty lists everywhere
         c->M = 0;

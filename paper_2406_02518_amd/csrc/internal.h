@@ -440,11 +440,14 @@ hipError_t launch_bin_small(int n, int V, const uint32_t *cnt, const uint2 *rect
 // indices to tval; tmp (same layout as ent) is scratch for ranges longer than
 // the LDS holds.  tile_cnt is the tile scan's of the same step.  Ranges that
 // end beyond capacity are left alone.  Long tiles (lt, listed by the tile scan)
-// are left to launch_tile_sort_long unless take_long is set: then this launch
-// sorts them too, through global memory (meant for steps that rarely or never
-// have any).
+// are left to launch_tile_sort_long (kShort), sorted too but through global
+// memory (kAll: meant for steps that rarely or never have any), or sorted too
+// in an instance with the LDS for them (kWide: one workgroup per CU, meant for
+// tile_sort_one_launch, no more tiles than CUs).
+enum class TileSort { kShort, kAll, kWide };
+bool tile_sort_one_launch(int n_tiles);
 hipError_t launch_tile_sort(const uint2 *ranges, const uint32_t *tile_cnt, int n_tiles, const uint2 *ent, uint2 *tmp,
-                            uint32_t *tval, uint32_t capacity, bool take_long, hipStream_t s);
+                            uint32_t *tval, uint32_t capacity, TileSort how, hipStream_t s);
 // The listed long tiles, taken round-robin by at most long_grid workgroups
 // (none: no launch).
 hipError_t launch_tile_sort_long(const uint2 *ranges, int n_tiles, const uint2 *ent, uint2 *tmp, uint32_t *tval,

@@ -152,3 +152,36 @@ def test_groups_of_many_tiles_equal_single_views():
         assert at == M and M > n
     finally:
         r.close()
+
+
+@pytest.mark.parametrize("n,w,h", [(20000, 40, 30), (60000, 24, 20), (60000, 256, 250)])
+def test_long_tiles_of_few(n, w, h):
+    """Long ranges among no more tiles than the card has compute units, sorted
+    beside the short ones in one launch: a render that has seen the layout, and a
+    captured step, against the first render (two launches); lists beyond the LDS
+    (more than 14336 entries in a tile) included."""
+    sc = synth.random_scene(29, n, k=4, L=1, extent=18.0, std_range=(1.0, 4.0))
+    views = _views(1, w, h)
+    r = binding.Renderer(0, stream=torch.cuda.Stream())
+    try:
+        opts = dict(tile_w=16, tile_h=16, split=256)
+        first = _lists(r, sc, views, opts)
+        again = _lists(r, sc, views, opts)
+        for x, y in zip(again, first):
+            np.testing.assert_array_equal(x, y)
+        ln = first[2].reshape(-1, 2)[:, 1].astype(np.int64) - first[2].reshape(-1, 2)[:, 0]
+        assert ln.size <= 256 and ln.max() > (14336 if (n, w) == (60000, 24) else 2560)
+        P = r.image_size()
+        img, dl, w_ = torch.empty(P, device="cuda"), torch.empty(P, device="cuda"), torch.ones(P, device="cuda")
+        loss, grads = torch.empty(1, device="cuda"), r.alloc_grads()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(r.stream):
+            binding.ddgs_step_capture(r.ctx, binding.LOSS_LINEAR, w_.data_ptr(), 0.0, img.data_ptr(), dl.data_ptr(),
+                                      loss.data_ptr(), r.grads_struct(grads))
+        for _ in range(3):
+            binding.ddgs_step_launch(r.ctx)
+            assert r.check_step() == 0
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(img.cpu().numpy(), first[0])
+    finally:
+        r.close()
