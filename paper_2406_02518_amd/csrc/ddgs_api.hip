@@ -141,7 +141,7 @@ struct ddgs_ctx {
     } *host = nullptr;
     hipEvent_t host_event = nullptr;
 
-    // pinned staging of the view table uploads
+    // pinned staging of the view table uploads (behind the host words)
     void *stage_host = nullptr;
     size_t stage_bytes = 0;
     hipEvent_t stage_event = nullptr;
@@ -240,9 +240,23 @@ ddgs_status ensure(ddgs_ctx *c, const char *name, size_t bytes, void **out)
     return DDGS_OK;
 }
 
-ddgs_status ensure_host(ddgs_ctx *c)
+// The pinned host memory: the words above and at least `stage` bytes of staging
+// behind them, one allocation (each costs a context's first call some 50 us).
+ddgs_status ensure_host(ddgs_ctx *c, size_t stage = 0)
 {
-    if (!c->host) HIP_TRY(c, hipHostMalloc((void **)&c->host, sizeof(*c->host), hipHostMallocCoherent));
+    if (c->host && c->stage_bytes >= stage) return DDGS_OK;
+    if (c->host) {
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        HIP_TRY(c, hipHostFree(c->host));
+    }
+    c->host = nullptr;
+    c->stage_host = nullptr;
+    c->stage_bytes = 0;
+    void *p = nullptr;
+    HIP_TRY(c, hipHostMalloc(&p, sizeof(*c->host) + stage + 1024, hipHostMallocCoherent));
+    c->host = (ddgs_ctx::HostWords *)p;
+    c->stage_host = c->host + 1;
+    c->stage_bytes = stage + 1024;
     return DDGS_OK;
 }
 
@@ -392,13 +406,7 @@ ddgs_status prepare_views(ddgs_ctx *c)
         HIP_TRY(c, hipEventSynchronize(c->stage_event));
         c->stage_pending = false;
     }
-    if (c->stage_bytes < need) {
-        if (c->stage_host) HIP_TRY(c, hipHostFree(c->stage_host));
-        c->stage_host = nullptr;
-        c->stage_bytes = 0;
-        HIP_TRY(c, hipHostMalloc(&c->stage_host, need + 1024, hipHostMallocDefault));
-        c->stage_bytes = need + 1024;
-    }
+    DDGS_TRY(ensure_host(c, need));
     char *h = (char *)c->stage_host;
     if (V > 0) std::memcpy(h, c->vdev_h.data(), sizeof(ViewDev) * V);
     std::memcpy(h + loss_base_offset(V), c->loss_tile_base_h.data(), sizeof(int32_t) * (V + 1));
@@ -1015,7 +1023,6 @@ void ddgs_destroy(ddgs_ctx *c)
     if (c->ev_sort_tail_e) (void)hipEventDestroy(c->ev_sort_tail_e);
     if (c->stage_event) (void)hipEventDestroy(c->stage_event);
     if (c->host_event) (void)hipEventDestroy(c->host_event);
-    if (c->stage_host) (void)hipHostFree(c->stage_host);
     if (c->host) (void)hipHostFree(c->host);
     delete c;
 }
