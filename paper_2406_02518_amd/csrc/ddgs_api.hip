@@ -260,6 +260,17 @@ ddgs_status ensure_host(ddgs_ctx *c, size_t stage = 0)
     return DDGS_OK;
 }
 
+// A call that reads a result back, or leaves one to be read back, belongs in no
+// graph that a caller captures.
+ddgs_status refuse_capture(ddgs_ctx *c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+    if (st != hipStreamCaptureStatusNone)
+        return fail(c, DDGS_ERR_HIP, "the stream is being captured (ddgs_step_capture captures a step)");
+    return DDGS_OK;
+}
+
 ddgs_status resolve_total(ddgs_ctx *c);
 
 // Releases every workspace buffer (library-owned ones are freed).
@@ -1402,6 +1413,7 @@ ddgs_status ddgs_rads_prepare(ddgs_ctx *c, const ddgs_volume *vol, float *level,
             return fail(c, DDGS_ERR_INVALID_ARG, "need finite spacing > 0 and a finite origin");
     if (!vol->hu || ((uintptr_t)vol->hu) % 4 != 0) return fail(c, DDGS_ERR_INVALID_ARG, "null or unaligned volume");
     HIP_TRY(c, hipSetDevice(c->device));
+    DDGS_TRY(refuse_capture(c));
     hipStream_t s = c->stream;
     RadsVol v{vol->nx, vol->ny, vol->nz, vol->spacing[0], vol->spacing[1], vol->spacing[2],
               vol->origin[0], vol->origin[1], vol->origin[2], vol->hu};
@@ -1551,6 +1563,7 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
     if (!images) return fail(c, DDGS_ERR_INVALID_ARG, "null images");
     HIP_TRY(c, hipSetDevice(c->device));
     DDGS_TRY(check_ready(c));
+    DDGS_TRY(refuse_capture(c));
     c->rendered = false;
     DDGS_TRY(ensure_static(c));
     DDGS_TRY(ensure_entries(c, std::max<int64_t>(c->entry_cap, 1)));

@@ -185,3 +185,29 @@ def test_long_tiles_of_few(n, w, h):
             np.testing.assert_array_equal(img.cpu().numpy(), first[0])
     finally:
         r.close()
+
+
+@pytest.mark.parametrize("n", [500, 12000])
+def test_plain_render_refuses_a_capture(n):
+    """A plain render reads its entry total back, at once or later, so a stream
+    that is being captured is refused, and the render works again afterwards."""
+    sc = synth.random_scene(31, n, k=4, L=1, extent=18.0)
+    r = binding.Renderer(0, stream=torch.cuda.Stream())
+    try:
+        r.set_scene(sc)
+        r.set_views(_views(1, 40, 33))
+        torch.cuda.synchronize()
+        img = r.render().clone()
+        out, spare = torch.empty_like(img), torch.zeros(8, device="cuda")
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(r.stream):
+            graph.capture_begin(capture_error_mode="thread_local")
+            spare.add_(1.0)
+            with pytest.raises(binding.DDGSError):
+                binding.ddgs_render(r.ctx, out.data_ptr())
+            graph.capture_end()
+        torch.cuda.synchronize()
+        assert torch.equal(r.render(), img)
+    finally:
+        r.close()
