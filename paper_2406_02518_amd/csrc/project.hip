@@ -424,11 +424,24 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
 
 // ------------------------------------------------------------ backward chain
 
-constexpr int kPoseRound = 768;  // resident blocks of a pose-only backward (launch_project_bwd)
+constexpr int kPoseRound = 1024;  // resident blocks of a pose-only backward (launch_project_bwd)
 
-template <int KMAX, int L>
+//
+// Pose only (POSE; no sums per Gaussian): without the accumulators there is room
+// to hold the next view's first slots, whose loads then run under this view's
+// arithmetic, at four waves per SIMD, and the views' partials stay in LDS, so
+// that the waves meet once per block instead of once per view (64 views x 300k
+// Gaussians 664 -> 505 us, 8 x 50k 17.6 -> 13.5 us; 2 GB of slots and counts:
+// 4 TB/s).  The full instance has no registers for it: with the slots read ahead
+// 769 us (four, spilling) and 825 us (two waves per SIMD) against 733 us at
+// 16 uneven views x 1M.
+constexpr int kPoseViews = 32;  // views of a pose-only block
+template <int KMAX, int L, bool POSE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void project_bwd_kernel(ProjBwdArgs a)
 {
+    // (fused within an expression only: both instances round alike, and a pose
+    // gradient is the same to the bit with and without the others)
+#pragma clang fp contract(on)
     constexpr int KL = L * (L + 2);
     const int n = a.m.n;
     const int i = blockIdx.x * kBlock + threadIdx.x;
@@ -439,12 +452,43 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     const int nd = n - a.m.n_iso, id = ii - a.m.n_iso;
     // this block's views
     const int v0 = (int)blockIdx.y * a.views_per_block, v1 = min(a.V, v0 + a.views_per_block);
-    // the next view's slot count and first slot, read one view ahead (the
-    // first view's before the parameters, since its slot reads wait on them)
-    uint32_t c_next = 0, off_next = 0;
-    if (valid && v0 < v1) {
-        c_next = a.cnt[(size_t)v0 * n + ii];
-        off_next = first_slot(a.slot_bofs, a.slot_nblk, v0, ii, a.slot_lp[(size_t)v0 * n + ii]);
+    // a view's slot count and first slot (the offset is only used when the count
+    // is non-zero; slots past the capacity do not exist, an overflowed step)
+    auto read_count = [&](int v, uint32_t &c, uint32_t &off) {
+        c = 0;
+        off = 0;
+        if (valid && v < v1) {
+            c = a.cnt[(size_t)v * n + ii];
+            off = first_slot(a.slot_bofs, a.slot_nblk, v, ii, a.slot_lp[(size_t)v * n + ii]);
+        }
+    };
+    auto clamp_count = [&](uint32_t &c, uint32_t off) {
+        if (c > 0) {
+            if (off >= a.slot_cap) c = 0;
+            else if ((uint64_t)off + c > a.slot_cap) c = a.slot_cap - off;
+        }
+    };
+    // the next view's, read one view ahead (the first view's before the
+    // parameters, since its slot reads wait on them)
+    uint32_t c_next, off_next;
+    read_count(v0, c_next, off_next);
+    // pose only: the first slots of the next view too, and its successor's count
+    constexpr int AHEAD = 4;
+    float4 f0[AHEAD], f1[AHEAD];
+    uint32_t c_after = 0, off_after = 0;
+    auto read_first = [&](uint32_t c, uint32_t off) {
+        if (c == 0) return;
+#pragma unroll
+        for (int t = 0; t < AHEAD; ++t) {
+            const size_t q = (size_t)off + min((uint32_t)t, c - 1u);
+            f0[t] = a.slot[2 * q];
+            f1[t] = a.slot[2 * q + 1];
+        }
+    };
+    if constexpr (POSE) {
+        clamp_count(c_next, off_next);
+        read_first(c_next, off_next);
+        read_count(v0 + 1, c_after, off_after);
     }
     // isotropic radiosity, or for entangled models the isotropic logit (read
     // early too: values derived from it are computed before the view loop)
@@ -460,19 +504,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     // moving them up)
     const float al = a.gc.alpha[ii];
     float quat0[4] = {1.f, 0.f, 0.f, 0.f}, lsc0[3] = {0.f, 0.f, 0.f}, st0[3] = {0.f, 0.f, 0.f};
-    if (a.per_gaussian) {
+    if (!POSE && a.per_gaussian) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) quat0[q] = a.m.quat[q * n + ii];
 #pragma unroll
         for (int q = 0; q < 3; ++q) lsc0[q] = a.m.log_scale[q * n + ii];
     }
-    if (a.st_grad) {
+    if (!POSE && a.st_grad) {
         st0[0] = a.st_grad[ii];
         st0[1] = a.st_cnt[ii];
         st0[2] = a.st_rad[ii];
     }
     constexpr int NW = kBlock / kWave;
-    __shared__ float sP[2][NW][9];
+    __shared__ float sP[POSE ? kPoseViews : 2][NW][9];
     const int w = threadIdx.x / kWave;
     float h[KL];
 #pragma unroll
@@ -496,21 +540,24 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     for (int v = v0; v < v1; ++v) {
         const ViewDev &V = a.views[v];
         float pose[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        // (the offset is only used when the count is non-zero)
         uint32_t c = c_next, off = off_next;
-        if (valid && v + 1 < v1) {
-            c_next = a.cnt[(size_t)(v + 1) * n + ii];
-            off_next = first_slot(a.slot_bofs, a.slot_nblk, v + 1, ii, a.slot_lp[(size_t)(v + 1) * n + ii]);
-        }
-        // slots past the capacity do not exist (overflowed step)
-        if (c > 0) {
-            if (off >= a.slot_cap) c = 0;
-            else if ((uint64_t)off + c > a.slot_cap) c = a.slot_cap - off;
-        }
         float g7[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        uint32_t e = 0;
+        if constexpr (POSE) {
+#pragma unroll
+            for (int t = 0; t < AHEAD; ++t) {
+                if ((uint32_t)t < c) {
+                    g7[0] += f0[t].x; g7[1] += f0[t].y; g7[2] += f0[t].z; g7[3] += f0[t].w;
+                    g7[4] += f1[t].x; g7[5] += f1[t].y; g7[6] += f1[t].z;
+                }
+            }
+            e = min(c, (uint32_t)AHEAD);
+        } else {
+            read_count(v + 1, c_next, off_next);
+            clamp_count(c, off);
+        }
         // the pair's slots in rectangle order; four entries' loads in flight
         // at once (the sums keep the same order)
-        uint32_t e = 0;
         for (; e + 4u <= c; e += 4u) {
             float4 s0[4], s1[4];
 #pragma unroll
@@ -543,6 +590,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
                 }
             }
         }
+        if constexpr (POSE) {
+            // (in flight during this view's arithmetic)
+            c_next = c_after;
+            off_next = off_after;
+            clamp_count(c_next, off_next);
+            read_first(c_next, off_next);
+            read_count(v + 2, c_after, off_after);
+        }
         Geom g;
         if (c > 0 && project_geom(V, mx, my, mz, cw, a.o, g)) {
             // the slots hold moments of q = dL/ds G over the pixels, with
@@ -559,7 +614,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
                 g7[3] = -al * g7[3];
                 g7[4] = -0.5f * al * g7[4];
             }
-            if (a.st_grad) {
+            if (!POSE && a.st_grad) {
                 // visible in this view: 2D-mean gradient in normalised device
                 // units and the projected radius kappa sqrt(lambda_max)
                 const float gx = g7[0] * (0.5f * (float)V.W), gy = g7[1] * (0.5f * (float)V.H);
@@ -614,6 +669,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
             pose[4] = rmz * gxc - rmx * gzc + 2.0f * (N20 - N02);
             pose[5] = rmx * gyc - rmy * gxc + 2.0f * (N01 - N10);
             // world frame
+            if constexpr (!POSE) {
             gmu[0] += R[0] * gxc + R[3] * gyc + R[6] * gzc;
             gmu[1] += R[1] * gxc + R[4] * gyc + R[7] * gzc;
             gmu[2] += R[2] * gxc + R[5] * gyc + R[8] * gzc;
@@ -632,10 +688,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
             GSw[4] += R[1] * U[2] + R[4] * U[5] + R[7] * U[8];
             GSw[5] += R[2] * U[2] + R[5] * U[5] + R[8] * U[8];
             galpha += g7[5];
+            }
             // radiosity (none when it is overridden)
             if (a.m.c_override) {
             } else if (!is_dir) {
-                zsum += g7[6] * ciso * (1.0f - ciso);
+                if constexpr (!POSE) zsum += g7[6] * ciso * (1.0f - ciso);
             } else {
                 const float rx = mx - V.so[0], ry = my - V.so[1], rz = mz - V.so[2];
                 const float il = 1.0f / sqrtf(rx * rx + ry * ry + rz * rz);
@@ -647,18 +704,20 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
                 for (int r = 0; r < KL; ++r) zl += Y[r] * h[r];
                 const float cd = 1.0f / (1.0f + expf(-zl));
                 const float gz = g7[6] * cd * (1.0f - cd);
-                if (a.m.entangled) zsum += gz;
+                if (!POSE && a.m.entangled) zsum += gz;
                 float wy[KL];
 #pragma unroll
                 for (int r = 0; r < KL; ++r) {
-                    u[r] += gz * Y[r];
+                    if constexpr (!POSE) u[r] += gz * Y[r];
                     wy[r] = gz * h[r];
                 }
                 float gdx, gdy, gdz;
                 sh_basis_grad<L>(dx, dy, dz, wy, gdx, gdy, gdz);
                 const float dd = gdx * dx + gdy * dy + gdz * dz;
                 const float grx = (gdx - dx * dd) * il, gry = (gdy - dy * dd) * il, grz = (gdz - dz * dd) * il;
-                gmu[0] += grx; gmu[1] += gry; gmu[2] += grz;
+                if constexpr (!POSE) {
+                    gmu[0] += grx; gmu[1] += gry; gmu[2] += grz;
+                }
                 pose[6] = R[0] * grx + R[1] * gry + R[2] * grz;
                 pose[7] = R[3] * grx + R[4] * gry + R[5] * grz;
                 pose[8] = R[6] * grx + R[7] * gry + R[8] * grz;
@@ -666,21 +725,36 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
         }
         // per-block pose partials, component-major (deterministic: the
         // waves' sums added in a fixed order; reduced in FP64 later).  Two
-        // buffers: no wave gets two views ahead of the barrier.
+        // buffers: no wave gets two views ahead of the barrier.  Pose only: a
+        // buffer per view of the block and one barrier at the end.
 #pragma unroll
         for (int q = 0; q < 9; ++q) pose[q] = wave_sum_to_lane63(pose[q]);
+        const int pv = POSE ? v - v0 : v & 1;
         if (lane == kWave - 1) {
 #pragma unroll
-            for (int q = 0; q < 9; ++q) sP[v & 1][w][q] = pose[q];
+            for (int q = 0; q < 9; ++q) sP[pv][w][q] = pose[q];
         }
-        __syncthreads();
-        if (threadIdx.x < 9) {
-            const int q = threadIdx.x;
-            float t = sP[v & 1][0][q];
+        if constexpr (!POSE) {
+            __syncthreads();
+            if (threadIdx.x < 9) {
+                const int q = threadIdx.x;
+                float t = sP[pv][0][q];
 #pragma unroll
-            for (int wv = 1; wv < NW; ++wv) t += sP[v & 1][wv][q];
-            a.pose_part[((size_t)v * 9 + q) * gridDim.x + blockIdx.x] = t;
+                for (int wv = 1; wv < NW; ++wv) t += sP[pv][wv][q];
+                a.pose_part[((size_t)v * 9 + q) * gridDim.x + blockIdx.x] = t;
+            }
         }
+    }
+    if constexpr (POSE) {
+        __syncthreads();
+        for (int j = threadIdx.x; j < 9 * (v1 - v0); j += kBlock) {
+            const int pv = j / 9, q = j - 9 * pv;
+            float t = sP[pv][0][q];
+#pragma unroll
+            for (int wv = 1; wv < NW; ++wv) t += sP[pv][wv][q];
+            a.pose_part[((size_t)(v0 + pv) * 9 + q) * gridDim.x + blockIdx.x] = t;
+        }
+        return;
     }
     if (valid && a.st_grad && !(a.skip && (*a.skip & 1u))) {
         a.st_grad[i] = st0[0] + st_grad;
@@ -997,19 +1071,20 @@ hipError_t launch_project_bwd(const ProjBwdArgs &a, hipStream_t s)
         // Views per block.  Sums per Gaussian (gradients, statistics) need
         // every view in one block.  Without them (registration) the views are
         // dealt to more blocks, at one more read of a block's parameters each:
-        // to about five rounds of the card's resident blocks (three waves per
-        // SIMD: 768) where there is more than one anyway, so that the last round
+        // to about five rounds of the card's resident blocks (four waves per
+        // SIMD: 1024) where there is more than one anyway, so that the last round
         // is a small part (64 views x 300k Gaussians, 1172 blocks: 762 -> 657 us
-        // with 16 views each), else to one full round (8 views x 50k, 196
-        // blocks: 26 -> 17 us).
+        // at three waves per SIMD with 16 views each), else to one full round
+        // (8 views x 50k, 196 blocks: 26 -> 17 us).
         ProjBwdArgs b = a;
         b.views_per_block = a.V;
         if (!a.per_gaussian && !a.st_grad) {
             const int want = ((nb >= kPoseRound ? 5 * kPoseRound : kPoseRound) + nb - 1) / nb;
-            b.views_per_block = std::max(1, (a.V + want - 1) / want);
+            b.views_per_block = std::min(kPoseViews, std::max(1, (a.V + want - 1) / want));
         }
         const int groups = (a.V + b.views_per_block - 1) / b.views_per_block;
-        project_bwd_kernel<KK, LL><<<dim3(nb, groups), kBlock, 0, s>>>(b);
+        if (!a.per_gaussian && !a.st_grad) project_bwd_kernel<KK, LL, true><<<dim3(nb, groups), kBlock, 0, s>>>(b);
+        else project_bwd_kernel<KK, LL, false><<<dim3(nb, groups), kBlock, 0, s>>>(b);
         if (a.zbuf && (a.dfeat || a.bpart)) feat_grad_kernel<KK, LL><<<nb, kBlock, 0, s>>>(a);
         return hipGetLastError();
     });
