@@ -433,9 +433,9 @@ constexpr int kPoseRound = 1024;  // resident blocks of a pose-only backward (la
 // that the waves meet once per block instead of once per view (64 views x 300k
 // Gaussians 664 -> 505 us, 8 x 50k 17.6 -> 13.5 us; 2 GB of slots and counts:
 // 4 TB/s).  The full instance has no registers for it: with the slots read ahead
-// 769 us (four, spilling) and 825 us (two waves per SIMD) against 733 us at
+// 769 us (three waves per SIMD, spilling) and 825 us (two) against 733 us at
 // 16 uneven views x 1M.
-constexpr int kPoseViews = 32;  // views of a pose-only block
+constexpr int kPoseViews = 32;  // views of a pose-only block, or between a full one's barriers
 template <int KMAX, int L, bool POSE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void project_bwd_kernel(ProjBwdArgs a)
 {
@@ -516,7 +516,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
         st0[2] = a.st_rad[ii];
     }
     constexpr int NW = kBlock / kWave;
-    __shared__ float sP[POSE ? kPoseViews : 2][NW][9];
+    __shared__ float sP[kPoseViews][NW][9];
     const int w = threadIdx.x / kWave;
     float h[KL];
 #pragma unroll
@@ -537,6 +537,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
 #pragma unroll
     for (int r = 0; r < KL; ++r) u[r] = 0.0f;
 
+    // the partials of `views` views from `first` on
+    auto store_poses = [&](int first, int views) {
+        for (int j = threadIdx.x; j < 9 * views; j += kBlock) {
+            const int jv = j / 9, q = j - 9 * jv;
+            float t = sP[jv][0][q];
+#pragma unroll
+            for (int wv = 1; wv < NW; ++wv) t += sP[jv][wv][q];
+            a.pose_part[((size_t)(first + jv) * 9 + q) * gridDim.x + blockIdx.x] = t;
+        }
+    };
     for (int v = v0; v < v1; ++v) {
         const ViewDev &V = a.views[v];
         float pose[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -724,36 +734,28 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
             }
         }
         // per-block pose partials, component-major (deterministic: the
-        // waves' sums added in a fixed order; reduced in FP64 later).  Two
-        // buffers: no wave gets two views ahead of the barrier.  Pose only: a
-        // buffer per view of the block and one barrier at the end.
+        // waves' sums added in a fixed order; reduced in FP64 later).  They
+        // stay in LDS for kPoseViews views (a pose-only block has no more), so
+        // that the waves seldom meet: with a barrier per view the full instance
+        // took 733 us at 16 uneven views x 1M, without 698 us.
 #pragma unroll
         for (int q = 0; q < 9; ++q) pose[q] = wave_sum_to_lane63(pose[q]);
-        const int pv = POSE ? v - v0 : v & 1;
+        const int pv = POSE ? v - v0 : (v - v0) % kPoseViews;
         if (lane == kWave - 1) {
 #pragma unroll
             for (int q = 0; q < 9; ++q) sP[pv][w][q] = pose[q];
         }
         if constexpr (!POSE) {
-            __syncthreads();
-            if (threadIdx.x < 9) {
-                const int q = threadIdx.x;
-                float t = sP[pv][0][q];
-#pragma unroll
-                for (int wv = 1; wv < NW; ++wv) t += sP[pv][wv][q];
-                a.pose_part[((size_t)v * 9 + q) * gridDim.x + blockIdx.x] = t;
+            if (v == v1 - 1 || pv == kPoseViews - 1) {  // (uniform)
+                __syncthreads();
+                store_poses(v - pv, pv + 1);
+                __syncthreads();
             }
         }
     }
     if constexpr (POSE) {
         __syncthreads();
-        for (int j = threadIdx.x; j < 9 * (v1 - v0); j += kBlock) {
-            const int pv = j / 9, q = j - 9 * pv;
-            float t = sP[pv][0][q];
-#pragma unroll
-            for (int wv = 1; wv < NW; ++wv) t += sP[pv][wv][q];
-            a.pose_part[((size_t)(v0 + pv) * 9 + q) * gridDim.x + blockIdx.x] = t;
-        }
+        store_poses(v0, v1 - v0);
         return;
     }
     if (valid && a.st_grad && !(a.skip && (*a.skip & 1u))) {
