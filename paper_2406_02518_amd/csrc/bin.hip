@@ -385,8 +385,8 @@ constexpr int kBinBlock = 1024;
 
 // U: a thread's pairs loaded together; the first ones before the counters are
 // cleared (a workgroup lives for a few memory latencies: 151 -> 115 us at
-// 64 views x 300k).
-template <int U>
+// 64 views x 300k; with the counts and masks read past the L2, PAST_L2, 102 us).
+template <int U, bool PAST_L2>
 __global__ __launch_bounds__(kBinBlock) void bin_count_kernel(BinArgs a)
 {
     extern __shared__ uint32_t hist[];
@@ -398,13 +398,14 @@ __global__ __launch_bounds__(kBinBlock) void bin_count_kernel(BinArgs a)
     const int i0 = g * a.per, i1 = min(a.n, i0 + a.per);
     uint32_t cnt[U], mask[U];
     uint2 rc[U];
+    auto read = [](const uint32_t *p) { return PAST_L2 ? __builtin_nontemporal_load(p) : *p; };
     auto load = [&](int i) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t r = (int64_t)v * a.n + min(i + u * kBinBlock, i1 - 1);
-            cnt[u] = i + u * kBinBlock < i1 ? a.cnt[r] : 0u;
+            cnt[u] = i + u * kBinBlock < i1 ? read(a.cnt + r) : 0u;
             rc[u] = a.rect[r];
-            mask[u] = a.tmask[r];
+            mask[u] = read(a.tmask + r);
         }
     };
     int i = i0 + (int)threadIdx.x;
@@ -996,8 +997,9 @@ hipError_t launch_bin_count(int n, int V, const uint32_t *cnt, const uint2 *rect
     const int wins = (max_view_tiles + kWin - 1) / kWin;
     const size_t lds = sizeof(uint32_t) * std::min(max_view_tiles, kWin);
     const dim3 grid(a.groups, V, wins);
-    if (per >= kPerLarge) bin_count_kernel<4><<<grid, kBinBlock, lds, s>>>(a);
-    else bin_count_kernel<1><<<grid, kBinBlock, lds, s>>>(a);
+    if (per >= kPerLarge) bin_count_kernel<4, true><<<grid, kBinBlock, lds, s>>>(a);
+    else if (past_l2(n, V)) bin_count_kernel<1, true><<<grid, kBinBlock, lds, s>>>(a);
+    else bin_count_kernel<1, false><<<grid, kBinBlock, lds, s>>>(a);
     bin_colscan_kernel<<<(n_tiles + kColTiles - 1) / kColTiles, kColTiles * kColBlocks, 0, s>>>(a, n_tiles, tile_cnt);
     return hipGetLastError();
 }

@@ -259,6 +259,17 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
     return x;
 }
 
+// Batches whose records (64 B per pair) exceed the 256 MB behind the L2s write
+// and read past them what they do not use again soon.
+inline bool past_l2(int64_t n, int64_t V) { return n * V > (int64_t)4 << 20; }
+
+// a store whose line is not kept in the L2
+__device__ __forceinline__ void store_past_l2(float4 *p, float4 x)
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store(f4{x.x, x.y, x.z, x.w}, reinterpret_cast<f4 *>(p));
+}
+
 // Smallest / largest value over the wave's lanes (the same in every lane).
 // Every lane of the wave must be active.
 template <class OP>

@@ -276,7 +276,7 @@ __device__ __forceinline__ uint32_t tile_mask(const Geom &g, const RenderOpts &o
 // Projection of Gaussian i into view v from its cache values (cw, alpha,
 // ciso; hd(r) gives h_r of a directional Gaussian), then this block's scan of
 // the tile counts for the slot numbering (every thread of the block calls it).
-template <int L, class HD>
+template <int L, bool PAST_L2, class HD>
 __device__ __forceinline__ void project_one(const ModelDev &m, const ViewDev *views, const RenderOpts &o,
                                             const ProjOut &po, int v, int i, const float (&cw)[6], float alpha,
                                             float ciso, HD hd)
@@ -366,6 +366,9 @@ __device__ __forceinline__ void project_one(const ModelDev &m, const ViewDev *vi
     // record wrote 64 partial lines per store; many-view projections are bound
     // by these writes: 64 views x 300k Gaussians 709 -> 396 us, 16 x 1M 589 ->
     // 415 us (one view of 500k, where the cache is computed too, 30 -> 29 us).
+    // PAST_L2 (large batches): non-temporal, since such records are not read
+    // before the caches have been through all of them (16 x 1M 397 -> 375 us, and
+    // the count behind it 111 -> 95 us; 8 x 50k is 0.7 % slower with it).
     __shared__ float4 st[kBlock / kWave][kWave * 3];
     float4 *const sw = &st[w][0];
     sw[lane] = r0;
@@ -379,7 +382,10 @@ __device__ __forceinline__ void project_one(const ModelDev &m, const ViewDev *vi
     for (int q = 0; q < 4; ++q) {
         const int rec = q * 16 + (lane >> 2), part = lane & 3;
         const float4 x = part < 3 ? sw[part * kWave + rec] : make_float4(0.f, 0.f, 0.f, 0.f);
-        if (i0 + rec < n) po.rec[4 * ((size_t)v * n + i0 + rec) + part] = x;
+        if (i0 + rec >= n) continue;
+        float4 *const p = po.rec + 4 * ((size_t)v * n + i0 + rec) + part;
+        if constexpr (PAST_L2) store_past_l2(p, x);
+        else *p = x;
     }
     if (threadIdx.x == 0) po.slot_btot[(size_t)v * gridDim.x + blockIdx.x] = total;
     __syncthreads();  // (wsum is reused by the next call)
@@ -387,7 +393,7 @@ __device__ __forceinline__ void project_one(const ModelDev &m, const ViewDev *vi
 
 // One block per kSlotBlock Gaussians and view (grid.y): the cache is read
 // back from gc.
-template <int L>
+template <int L, bool PAST_L2>
 __global__ __launch_bounds__(kBlock) void project_kernel(ModelDev m, GaussCache gc, const ViewDev *views,
                                                          RenderOpts o, ProjOut po)
 {
@@ -401,7 +407,7 @@ __global__ __launch_bounds__(kBlock) void project_kernel(ModelDev m, GaussCache 
     const bool iso_c = i < m.n_iso || m.entangled;
     const float ciso = (i < n && iso_c) ? gc.ciso[ii] : 0.0f;
     const int nd = n - m.n_iso, id = ii - m.n_iso;
-    project_one<L>(m, views, o, po, blockIdx.y, i, cw, alpha, ciso,
+    project_one<L, PAST_L2>(m, views, o, po, blockIdx.y, i, cw, alpha, ciso,
                    [&](int r) { return gc.hdir[(size_t)r * nd + id]; });
 }
 
@@ -419,7 +425,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
     const int i = blockIdx.x * kBlock + threadIdx.x;
     float cw[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, alpha = 0.0f, ciso = 0.0f, h[KL];
     if (i < m.n) prep_one<KMAX, L>(m, gc, i, sb, sB, cw, alpha, ciso, h);
-    project_one<L>(m, views, o, po, 0, i, cw, alpha, ciso, [&](int r) { return h[r]; });
+    project_one<L, false>(m, views, o, po, 0, i, cw, alpha, ciso, [&](int r) { return h[r]; });
 }
 
 // ------------------------------------------------------------ backward chain
@@ -1058,7 +1064,8 @@ hipError_t launch_prep_project(const ModelDev &m, const GaussCache &gc, const Vi
             prep_project_kernel<KK, LL><<<nb, kBlock, 0, s>>>(m, gc, views, o, po);
         } else {
             prep_kernel<KK, LL><<<nb, kBlock, 0, s>>>(m, gc);
-            project_kernel<LL><<<dim3(nb, V), kBlock, 0, s>>>(m, gc, views, o, po);
+            if (past_l2(m.n, V)) project_kernel<LL, true><<<dim3(nb, V), kBlock, 0, s>>>(m, gc, views, o, po);
+            else project_kernel<LL, false><<<dim3(nb, V), kBlock, 0, s>>>(m, gc, views, o, po);
         }
         return hipGetLastError();
     });
