@@ -367,8 +367,9 @@ ddgs_status ddgs_set_allocator(ddgs_ctx *ctx, ddgs_alloc_fn alloc, ddgs_free_fn 
 
 /* Renders every view (Eq. 1 with Eq. 3) into images (device,
  * ddgs_image_size floats).  Reads the number of tile entries back to size
- * the sort (one stream synchronisation; small inputs, whose buffers hold
- * every tile of every Gaussian, do without).  Keeps what the backward needs
+ * the sort: it waits for the launches that count them, not for the stream
+ * (small inputs, whose buffers hold every tile of every Gaussian, do without).
+ * A stream under capture is refused (DDGS_ERR_HIP).  Keeps what the backward needs
  * (the sorted tile lists, per-pixel final value and last contributor). */
 ddgs_status ddgs_render(ddgs_ctx *ctx, float *images);
 
@@ -521,8 +522,8 @@ ddgs_status ddgs_debug_pair_counts(ddgs_ctx *ctx, int64_t *evaluated, int64_t *c
 
 /* Device time of the last render/backward per stage, ms (filled when timing
  * is enabled with ddgs_enable_timing; captured steps are not timed).  The
- * sort stage is the sum of its two parts: between them a render reads the
- * entry total back to the host, which is not device work. */
+ * sort stage is the sum of its two parts: between them a timed render waits
+ * for the entry total on the host, which is not device work. */
 enum { DDGS_T_PROJECT = 0, DDGS_T_SORT = 1, DDGS_T_RASTER_FWD = 2, DDGS_T_LOSS = 3,
        DDGS_T_RASTER_BWD = 4, DDGS_T_PROJECT_BWD = 5, DDGS_T_COUNT = 6 };
 ddgs_status ddgs_enable_timing(ddgs_ctx *ctx, int enable);
