@@ -75,12 +75,20 @@ struct ScanArgs {
     // long tiles (count > kSortShort): the list, its length, and per-block
     // counts of the three-launch scan
     uint32_t *long_list, *long_n, *long_bsum;
-    // pinned host words (null: none): the entry total (low, high word) and the
-    // number of long tiles, for a host that waits for this launch's end
+    // pinned host words (null: none): the entry total (low, high word), the
+    // number of long tiles and of those beyond kSortLong (or a larger number), for
+    // a host that waits for this launch's end
     uint32_t *host;
 };
 
 __device__ __forceinline__ uint32_t is_long(uint32_t cnt) { return cnt > (uint32_t)kSortShort ? 1u : 0u; }
+// long in the low half, beyond kSortLong in the high half (for sums over at
+// most kTileScanSelfMax tiles)
+__device__ __forceinline__ uint32_t long_class(uint32_t cnt)
+{
+    static_assert(kTileScanSelfMax < 1 << 16, "the halves do not overflow");
+    return is_long(cnt) | (cnt > (uint32_t)kSortLong ? 1u << 16 : 0u);
+}
 
 __device__ void slot_block_scan(uint32_t *slot_btot, int64_t slot_nb, uint32_t carry, uint32_t *wl)
 {
@@ -119,13 +127,14 @@ __device__ void finish_scan(const ScanArgs &a, uint64_t t)
     }
 }
 
-__device__ void finish_long(const ScanArgs &a, uint64_t t, uint32_t n_long)
+__device__ void finish_long(const ScanArgs &a, uint64_t t, uint32_t n_long, uint32_t n_longer)
 {
     *a.long_n = n_long;
     if (a.host) {
         a.host[0] = (uint32_t)t;
         a.host[1] = (uint32_t)(t >> 32);
         a.host[2] = n_long;
+        a.host[3] = n_longer;
     }
 }
 
@@ -154,7 +163,7 @@ __global__ __launch_bounds__(kBlock) void tile_scan_self_kernel(ScanArgs a)
     for (int t = threadIdx.x; t < base; t += kBlock) {
         const uint32_t x = a.tile_cnt[t];
         c += x;
-        cl += is_long(x);
+        cl += long_class(x);
         if (sp) ci += (x + sp - 1u) / sp;
     }
 #pragma unroll
@@ -183,9 +192,9 @@ __global__ __launch_bounds__(kBlock) void tile_scan_self_kernel(ScanArgs a)
     const uint32_t pre = block_scan(v, wl, tot);
     if (t < a.n_tiles) write_range(a, t, carry + pre, v);
     uint32_t ltot;
-    const uint32_t lf = is_long(v);
+    const uint32_t lf = long_class(v);
     const uint32_t lpre = lcarry + block_scan(lf, wl, ltot);
-    if (lf) a.long_list[lpre] = (uint32_t)t;
+    if (lf) a.long_list[lpre & 0xFFFFu] = (uint32_t)t;
     uint32_t itot = 0;
     if (sp) {
         // (chunks of the unclamped count: past a clamped range end an item is
@@ -201,7 +210,7 @@ __global__ __launch_bounds__(kBlock) void tile_scan_self_kernel(ScanArgs a)
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
         finish_scan(a, carry + tot);
-        finish_long(a, carry + tot, lcarry + ltot);
+        finish_long(a, carry + tot, (lcarry + ltot) & 0xFFFFu, (lcarry + ltot) >> 16);
         if (sp) {
             const uint32_t ni = icarry + itot;
             *a.n_items = ni > a.max_items ? a.max_items : ni;
@@ -313,7 +322,7 @@ __global__ __launch_bounds__(1024) void tile_top_kernel(uint64_t *bsum, uint32_t
     }
     if (threadIdx.x == 0) {
         finish_scan(a, carry_s);
-        finish_long(a, carry_s, lcarry_s);
+        finish_long(a, carry_s, lcarry_s, lcarry_s);
     }
 }
 
@@ -572,7 +581,7 @@ __global__ __launch_bounds__(kBinBlock) void bin_scatter_kernel(BinArgs a, const
 // longer ranges, up to 7168 in LDS (two workgroups of 74 KB per CU), with
 // 1024 threads in a second launch.  Each launch leaves the other's tiles.
 constexpr int kSortShortBlock = 512;
-constexpr int kSortLong = 7168, kSortLongBlock = 1024;
+constexpr int kSortLongBlock = 1024;
 constexpr int kSortLongGrid = 512;  // two workgroups per CU
 // With no more listed tiles than CUs one workgroup per CU is all there is to
 // run, so the launch takes an instance that holds 14336 entries in 131 KB of
@@ -581,7 +590,10 @@ constexpr int kSortLongGrid = 512;  // two workgroups per CU
 // 15 us).  With more tiles two smaller workgroups per CU are faster.  With no
 // more tiles at all than CUs that instance takes every tile in one launch: the
 // short ranges are sorted beside the long ones (100k Gaussians / 256^2, 256
-// tiles: 7.5 + 12.9 -> 12.6 us).
+// tiles: 7.5 + 12.9 -> 12.6 us); with no more than fit at two per CU the
+// 7168-entry instance does, as long as no longer range is known (200k / 384 x
+// 300, 456 tiles: 6.8 + 10.0 -> 8.5 us; 500k / 512^2, 1024 tiles, would go from
+// 9.2 + 11.7 to 19.4 us only).
 constexpr int kSortLongBig = 14336, kSortLongBigGrid = 256;
 // Buckets: 2048 for the short ranges, 4096 beyond: the LDS that a second array
 // of bucket starts took ranks longer ranges against half as many entries.
@@ -1021,14 +1033,20 @@ hipError_t launch_bin_scatter(int n, int V, const uint32_t *cnt, const uint2 *re
     return hipGetLastError();
 }
 
-bool tile_sort_one_launch(int n_tiles) { return n_tiles <= kSortLongBigGrid; }
+bool tile_sort_one_launch(int n_tiles, int64_t n_longer)
+{
+    return n_tiles <= kSortLongBigGrid || (n_tiles <= kSortLongGrid && n_longer == 0);
+}
 
 hipError_t launch_tile_sort(const uint2 *ranges, const uint32_t *tile_cnt, int n_tiles, const uint2 *ent, uint2 *tmp,
                             uint32_t *tval, uint32_t capacity, TileSort how, hipStream_t s)
 {
     if (n_tiles <= 0) return hipSuccess;
     const int take_long = how == TileSort::kShort ? 0 : 1;
-    if (how == TileSort::kWide)
+    if (how == TileSort::kWide && n_tiles > kSortLongBigGrid)
+        tile_sort_kernel<kSortLong, kSortLongBlock><<<n_tiles, kSortLongBlock, 0, s>>>(
+            ranges, tile_cnt, n_tiles, ent, tmp, tval, capacity, take_long);
+    else if (how == TileSort::kWide)
         tile_sort_kernel<kSortLongBig, kSortLongBlock><<<n_tiles, kSortLongBlock, 0, s>>>(
             ranges, tile_cnt, n_tiles, ent, tmp, tval, capacity, take_long);
     else

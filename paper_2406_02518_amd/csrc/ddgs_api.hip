@@ -125,7 +125,7 @@ struct ddgs_ctx {
     // has, through global memory).  Fewer workgroups than long tiles only
     // take several each; the lists are the same either way.
     int long_grid = 0;
-    int64_t long_seen = -1, long_seen_n = -1;
+    int64_t long_seen = -1, longer_seen = -1, long_seen_n = -1;
     int long_seen_tiles = -1;
 
     // target image of the captured step's loss (uploaded with the view table)
@@ -136,7 +136,7 @@ struct ddgs_ctx {
     // tiles of a plain render; the totals of a volume.  (A copy to pageable
     // memory instead: 254 -> 217 us for a 256^3 volume's dual sampling.)
     struct HostWords {
-        uint32_t total[3];
+        uint32_t total[4];
         RadsTotals rads;
     } *host = nullptr;
     hipEvent_t host_event = nullptr;
@@ -497,6 +497,9 @@ int64_t long_tiles_seen(const ddgs_ctx *c)
     return c->long_seen_n == c->model.n && c->long_seen_tiles == c->n_tiles ? c->long_seen : -1;
 }
 
+// the same for tiles beyond kSortLong
+int64_t longer_tiles_seen(const ddgs_ctx *c) { return long_tiles_seen(c) < 0 ? -1 : c->longer_seen; }
+
 // long-range sort grid of a captured step (see ddgs_ctx::long_grid)
 int captured_long_grid(const ddgs_ctx *c)
 {
@@ -719,7 +722,8 @@ ddgs_status enqueue_back(ddgs_ctx *c, int64_t cap, float *images, const TileSort
     const int n = (int)c->model.n;
     if (c->timing) (void)hipEventRecord(c->ev_sort_tail_s, c->stream);
     const TileSort how = ahead ? *ahead : c->long_grid <= 0 ? TileSort::kAll
-                         : tile_sort_one_launch(c->n_tiles) ? TileSort::kWide : TileSort::kShort;
+                         : tile_sort_one_launch(c->n_tiles, longer_tiles_seen(c)) ? TileSort::kWide
+                                                                                  : TileSort::kShort;
     if (!ahead) DDGS_TRY(enqueue_sort_head(c, cap, how));
     if (how == TileSort::kShort)
         HIP_TRY(c, launch_tile_sort_long(buf<uint2>(c, "ranges"), c->n_tiles, buf<uint2>(c, "bin_ent"),
@@ -1602,15 +1606,16 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
         bool ahead = c->entry_cap > 1 && !c->timing && !c->keep_unsorted;
         // (long tiles, if an earlier render of this layout had some and there
         // are few tiles, in the same launch; else in a second one, if there are any)
-        const TileSort how = tile_sort_one_launch(c->n_tiles) && long_tiles_seen(c) > 0 ? TileSort::kWide
-                                                                                         : TileSort::kShort;
+        const bool one = long_tiles_seen(c) > 0 && tile_sort_one_launch(c->n_tiles, longer_tiles_seen(c));
+        const TileSort how = one ? TileSort::kWide : TileSort::kShort;
         if (ahead) DDGS_TRY(enqueue_sort_head(c, held, how));
         HIP_TRY(c, hipEventSynchronize(c->host_event));
         const uint32_t *const sc = c->host->total;
         const uint64_t total = (uint64_t)sc[0] | ((uint64_t)sc[1] << 32);
         const int64_t n_long = sc[2];
-        if (c->long_seen_n != c->model.n || c->long_seen_tiles != c->n_tiles) c->long_seen = -1;
+        if (c->long_seen_n != c->model.n || c->long_seen_tiles != c->n_tiles) c->long_seen = c->longer_seen = -1;
         c->long_seen = std::max(c->long_seen, n_long);
+        c->longer_seen = std::max<int64_t>(c->longer_seen, sc[3]);
         c->long_seen_n = c->model.n;
         c->long_seen_tiles = c->n_tiles;
         c->long_grid = (int)std::min<int64_t>(n_long, 1 << 30);

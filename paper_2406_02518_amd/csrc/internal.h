@@ -396,10 +396,12 @@ hipError_t launch_ranges(const uint32_t *keys, const uint32_t *m_dev, int64_t m_
 // [slot_ssum_words(slot_nb)] scratch).
 // With `items` (only where tile_scan_makes_items: the one-launch scan), the
 // same launch also writes the work items of `split` entries per tile (what
-// launch_items writes).  host (or NULL): three pinned host words for the entry
-// total and the number of long tiles, valid once the launch has ended.
+// launch_items writes).  host (or NULL): four pinned host words for the entry
+// total, the number of long tiles and of those beyond kSortLong (the three-launch
+// scan gives the former for both), valid once the launch has ended.
 constexpr int kTileScanSelfMax = 16384;
 constexpr int kSortShort = 2560;  // longest range the per-tile sort's first launch takes
+constexpr int kSortLong = 7168;   // longest one its second launch holds in LDS at two workgroups per CU
 struct TileItems {
     int split;
     uint32_t *cnt, *base;
@@ -453,10 +455,11 @@ hipError_t launch_bin_small(int n, int V, const uint32_t *cnt, const uint2 *rect
 // end beyond capacity are left alone.  Long tiles (lt, listed by the tile scan)
 // are left to launch_tile_sort_long (kShort), sorted too but through global
 // memory (kAll: meant for steps that rarely or never have any), or sorted too
-// in an instance with the LDS for them (kWide: one workgroup per CU, meant for
-// tile_sort_one_launch, no more tiles than CUs).
+// in an instance with the LDS for them (kWide: meant for tile_sort_one_launch, no
+// more tiles than CUs, or than two per CU with n_longer = 0 known beyond
+// kSortLong; n_longer < 0: not known).
 enum class TileSort { kShort, kAll, kWide };
-bool tile_sort_one_launch(int n_tiles);
+bool tile_sort_one_launch(int n_tiles, int64_t n_longer);
 hipError_t launch_tile_sort(const uint2 *ranges, const uint32_t *tile_cnt, int n_tiles, const uint2 *ent, uint2 *tmp,
                             uint32_t *tval, uint32_t capacity, TileSort how, hipStream_t s);
 // The listed long tiles, taken round-robin by at most long_grid workgroups

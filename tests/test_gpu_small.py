@@ -211,3 +211,25 @@ def test_plain_render_refuses_a_capture(n):
         assert torch.equal(r.render(), img)
     finally:
         r.close()
+
+
+def test_long_tiles_at_two_per_compute_unit():
+    """Between one and two tiles per compute unit the ranges are sorted in one
+    launch while none is known beyond what that launch's LDS holds: a first
+    render, one that has seen the layout, then one of the same layout with a range
+    beyond it, and one that knows of it, each equal to a fresh renderer's."""
+    opts, views = dict(tile_w=16, tile_h=16, split=256), [synth.view(320, 310, 0.9, 1000.0, 600.0, 20.0)]
+    even = synth.random_scene(37, 20000, k=4, L=1, extent=18.0, std_range=(0.5, 1.5))
+    heap = synth.random_scene(38, 20000, k=4, L=1, extent=5.0, std_range=(0.5, 1.5))
+    a = make_renderer()
+    try:
+        for sc, low, high in [(even, 2560, 7168), (even, 2560, 7168), (heap, 7168, 20001), (heap, 7168, 20001)]:
+            b = make_renderer()
+            got, exp = _lists(a, sc, views, opts), _lists(b, sc, views, opts)
+            b.close()
+            for x, y in zip(got, exp):
+                np.testing.assert_array_equal(x, y)
+            rg = got[2].reshape(-1, 2).astype(np.int64)
+            assert rg.shape[0] == 400 and low < (rg[:, 1] - rg[:, 0]).max() <= high
+    finally:
+        a.close()
