@@ -143,6 +143,31 @@ __device__ __forceinline__ int next_item(const RasterArgs &a, int &iter, int *sh
     return a.queue ? (int)a.queue[k] : k;
 }
 
+// Half-widths of a box around the mean that holds every pixel the cut-off test
+// may pass, from the stored conic (kw: kappa, widened by 0.1 % for the rounding
+// of the means, the half-widths and the box tests).  The ellipse's are kappa
+// sqrt(A11 / det) and kappa sqrt(A00 / det) with det = A00 A11 - A01^2, which
+// cancels for long thin footprints (by a relative 2^-24 A00 A11 / det: 6 % at
+// 1000 x 0.5 pixels).  The test rounds d^T A d by at most 8 2^-24 (A00 dx^2 +
+// 2 |A01 dx dy| + A11 dy^2), so what it passes lies in the ellipse of the form
+// with A00 and A11 smaller and |A01| larger by that factor, whose determinant is
+// at least det - 33 2^-24 A00 A11; with det's own rounding, 3e-6 A00 A11 are
+// taken off.  Where nothing is left (footprints longer than about 1200 times
+// their width, or products near the smallest float) the box has no bounds, and
+// its tests are written so that a NaN passes them too.
+__device__ __forceinline__ float2 cutoff_box(float kw, float A00, float A01, float A11)
+{
+    const float p = A00 * A11;
+    const float det = __fmaf_rn(-A01, A01, p) - 3e-6f * p;
+    const float idet = det > 1e-30f ? 1.0f / det : INFINITY;
+    return make_float2(kw * sqrtf(A11 * idet), kw * sqrtf(A00 * idet));
+}
+// the interval [x - h, x + h] reaches [lo, hi]
+__device__ __forceinline__ bool box_reaches(float x, float h, float lo, float hi)
+{
+    return !(x - h > hi) & !(x + h < lo);
+}
+
 // SPLIT: work items are chunks (a.split > 0), so no per-pixel last index is
 // kept; COUNT: pair counters on.
 template <int TW, int TH, bool SPLIT, bool COUNT>
@@ -285,9 +310,8 @@ __global__ __launch_bounds__(TW *TH) void raster_fwd_kernel(RasterArgs a)
 // an 8 x 8 part of the tile and lane l covers pixel (4 (q % 2) + r % 4,
 // 4 (q / 2) + r / 4) of it (q = l / 16, r = l % 16), so that each 16-lane row
 // covers one cell; each batch of entries is listed per cell whose pixel
-// centres the ellipse's bounding box reaches (half-widths kappa
-// sqrt(Sigma_xx), kappa sqrt(Sigma_yy) of Sigma = A^-1, widened by 0.1 %, far
-// above the rounding of the per-pixel test), and the wave runs the longest of
+// centres the ellipse's bounding box reaches (cutoff_box, which holds every
+// pixel that the rounded per-pixel test passes), and the wave runs the longest of
 // its four lists, the lanes of each cell taking their own list's entries in
 // depth order (shorter lists are padded with a record that no pixel reaches).
 // An entry left out of a cell's list misses all its pixels, where the update
@@ -394,15 +418,14 @@ __global__ __launch_bounds__(TW *TH) void raster_fwd_cells_kernel(RasterArgs a)
                 over = r1.y > 0.5f * smax;
                 // bounding box of the cut-off ellipse against the cells'
                 // pixel-centre ranges [4 i + 0.5, 4 i + 3.5] of the tile
-                const float idet = 1.0f / (r0.z * r1.x - r0.w * r0.w);
-                const float hx = kw * sqrtf(r1.x * idet), hy = kw * sqrtf(r0.z * idet);
+                const float2 h = cutoff_box(kw, r0.z, r0.w, r1.x);
                 const float ux = r0.x - tx0, uy = r0.y - ty0;
 #pragma unroll
                 for (int i = 0; i < CX; ++i)
-                    rm |= (ux - hx <= 4.0f * i + 3.5f && ux + hx >= 4.0f * i + 0.5f) ? 1u << i : 0u;
+                    rm |= box_reaches(ux, h.x, 4.0f * i + 0.5f, 4.0f * i + 3.5f) ? 1u << i : 0u;
 #pragma unroll
                 for (int i = 0; i < CY; ++i)
-                    rm |= (uy - hy <= 4.0f * i + 3.5f && uy + hy >= 4.0f * i + 0.5f) ? 1u << (CX + i) : 0u;
+                    rm |= box_reaches(uy, h.y, 4.0f * i + 0.5f, 4.0f * i + 3.5f) ? 1u << (CX + i) : 0u;
                 scale_conic(r0, r1);
                 s0[tid] = r0;
                 s1[tid] = r1;
@@ -989,15 +1012,13 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TW * TH 
                 if constexpr (MULTI) {
                     // the parts of the tile whose pixel centres the bounding
                     // box of the cut-off ellipse reaches (as in the forward)
-                    const float idet = 1.0f / (r0.z * r1.x - r0.w * r0.w);
-                    const float hx = kw * sqrtf(r1.x * idet), hy = kw * sqrtf(r0.z * idet);
+                    const float2 h = cutoff_box(kw, r0.z, r0.w, r1.x);
                     const float ux = r0.x - (float)(tx * TW), uy = r0.y - (float)(ty * TH);
                     uint32_t m = 0u;
 #pragma unroll
                     for (int q = 0; q < NW; ++q) {
                         const float ox = 8.0f * (q % PX), oy = 8.0f * (q / PX);
-                        const bool in = ux - hx <= ox + 7.5f && ux + hx >= ox + 0.5f && uy - hy <= oy + 7.5f &&
-                                        uy + hy >= oy + 0.5f;
+                        const bool in = box_reaches(ux, h.x, ox + 0.5f, ox + 7.5f) & box_reaches(uy, h.y, oy + 0.5f, oy + 7.5f);
                         m |= in ? 1u << q : 0u;
                     }
                     reach[tid] = (uint8_t)m;
