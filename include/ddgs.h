@@ -406,7 +406,9 @@ ddgs_status ddgs_loss(ddgs_ctx *ctx, int kind, const float *images, const float 
  * and step counts unchanged), so an overflowed replay can be run again.
  * The model and views may change contents between replays but not shapes
  * (n, views' W/H); ddgs_set_model / ddgs_set_views with a different shape
- * drop the graph.
+ * drop the graph, and so does a plain ddgs_render between replays that needs
+ * larger buffers than the step holds (more tile entries than its capacity and
+ * than any render before).
  *
  * Retry after DDGS_ERR_CAPACITY: ddgs_step_report returns what the last
  * ddgs_check found -- the number of replays whose updates were skipped

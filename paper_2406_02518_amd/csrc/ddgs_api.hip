@@ -182,8 +182,21 @@ ddgs_status fail(ddgs_ctx *c, ddgs_status s, const std::string &msg)
 constexpr size_t kWsAlign = 256;
 size_t ws_round(size_t x) { return (x + kWsAlign - 1) / kWsAlign * kWsAlign; }
 
+void drop_graph(ddgs_ctx *c);
+
+// Whether a captured step may hold the buffer's address: every buffer but those
+// of the calls outside the render path.
+bool held_by_steps(const char *name)
+{
+    static const char *const others[] = {"rads_", "knn_", "dn_", "dbg_", "aux_", "tune_", "capture_probe_img", "fit_mv_next"};
+    for (const char *o : others)
+        if (std::strncmp(name, o, std::strlen(o)) == 0) return false;
+    return true;
+}
+
 // (Re)allocates a workspace buffer of at least `bytes` (contents undefined),
-// with room to grow by a quarter.  With a caller workspace the buffer is
+// with room to grow by a quarter.  A captured step that holds the buffer which
+// moves is dropped.  With a caller workspace the buffer is
 // carved from it (a grown buffer takes new space; the region is never
 // reused before ddgs_set_workspace is called again).  In a dry run only the
 // sizes of fresh buffers are added up.  Never called while a stream capture
@@ -199,6 +212,10 @@ ddgs_status ensure(ddgs_ctx *c, const char *name, size_t bytes, void **out)
     }
     DevBuf &b = c->bufs[name];
     if (b.bytes < bytes) {
+        if (b.p && c->exec && held_by_steps(name)) {
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
+            drop_graph(c);
+        }
         if (c->ws_base) {
             if (c->ws_used + nb > c->ws_size)
                 return fail(c, DDGS_ERR_OOM, std::string("workspace too small: ") + name + " needs " +
@@ -1577,10 +1594,10 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
     // every tile of every Gaussian: such a render needs no total from the
     // device and does not wait for it (the stream synchronisation and the
     // launches it held back cost about 30 us of a 2000-Gaussian call).  A
-    // caller region is not grown for it.
+    // caller region is not grown for it, nor are the buffers a captured step holds.
     const int64_t worst = c->model.n * (int64_t)c->n_tiles;
     const bool small = VN > 0 && bin_small(c->model.n, (int64_t)c->views_h.size(), c->n_tiles) &&
-                       worst <= kSmallEntries && (c->entry_cap >= worst || !c->ws_base);
+                       worst <= kSmallEntries && (c->entry_cap >= worst || (!c->ws_base && !c->exec));
     if (small) {
         DDGS_TRY(ensure_entries(c, std::max(worst, c->entry_cap)));
         DDGS_TRY(enqueue_front(c, (uint32_t)std::min<int64_t>(c->entry_cap, 0xFFFFFFFFll), false, true));

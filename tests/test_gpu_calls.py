@@ -1,0 +1,107 @@
+"""Calls between and inside other calls: plain renders beside a captured step,
+and calls on a stream that the caller is capturing."""
+import numpy as np
+import pytest
+
+from paper_2406_02518_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _view(az=0.0, w=40, h=33):
+    return synth.view(w, h, 0.9, 1000.0, 600.0, az)
+
+
+def _renderer():
+    return binding.Renderer(0, stream=torch.cuda.Stream())
+
+
+def _scene(n, seed=31):
+    return synth.random_scene(seed, n, k=4, L=1, extent=18.0)
+
+
+def _capture(r, capacity):
+    r.set_options(capacity=capacity)
+    P = r.image_size()
+    s = {"img": torch.empty(P, device="cuda"), "dl": torch.empty(P, device="cuda"),
+         "loss": torch.empty(len(r.views), device="cuda"), "grads": r.alloc_grads(),
+         "w": torch.sin(torch.arange(P, device="cuda", dtype=torch.float32))}
+    torch.cuda.synchronize()
+    with torch.cuda.stream(r.stream):
+        binding.ddgs_step_capture(r.ctx, binding.LOSS_LINEAR, s["w"].data_ptr(), 0.0, s["img"].data_ptr(),
+                                  s["dl"].data_ptr(), s["loss"].data_ptr(), r.grads_struct(s["grads"]))
+    return s
+
+
+def _fresh(sc, views, w):
+    """Image, gradients and entry total from a renderer of their own."""
+    r = _renderer()
+    try:
+        r.set_scene(sc)
+        r.set_views(views)
+        img = r.render().clone()
+        g = {k: v.clone() for k, v in r.backward(w).items()}
+        torch.cuda.synchronize()
+        return img, g, r.num_rendered()
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("n,w,h", [(2000, 64, 64), (700, 40, 33), (9000, 60, 52)])
+def test_plain_render_between_replays(n, w, h):
+    """A step captured with an explicit capacity that fits (there is no sizing
+    render), a plain render of the same scene, whose one-workgroup binning would
+    take every tile of every Gaussian, and the replays behind it: the same
+    results, with what the renderer may have freed in other tensors' hands."""
+    sc, views = _scene(n), [_view(10.0, w, h)]
+    wt = torch.sin(torch.arange(w * h, device="cuda", dtype=torch.float32))
+    exp, exp_g, need = _fresh(sc, views, wt)
+    r = _renderer()
+    try:
+        r.set_scene(sc)
+        r.set_views(views)
+        s = _capture(r, need + 100)
+        for _ in range(3):
+            assert torch.equal(r.render(), exp)
+            torch.cuda.synchronize()
+            others = [torch.full((sz,), 7.0, device="cuda") for sz in (1 << 12, 1 << 16, 1 << 18, 1 << 20)]
+            s["img"].zero_()
+            for g in s["grads"].values():
+                g.zero_()
+            torch.cuda.synchronize()
+            binding.ddgs_step_launch(r.ctx)
+            assert r.check_step() == 0
+            torch.cuda.synchronize()
+            assert torch.equal(s["img"], exp)
+            for k in exp_g:
+                assert torch.equal(s["grads"][k], exp_g[k]), k
+            assert all(bool((x == 7.0).all()) for x in others)
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("n", [2000, 9000])
+def test_plain_render_that_outgrows_a_step_drops_it(n):
+    """A plain render that needs more entries than the step was captured for moves
+    the buffers that the step holds: the launch is refused, and a new capture
+    works."""
+    sc, views = _scene(n), [_view(10.0, 60, 52)]
+    exp, _, need = _fresh(sc, views, torch.ones(60 * 52, device="cuda"))
+    r = _renderer()
+    try:
+        r.set_scene(sc)
+        r.set_views(views)
+        _capture(r, need // 4)
+        assert torch.equal(r.render(), exp)
+        with pytest.raises(binding.DDGSError) as e:
+            binding.ddgs_step_launch(r.ctx)
+        assert e.value.status == binding.ERR_STATE
+        s = _capture(r, need)
+        binding.ddgs_step_launch(r.ctx)
+        assert r.check_step() == 0
+        torch.cuda.synchronize()
+        assert torch.equal(s["img"], exp)
+    finally:
+        r.close()
