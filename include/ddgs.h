@@ -369,8 +369,10 @@ ddgs_status ddgs_set_allocator(ddgs_ctx *ctx, ddgs_alloc_fn alloc, ddgs_free_fn 
  * ddgs_image_size floats).  Reads the number of tile entries back to size
  * the sort: it waits for the launches that count them, not for the stream
  * (small inputs, whose buffers hold every tile of every Gaussian, do without).
- * A stream under capture is refused (DDGS_ERR_HIP).  Keeps what the backward needs
- * (the sorted tile lists, per-pixel final value and last contributor). */
+ * A stream under capture is refused (DDGS_ERR_HIP) before anything is enqueued
+ * or changed, except for an empty model whose views a call before has uploaded.
+ * Keeps what the backward needs (the sorted tile lists, per-pixel final value and
+ * last contributor). */
 ddgs_status ddgs_render(ddgs_ctx *ctx, float *images);
 
 /* Gradient of L = sum_p dL_dimages[p] I(p) with respect to the model and the

@@ -277,7 +277,7 @@ ddgs_status ensure_host(ddgs_ctx *c, size_t stage = 0)
     return DDGS_OK;
 }
 
-// A call that reads a result back, or leaves one to be read back, belongs in no
+// A call that reads a result back, or captures a graph itself, belongs in no
 // graph that a caller captures.
 ddgs_status refuse_capture(ddgs_ctx *c)
 {
@@ -446,10 +446,16 @@ ddgs_status prepare_views(ddgs_ctx *c)
     return DDGS_OK;
 }
 
-ddgs_status check_ready(ddgs_ctx *c)
+ddgs_status check_set(ddgs_ctx *c)
 {
     if (!c->has_model) return fail(c, DDGS_ERR_STATE, "no model set");
     if (c->views_h.empty()) return fail(c, DDGS_ERR_STATE, "no views set");
+    return DDGS_OK;
+}
+
+ddgs_status check_ready(ddgs_ctx *c)
+{
+    DDGS_TRY(check_set(c));
     return prepare_views(c);
 }
 
@@ -1583,8 +1589,13 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
     if (!c) return DDGS_ERR_INVALID_ARG;
     if (!images) return fail(c, DDGS_ERR_INVALID_ARG, "null images");
     HIP_TRY(c, hipSetDevice(c->device));
+    DDGS_TRY(check_set(c));
+    // before the view table is uploaded: recorded into the caller's graph, the
+    // upload would not run, and later renders would take the table for current.
+    // (An empty model's render reads nothing back, and goes into a graph if there
+    // is nothing to upload or clear.)
+    if (c->model.n > 0 || c->views_dirty || !buf<uint32_t>(c, "scalars")) DDGS_TRY(refuse_capture(c));
     DDGS_TRY(check_ready(c));
-    DDGS_TRY(refuse_capture(c));
     c->rendered = false;
     DDGS_TRY(ensure_static(c));
     DDGS_TRY(ensure_entries(c, std::max<int64_t>(c->entry_cap, 1)));
@@ -1715,6 +1726,8 @@ ddgs_status ddgs_step_capture(ddgs_ctx *c, int kind, const float *target, float 
     if (!images || !dL || !g || !target) return fail(c, DDGS_ERR_INVALID_ARG, "null argument");
     if (kind < 0 || kind > 2) return fail(c, DDGS_ERR_INVALID_ARG, "unknown loss kind");
     HIP_TRY(c, hipSetDevice(c->device));
+    DDGS_TRY(check_set(c));
+    DDGS_TRY(refuse_capture(c));  // (before the view table's upload, as in ddgs_render)
     DDGS_TRY(check_ready(c));
     if (c->model.n == 0) return fail(c, DDGS_ERR_UNSUPPORTED, "a captured step needs n > 0");
     if (!c->stream) return fail(c, DDGS_ERR_INVALID_ARG, "capture needs a non-default stream");
@@ -2256,6 +2269,8 @@ ddgs_status ddgs_autotune(ddgs_ctx *c, const char *cache_path, int repeats, floa
     if (!c) return DDGS_ERR_INVALID_ARG;
     if (repeats < 1) repeats = 5;
     HIP_TRY(c, hipSetDevice(c->device));
+    DDGS_TRY(check_set(c));
+    DDGS_TRY(refuse_capture(c));
     DDGS_TRY(check_ready(c));
     const int64_t n = c->model.n, k = c->model.k, KL = kl_of(c->model.L), V = (int64_t)c->views_h.size();
     const ddgs_options base = c->opt;

@@ -105,3 +105,84 @@ def test_plain_render_that_outgrows_a_step_drops_it(n):
         assert torch.equal(s["img"], exp)
     finally:
         r.close()
+
+
+def _refused(r, calls):
+    """Runs the calls on r's stream while it is being captured; each is refused, and
+    the graph around them stays whole."""
+    spare = torch.zeros(8, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(r.stream):
+        graph.capture_begin(capture_error_mode="thread_local")
+        spare.add_(1.0)
+        for call in calls:
+            with pytest.raises(binding.DDGSError) as e:
+                call()
+            assert e.value.status == binding.ERR_HIP
+        graph.capture_end()
+    for _ in range(3):
+        graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(spare, torch.full_like(spare, 3.0))
+
+
+@pytest.mark.parametrize("n", [500, 12000])
+@pytest.mark.parametrize("fresh", [False, True])
+def test_refused_calls_leave_the_views_to_the_next_render(n, fresh):
+    """New views set before a call that a capturing stream refuses: nothing of the
+    call goes into the graph, and the render behind the capture sees these views."""
+    sc, old, new = _scene(n), [_view(10.0)], [_view(55.0)]
+    exp, _, _ = _fresh(sc, new, torch.ones(40 * 33, device="cuda"))
+    other, _, _ = _fresh(sc, old, torch.ones(40 * 33, device="cuda"))
+    assert not torch.equal(exp, other)
+    r = _renderer()
+    try:
+        r.set_scene(sc)
+        if not fresh:
+            r.set_views(old)
+            r.render()
+        r.set_views(new)
+        P = r.image_size()
+        out = [torch.empty(P, device="cuda") for _ in range(3)]
+        loss, grads = torch.empty(1, device="cuda"), r.alloc_grads()
+        calls = [lambda: binding.ddgs_render(r.ctx, out[0].data_ptr()),
+                 lambda: binding.ddgs_step_capture(r.ctx, binding.LOSS_LINEAR, out[0].data_ptr(), 0.0,
+                                                   out[1].data_ptr(), out[2].data_ptr(), loss.data_ptr(),
+                                                   r.grads_struct(grads)),
+                 lambda: binding.ddgs_autotune(r.ctx)]
+        for c in calls:
+            _refused(r, [c])
+        _refused(r, calls)
+        assert torch.equal(r.render(), exp)
+    finally:
+        r.close()
+
+
+def test_empty_model_renders_into_a_graph():
+    """Nothing is read back for an empty model: its render goes into the caller's
+    graph, unless there are views to upload first."""
+    r = _renderer()
+    try:
+        sc = synth.random_scene(3, 0, k=4, L=1)
+        r.set_scene(sc)
+        r.set_views([_view()])
+        out = r.render()
+        assert not out.any()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(r.stream):
+            graph.capture_begin(capture_error_mode="thread_local")
+            binding.ddgs_render(r.ctx, out.data_ptr())
+            graph.capture_end()
+        for _ in range(3):
+            out.fill_(5.0)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert not out.any()
+        r.set_views([_view(30.0)])
+        _refused(r, [lambda: binding.ddgs_render(r.ctx, out.data_ptr())])
+        assert not r.render().any()
+    finally:
+        r.close()
