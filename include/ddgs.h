@@ -31,7 +31,8 @@
  *   - All device work is enqueued on the context's stream (settable, e.g.
  *     torch's current stream).  Entry points do not synchronise the stream
  *     except where stated (ddgs_render reads the number of tile entries back,
- *     except for small inputs, where ddgs_num_rendered does if it is asked;
+ *     except for small inputs, where ddgs_num_rendered waits for it if it is
+ *     asked before it is there (on a stream under capture too);
  *     ddgs_check and the debug getters synchronise).
  *   - Every function returns a ddgs_status; on failure nothing is written to
  *     the outputs that the status code does not mention, and the message is
@@ -463,7 +464,8 @@ ddgs_status ddgs_autotune(ddgs_ctx *ctx, const char *cache_path, int repeats, fl
  * at k = 8, L = 1. */
 ddgs_status ddgs_param_count(int k, int L, int64_t n, int64_t *per_gaussian, int64_t *shared);
 
-/* Number of (tile, Gaussian) entries of the last render. */
+/* Number of (tile, Gaussian) entries of the last render.  Enqueues nothing, and
+ * may be called while the stream is being captured. */
 ddgs_status ddgs_num_rendered(const ddgs_ctx *ctx, int64_t *n);
 
 enum {

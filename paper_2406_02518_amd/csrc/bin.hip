@@ -79,6 +79,11 @@ struct ScanArgs {
     // number of long tiles and of those beyond kSortLong (or a larger number), for
     // a host that waits for this launch's end
     uint32_t *host;
+    // one pinned word (null: none) that receives tag (high half) and the entry
+    // total in one store, for a host that looks for it without waiting for a launch
+    // (one-workgroup binning, whose totals stay far below 2^32)
+    uint64_t *small_host;
+    uint32_t tag;
 };
 
 __device__ __forceinline__ uint32_t is_long(uint32_t cnt) { return cnt > (uint32_t)kSortShort ? 1u : 0u; }
@@ -892,6 +897,9 @@ __global__ __launch_bounds__(kSmallBlock) void bin_small_kernel(BinArgs b, ScanA
     if (tid == 0) {
         finish_scan(a, tot[0]);
         *a.long_n = tot[1];
+        if (a.small_host)
+            __hip_atomic_store(a.small_host, ((uint64_t)a.tag << 32) | tot[0], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
         if (a.split) {
             *a.n_items = tot[2] > a.max_items ? a.max_items : tot[2];
             a.counter[0] = 0u;
@@ -917,12 +925,13 @@ hipError_t launch_bin_small(int n, int V, const uint32_t *cnt, const uint2 *rect
                             const uint32_t *zkey, const ViewDev *views, int n_tiles, uint32_t *tile_cnt,
                             uint2 *ranges, uint32_t *cursor, uint32_t capacity, uint64_t *total, uint32_t *m_out,
                             uint32_t *flags, uint32_t *skipped, unsigned long long *need, uint32_t *slot_btot,
-                            int64_t slot_nb, const TileItems *it, const LongTiles &lt, uint2 *out, hipStream_t s)
+                            int64_t slot_nb, const TileItems *it, const LongTiles &lt, uint2 *out,
+                            uint64_t *small_host, uint32_t tag, hipStream_t s)
 {
     if (!bin_small(n, V, n_tiles) || slot_nb > kSmallSlotBlocks || !lt.list || !lt.n) return hipErrorInvalidValue;
     const BinArgs b{n, V, 1, n, cnt, rect, tmask, zkey, views, nullptr};
     ScanArgs a{tile_cnt, n_tiles, ranges, cursor, capacity, total, m_out, flags, skipped, need, slot_btot, slot_nb,
-               0u, nullptr, nullptr, nullptr, 0u, nullptr, nullptr, lt.list, lt.n, lt.bsum, nullptr};
+               0u, nullptr, nullptr, nullptr, 0u, nullptr, nullptr, lt.list, lt.n, lt.bsum, nullptr, small_host, tag};
     if (it && it->split > 0) {
         a.split = (uint32_t)it->split;
         a.item_cnt = it->cnt;
@@ -946,7 +955,7 @@ hipError_t launch_tile_scan(const uint32_t *tile_cnt, int n_tiles, uint2 *ranges
                             const TileItems *it, const LongTiles &lt, uint32_t *host, hipStream_t s)
 {
     ScanArgs a{tile_cnt, n_tiles, ranges, cursor, capacity, total, m_out, flags, skipped, need, slot_btot, slot_nb,
-               0u, nullptr, nullptr, nullptr, 0u, nullptr, nullptr, lt.list, lt.n, lt.bsum, host};
+               0u, nullptr, nullptr, nullptr, 0u, nullptr, nullptr, lt.list, lt.n, lt.bsum, host, nullptr, 0u};
     if (!lt.list || !lt.n) return hipErrorInvalidValue;
     const int nb = (n_tiles + kBlock - 1) / kBlock;
     if (n_tiles <= kTileScanSelfMax) {

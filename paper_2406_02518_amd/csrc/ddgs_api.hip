@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -15,6 +16,7 @@
 #include <mutex>
 #include <sstream>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/ddgs.h"
@@ -101,8 +103,11 @@ struct ddgs_ctx {
     uint64_t model_gen = 0, views_gen = 0, opt_gen = 0;
     uint64_t r_model_gen = ~0ull, r_views_gen = ~0ull, r_opt_gen = ~0ull;
     int64_t M = 0;             // entries of the last render (-1: on the device only)
-    bool total_pending = false;  // M is read back when it is asked for (a small plain render)
-    hipStream_t total_stream = nullptr;  // the stream that render ran on
+    // a small plain render does not wait for its total, which arrives in
+    // host->small: M is taken from there when it is asked for
+    bool total_pending = false;
+    uint32_t total_tag = 0;              // the number of that render
+    hipStream_t total_stream = nullptr;  // the stream it ran on
     uint32_t *queue = nullptr;
     int64_t entry_cap = 0;     // capacity of the entry buffers
     bool keep_unsorted = false;
@@ -135,8 +140,11 @@ struct ddgs_ctx {
     // (host_event: behind that kernel): the entry total and the number of long
     // tiles of a plain render; the totals of a volume.  (A copy to pageable
     // memory instead: 254 -> 217 us for a 256^3 volume's dual sampling.)
+    // small: number (high half) and entry total of the last small plain render
+    // whose binning has run.
     struct HostWords {
         uint32_t total[4];
+        uint64_t small;
         RadsTotals rads;
     } *host = nullptr;
     hipEvent_t host_event = nullptr;
@@ -257,12 +265,15 @@ ddgs_status ensure(ddgs_ctx *c, const char *name, size_t bytes, void **out)
     return DDGS_OK;
 }
 
+ddgs_status resolve_total(ddgs_ctx *c);
+
 // The pinned host memory: the words above and at least `stage` bytes of staging
 // behind them, one allocation (each costs a context's first call some 50 us).
 ddgs_status ensure_host(ddgs_ctx *c, size_t stage = 0)
 {
     if (c->host && c->stage_bytes >= stage) return DDGS_OK;
     if (c->host) {
+        DDGS_TRY(resolve_total(c));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         HIP_TRY(c, hipHostFree(c->host));
     }
@@ -272,29 +283,31 @@ ddgs_status ensure_host(ddgs_ctx *c, size_t stage = 0)
     void *p = nullptr;
     HIP_TRY(c, hipHostMalloc(&p, sizeof(*c->host) + stage + 1024, hipHostMallocCoherent));
     c->host = (ddgs_ctx::HostWords *)p;
+    c->host->small = 0;
     c->stage_host = c->host + 1;
     c->stage_bytes = stage + 1024;
     return DDGS_OK;
+}
+
+bool stream_captured(ddgs_ctx *c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+    return st != hipStreamCaptureStatusNone;
 }
 
 // A call that reads a result back, or captures a graph itself, belongs in no
 // graph that a caller captures.
 ddgs_status refuse_capture(ddgs_ctx *c)
 {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
-    if (st != hipStreamCaptureStatusNone)
+    if (stream_captured(c))
         return fail(c, DDGS_ERR_HIP, "the stream is being captured (ddgs_step_capture captures a step)");
     return DDGS_OK;
 }
 
-ddgs_status resolve_total(ddgs_ctx *c);
-
 // Releases every workspace buffer (library-owned ones are freed).
 void release_buffers(ddgs_ctx *c)
 {
-    (void)resolve_total(c);  // (the entry total is in one of them)
-    c->total_pending = false;
     (void)hipStreamSynchronize(c->stream);
     if (!c->ws_base)
         for (auto &kv : c->bufs) {
@@ -636,16 +649,27 @@ void set_items(ddgs_ctx *c, RasterArgs &ra, bool backward)
     ra.queue_counter = c->opt.persistent ? counter_ptr(c) + (backward ? 1 : 0) : nullptr;
 }
 
-// Reads the entry total of a small plain render, which did not wait for it.
+// The entry total of a small plain render, which did not wait for it: waits for
+// the render's stream, or, where that would void the caller's capture or the
+// stream is no longer the context's, only for the word itself (the binning was
+// enqueued outside any capture, so it runs whatever the host does).
 ddgs_status resolve_total(ddgs_ctx *c)
 {
     if (!c->total_pending) return DDGS_OK;
-    uint64_t t = 0;
-    HIP_TRY(c, hipSetDevice(c->device));
-    if (c->stream != c->total_stream) HIP_TRY(c, hipDeviceSynchronize());  // (the old stream may be gone)
-    HIP_TRY(c, hipMemcpyAsync(&t, total_ptr(c), sizeof(t), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    c->M = (int64_t)t;
+    auto word = [c] { return __atomic_load_n(&c->host->small, __ATOMIC_ACQUIRE); };
+    auto arrived = [c, word] { return (uint32_t)(word() >> 32) == c->total_tag; };
+    if (!arrived()) {
+        HIP_TRY(c, hipSetDevice(c->device));
+        if (c->stream == c->total_stream && !stream_captured(c)) {
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
+        } else {
+            const auto t0 = std::chrono::steady_clock::now();
+            while (!arrived() && std::chrono::steady_clock::now() - t0 < std::chrono::seconds(60))
+                std::this_thread::sleep_for(std::chrono::microseconds(20));
+        }
+        if (!arrived()) return fail(c, DDGS_ERR_HIP, "the last render's entry total did not arrive");
+    }
+    c->M = (int64_t)(uint32_t)word();
     c->total_pending = false;
     return DDGS_OK;
 }
@@ -696,7 +720,8 @@ ddgs_status enqueue_front(ddgs_ctx *c, uint32_t capacity, bool captured, bool sm
                                     capacity, total_ptr(c), mdev_ptr(c), flags_ptr(c),
                                     captured ? skipped_ptr(c) : nullptr, captured ? need_ptr(c) : nullptr,
                                     buf<uint32_t>(c, "slot_btot"), (int64_t)V * slot_blocks(m.n),
-                                    fold ? &ti : nullptr, long_tiles(c), buf<uint2>(c, "bin_ent"), s));
+                                    fold ? &ti : nullptr, long_tiles(c), buf<uint2>(c, "bin_ent"),
+                                    captured ? nullptr : &c->host->small, c->total_tag, s));
         stage_end(c, DDGS_T_SORT);
         return DDGS_OK;
     }
@@ -1061,7 +1086,10 @@ void ddgs_destroy(ddgs_ctx *c)
     if (c->ev_sort_tail_e) (void)hipEventDestroy(c->ev_sort_tail_e);
     if (c->stage_event) (void)hipEventDestroy(c->stage_event);
     if (c->host_event) (void)hipEventDestroy(c->host_event);
-    if (c->host) (void)hipHostFree(c->host);
+    if (c->host) {
+        (void)resolve_total(c);  // (nothing writes there any more)
+        (void)hipHostFree(c->host);
+    }
     delete c;
 }
 
@@ -1611,6 +1639,8 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
                        worst <= kSmallEntries && (c->entry_cap >= worst || (!c->ws_base && !c->exec));
     if (small) {
         DDGS_TRY(ensure_entries(c, std::max(worst, c->entry_cap)));
+        DDGS_TRY(ensure_host(c));
+        if (++c->total_tag == 0) c->total_tag = 1;  // (0: none has run)
         DDGS_TRY(enqueue_front(c, (uint32_t)std::min<int64_t>(c->entry_cap, 0xFFFFFFFFll), false, true));
         c->M = -1;
         c->total_pending = true;

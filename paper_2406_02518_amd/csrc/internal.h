@@ -442,13 +442,15 @@ hipError_t launch_bin_scatter(int n, int V, const uint32_t *cnt, const uint2 *re
                               hipStream_t s);
 // Count, scan, work items and scatter of a small input in one launch of one
 // workgroup (where bin_small says so), with the results of launch_bin_count,
-// launch_tile_scan and launch_bin_scatter.
+// launch_tile_scan and launch_bin_scatter.  small_host (or NULL): a pinned word
+// that receives tag << 32 | entry total.
 bool bin_small(int64_t n, int64_t V, int64_t n_tiles);
 hipError_t launch_bin_small(int n, int V, const uint32_t *cnt, const uint2 *rect, const uint32_t *tmask,
                             const uint32_t *zkey, const ViewDev *views, int n_tiles, uint32_t *tile_cnt,
                             uint2 *ranges, uint32_t *cursor, uint32_t capacity, uint64_t *total, uint32_t *m_out,
                             uint32_t *flags, uint32_t *skipped, unsigned long long *need, uint32_t *slot_btot,
-                            int64_t slot_nb, const TileItems *items, const LongTiles &lt, uint2 *out, hipStream_t s);
+                            int64_t slot_nb, const TileItems *items, const LongTiles &lt, uint2 *out,
+                            uint64_t *small_host, uint32_t tag, hipStream_t s);
 // Sorts every tile's range of ent by (depth key, index) and writes the
 // indices to tval; tmp (same layout as ent) is scratch for ranges longer than
 // the LDS holds.  tile_cnt is the tile scan's of the same step.  Ranges that

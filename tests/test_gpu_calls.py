@@ -186,3 +186,63 @@ def test_empty_model_renders_into_a_graph():
         assert not r.render().any()
     finally:
         r.close()
+
+
+@pytest.mark.parametrize("n", [1, 500, 8000])
+def test_num_rendered_on_a_capturing_stream(n):
+    """After a small render, whose total is not read back: the call returns it
+    and leaves the caller's capture whole."""
+    r = _renderer()
+    try:
+        r.set_scene(_scene(n))
+        r.set_views([_view()])
+        r.render()
+        exp = r.num_rendered()
+        spare = torch.zeros(8, device="cuda")
+        torch.cuda.synchronize()
+        r.render()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(r.stream):
+            graph.capture_begin(capture_error_mode="thread_local")
+            spare.add_(1.0)
+            got = r.num_rendered()
+            spare.add_(1.0)
+            graph.capture_end()
+        assert got == exp == r.num_rendered()
+        for _ in range(3):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(spare, torch.full_like(spare, 6.0))
+    finally:
+        r.close()
+
+
+def test_num_rendered_after_a_change_of_stream():
+    """The total of a small render is there for a context that has gone on to
+    another stream, also while that one is being captured, and after the workspace
+    has been given back."""
+    sc, views = _scene(700), [_view(20.0)]
+    _, _, exp = _fresh(sc, views, torch.ones(40 * 33, device="cuda"))
+    r = _renderer()
+    try:
+        r.set_scene(sc)
+        r.set_views(views)
+        other, spare = torch.cuda.Stream(), torch.zeros(8, device="cuda")
+        torch.cuda.synchronize()
+        r.render()
+        binding.ddgs_set_stream(r.ctx, other.cuda_stream)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(other):
+            graph.capture_begin(capture_error_mode="thread_local")
+            spare.add_(1.0)
+            got = r.num_rendered()
+            graph.capture_end()
+        binding.ddgs_set_stream(r.ctx, r.stream.cuda_stream)
+        assert got == exp
+        r.render()
+        torch.cuda.synchronize()
+        r.set_workspace(None)
+        assert r.num_rendered() == exp
+    finally:
+        r.close()
