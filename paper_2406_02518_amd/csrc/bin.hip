@@ -820,9 +820,11 @@ tile_sort_long_kernel(
 // workgroup's LDS from the counting to the scatter, so four launches (five
 // with the work items) become one and no count matrix is written.  At 2000
 // Gaussians / 64^2 each of those launches took 3 to 4 us of the card and about
-// 5 us of host time; this one takes 11 us.  The limit is where one workgroup's
-// two walks over the pairs (eight per thread) still cost less than that.
-constexpr int kSmallBlock = 1024, kSmallPairs = 8192, kSmallTiles = 4096, kSmallSlotBlocks = 1024;
+// 5 us of host time; this one takes 11 us there, and about 1.2 us more per 1000
+// entries, which all go through one CU: its callers bound the entries too.  Beyond
+// four pairs per thread the walks alone cost what the launches do (plain renders
+// of 8000 Gaussians, 11000 to 16000 entries: 78 to 86 us against 71 to 82).
+constexpr int kSmallBlock = 1024, kSmallPairs = 4096, kSmallTiles = 4096, kSmallSlotBlocks = 1024;
 
 __global__ __launch_bounds__(kSmallBlock) void bin_small_kernel(BinArgs b, ScanArgs a, uint32_t *tile_cnt, uint2 *out)
 {

@@ -108,6 +108,12 @@ struct ddgs_ctx {
     bool total_pending = false;
     uint32_t total_tag = 0;              // the number of that render
     hipStream_t total_stream = nullptr;  // the stream it ran on
+    // The entry total last known of a plain render, with its Gaussian count and
+    // tiles (expected_entries), and the same of the small renders since number
+    // small_first, whose totals are known once they are in host->small.
+    int64_t seen_total = -1, seen_n = -1, small_n = -1;
+    int seen_tiles = -1, small_tiles = -1;
+    uint32_t small_first = 0;
     uint32_t *queue = nullptr;
     int64_t entry_cap = 0;     // capacity of the entry buffers
     bool keep_unsorted = false;
@@ -678,6 +684,44 @@ ddgs_status resolve_total(ddgs_ctx *c)
 // each, and the raster grids cover all of them (up to 4096 workgroups at chunks
 // of 64, most of which find no work).
 constexpr int64_t kSmallEntries = (int64_t)1 << 18;
+// The one-workgroup binning scatters every entry from one CU, so what it costs
+// grows with the entries, which pairs and tiles do not bound.  Whole renders
+// against the general binning's with its wait, us: 2000 Gaussians, 7265 entries
+// 62 / 84, 14893 77 / 84, 24720 89 / 88, 91997 161 / 128; 4000 Gaussians, 14447
+// 75 / 84; 8000 Gaussians, 74477 150 / 95.  Where the total is not known, the most
+// there can be may be twice as large.
+constexpr int64_t kSmallPays = 16384;
+// A captured step waits for nothing either way and saves the launches only (us per
+// step: 500 Gaussians, 1010 entries 60 / 64; 1000, 12186 108 / 111; 2000, 9649 105 /
+// 105, 24720 122 / 116; 4000, 6326 95 / 89; 8000 Gaussians at 1024^2, 10.8 M 11500 /
+// 4700): fewer pairs, and a capacity of at most twice 12288 entries (the library's
+// own is twice the need).
+constexpr int64_t kSmallStepPairs = 2048, kSmallStepCapacity = 2 * 12288;
+bool small_step(const ddgs_ctx *c, int64_t capacity)
+{
+    const int64_t n = c->model.n, V = (int64_t)c->views_h.size();
+    return bin_small(n, V, c->n_tiles) && n * V <= kSmallStepPairs && capacity <= kSmallStepCapacity;
+}
+
+void note_total(ddgs_ctx *c, int64_t total, int64_t n, int tiles)
+{
+    c->seen_total = total;
+    c->seen_n = n;
+    c->seen_tiles = tiles;
+}
+
+// Entries of the last plain render of this Gaussian count and tile layout whose
+// total the host knows (-1: none), without waiting for one.
+int64_t expected_entries(ddgs_ctx *c)
+{
+    if (c->small_first && c->host) {
+        const uint64_t w = __atomic_load_n(&c->host->small, __ATOMIC_ACQUIRE);
+        // (numbers small_first .. total_tag)
+        if (w && (uint32_t)(w >> 32) - c->small_first <= c->total_tag - c->small_first)
+            note_total(c, (int64_t)(uint32_t)w, c->small_n, c->small_tiles);
+    }
+    return c->seen_n == c->model.n && c->seen_tiles == c->n_tiles ? c->seen_total : -1;
+}
 
 // Projection (which also counts every tile's entries) and the scan of the
 // tile counts into the tile ranges (stages shared by the plain and the
@@ -1635,12 +1679,18 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
     // launches it held back cost about 30 us of a 2000-Gaussian call).  A
     // caller region is not grown for it, nor are the buffers a captured step holds.
     const int64_t worst = c->model.n * (int64_t)c->n_tiles;
-    const bool small = VN > 0 && bin_small(c->model.n, (int64_t)c->views_h.size(), c->n_tiles) &&
-                       worst <= kSmallEntries && (c->entry_cap >= worst || (!c->ws_base && !c->exec));
+    const bool fits = VN > 0 && bin_small(c->model.n, (int64_t)c->views_h.size(), c->n_tiles) && worst <= kSmallEntries;
+    const int64_t expected = fits ? expected_entries(c) : -1;
+    const bool small = fits && (expected >= 0 ? expected <= kSmallPays : worst <= 2 * kSmallPays) && (c->entry_cap >= worst || (!c->ws_base && !c->exec));
     if (small) {
         DDGS_TRY(ensure_entries(c, std::max(worst, c->entry_cap)));
         DDGS_TRY(ensure_host(c));
         if (++c->total_tag == 0) c->total_tag = 1;  // (0: none has run)
+        if (c->small_first == 0 || c->small_n != c->model.n || c->small_tiles != c->n_tiles) {
+            c->small_first = c->total_tag;
+            c->small_n = c->model.n;
+            c->small_tiles = c->n_tiles;
+        }
         DDGS_TRY(enqueue_front(c, (uint32_t)std::min<int64_t>(c->entry_cap, 0xFFFFFFFFll), false, true));
         c->M = -1;
         c->total_pending = true;
@@ -1680,6 +1730,8 @@ ddgs_status ddgs_render(ddgs_ctx *c, float *images)
         ddgs_status st = DDGS_OK;
         if (total >= 0xFFFFFFFFull) st = fail(c, DDGS_ERR_CAPACITY, "more than 2^32-1 tile entries");
         c->M = (int64_t)total;
+        note_total(c, c->M, c->model.n, c->n_tiles);
+        c->small_first = 0;
         if (st == DDGS_OK && c->M > c->entry_cap) {
             st = ensure_entries(c, c->M);
             c->items_folded = false;
@@ -1805,7 +1857,7 @@ ddgs_status ddgs_step_capture(ddgs_ctx *c, int kind, const float *target, float 
     c->timing = false;
     HIP_TRY(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
     c->long_grid = captured_long_grid(c);
-    ddgs_status st = enqueue_front(c, (uint32_t)c->step_cap, true, bin_small(c->model.n, (int64_t)c->views_h.size(), c->n_tiles));
+    ddgs_status st = enqueue_front(c, (uint32_t)c->step_cap, true, small_step(c, c->step_cap));
     if (st == DDGS_OK) st = enqueue_back(c, c->step_cap, images);
     if (st == DDGS_OK) st = enqueue_loss(c, kind, images, target, lambda, loss_out, dL, true);
     if (st == DDGS_OK) st = enqueue_backward(c, dL, g, c->step_cap, true);
@@ -2422,7 +2474,7 @@ ddgs_status ddgs_autotune(ddgs_ctx *c, const char *cache_path, int repeats, floa
             st = fail(c, DDGS_ERR_HIP, "tuner: hipStreamBeginCapture failed");
             return;
         }
-        st = enqueue_front(c, (uint32_t)cap, true, bin_small(n, V, c->n_tiles));
+        st = enqueue_front(c, (uint32_t)cap, true, small_step(c, cap));
         if (st == DDGS_OK) st = enqueue_back(c, cap, img);
         if (st == DDGS_OK) st = enqueue_backward(c, dL, &g, cap, true);
         const hipError_t ec = hipStreamEndCapture(c->stream, &graph);
