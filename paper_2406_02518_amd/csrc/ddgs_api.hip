@@ -195,6 +195,8 @@ ddgs_status fail(ddgs_ctx *c, ddgs_status s, const std::string &msg)
 
 constexpr size_t kWsAlign = 256;
 size_t ws_round(size_t x) { return (x + kWsAlign - 1) / kWsAlign * kWsAlign; }
+// what ensure() takes for a buffer of `bytes`
+size_t ensured_bytes(size_t bytes) { return ws_round(bytes + bytes / 4 + 256); }
 
 void drop_graph(ddgs_ctx *c);
 
@@ -218,7 +220,7 @@ bool held_by_steps(const char *name)
 ddgs_status ensure(ddgs_ctx *c, const char *name, size_t bytes, void **out)
 {
     if (bytes == 0) bytes = 16;
-    const size_t nb = ws_round(bytes + bytes / 4 + 256);
+    const size_t nb = ensured_bytes(bytes);
     if (c->dry_run) {
         c->dry_total += nb;
         *out = nullptr;
@@ -639,6 +641,46 @@ ddgs_status aux_sort_ws(ddgs_ctx *c, int64_t n, SortWs *ws)
     *ws = SortWs{buf<uint32_t>(c, "aux_counts"), buf<uint32_t>(c, "aux_tot"), buf<uint64_t>(c, "aux_bsum"),
                  c->bufs["aux_counts"].bytes / sizeof(uint32_t), c->bufs["aux_bsum"].bytes / sizeof(uint64_t)};
     return DDGS_OK;
+}
+
+// Buffers of the neighbour search through a grid of G cells (N points of a volume
+// with M crossings).  The search without them gives the same scales, so where they
+// do not fit (DDGS_ERR_OOM) the call goes on without.  Of a caller region, which
+// carves what it gives once and for all, they take no more than the volume pass
+// left of the 16 bytes per voxel it once took (it takes less than 3).
+struct KnnBufs {
+    uint32_t *cnt, *cur, *list;  // cnt[G]: length of the list of open points
+    uint64_t *tot;
+    float4 *sorted;
+    SortWs ws;
+};
+ddgs_status knn_buffers(ddgs_ctx *c, int64_t N, int64_t G, int64_t M, KnnBufs *b)
+{
+    if (c->ws_base) {
+        const RadsVol &v = c->rads_vol;
+        const int64_t voxels = (int64_t)v.nx * v.ny * v.nz, m = std::max(M, G);
+        size_t need = 0;
+        auto add = [&](const char *name, size_t bytes) {
+            auto it = c->bufs.find(name);
+            if (it == c->bufs.end() || it->second.bytes < bytes) need += ensured_bytes(bytes);
+        };
+        add("knn_cnt", sizeof(uint32_t) * (size_t)(G + 1));
+        add("knn_cur", sizeof(uint32_t) * (size_t)G);
+        add("knn_list", sizeof(uint32_t) * (size_t)N);
+        add("knn_sorted", sizeof(float4) * (size_t)N);
+        add("knn_tot", sizeof(uint64_t));
+        add("aux_counts", sizeof(uint32_t) * (size_t)sort_counts_words(m));
+        add("aux_tot", sizeof(uint32_t) * (size_t)kSortTotWords);
+        add("aux_bsum", sizeof(uint64_t) * (size_t)sort_blocksum_words(m));
+        if (need > c->ws_size - c->ws_used || need > 13 * (size_t)voxels)
+            return fail(c, DDGS_ERR_OOM, "no room for the neighbour grid in the caller's region");
+    }
+    DDGS_TRY(ensure_t(c, "knn_cnt", (size_t)G + 1, &b->cnt));
+    DDGS_TRY(ensure_t(c, "knn_cur", (size_t)G, &b->cur));
+    DDGS_TRY(ensure_t(c, "knn_list", (size_t)N, &b->list));
+    DDGS_TRY(ensure_t(c, "knn_sorted", (size_t)N, &b->sorted));
+    DDGS_TRY(ensure_t(c, "knn_tot", 1, &b->tot));
+    return aux_sort_ws(c, std::max(M, G), &b->ws);
 }
 
 // Work-item fields shared by the forward and backward raster launches.
@@ -1583,25 +1625,21 @@ ddgs_status ddgs_rads_sample(ddgs_ctx *c, int64_t n1, const uint32_t *mc_keys, i
     }
     HIP_TRY(c, launch_rads_draws(c->rads_vol, buf<uint64_t>(c, "rads_swt"), buf<uint16_t>(c, "rads_w16"), dw_draws, n2,
                                  points, N, n1e, s));
-    if (log_scale && !knn_uses_grid(N)) {
-        HIP_TRY(c, launch_knn_brute(points, N, log_scale, s));
-    } else if (log_scale) {
+    if (log_scale) {
         const KnnGrid g = knn_grid(c->rads_vol, N);
         const int64_t G = g.cells();
-        uint32_t *cnt, *cur, *list;
-        uint64_t *tot;
-        float4 *sorted;
-        DDGS_TRY(ensure_t(c, "knn_cnt", (size_t)G + 1, &cnt));  // [G]: length of the list of open points
-        DDGS_TRY(ensure_t(c, "knn_cur", (size_t)G, &cur));
-        DDGS_TRY(ensure_t(c, "knn_list", (size_t)N, &list));
-        DDGS_TRY(ensure_t(c, "knn_sorted", (size_t)N, &sorted));
-        DDGS_TRY(ensure_t(c, "knn_tot", 1, &tot));
-        SortWs ws;
-        DDGS_TRY(aux_sort_ws(c, std::max(M, G), &ws));
-        HIP_TRY(c, launch_fill_u32(cnt, 0u, G + 1, s));
-        HIP_TRY(c, launch_knn_count(g, points, N, cnt, s));
-        HIP_TRY(c, launch_exclusive_scan(cnt, nullptr, cur, G, ws, tot, s));
-        HIP_TRY(c, launch_knn_grid(g, points, N, cur, sorted, list, cnt + G, log_scale, s));
+        KnnBufs b;
+        const ddgs_status st = knn_uses_grid(N) ? knn_buffers(c, N, G, M, &b) : DDGS_ERR_OOM;
+        if (st == DDGS_OK) {
+            HIP_TRY(c, launch_fill_u32(b.cnt, 0u, G + 1, s));
+            HIP_TRY(c, launch_knn_count(g, points, N, b.cnt, s));
+            HIP_TRY(c, launch_exclusive_scan(b.cnt, nullptr, b.cur, G, b.ws, b.tot, s));
+            HIP_TRY(c, launch_knn_grid(g, points, N, b.cur, b.sorted, b.list, b.cnt + G, log_scale, s));
+        } else if (st == DDGS_ERR_OOM) {
+            HIP_TRY(c, launch_knn_brute(points, N, log_scale, s));
+        } else {
+            return st;
+        }
     }
     *n_iso = n1e + n2 / 2;
     return DDGS_OK;
