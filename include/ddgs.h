@@ -295,7 +295,7 @@ ddgs_status ddgs_fit_reset_opacity(ddgs_ctx *ctx, float max_alpha);
  * ddgs_rads_sample writes N = min(n1, M) + n2 points, device [3][N]:
  *   - P^mc: the min(n1, M) crossings with the smallest mc_keys (device [M]
  *     u32, random keys supplied by the caller; ties by edge order), in key
- *     order;
+ *     order (any keys; quickest where they are spread evenly over an interval);
  *   - P^dw: n2 voxel centres, draw j picking the first voxel whose inclusive
  *     weight sum exceeds dw_draws[j] (device [n2] u64, uniform in [0, W)
  *     supplied by the caller; a draw >= W picks the last voxel).

@@ -1604,42 +1604,51 @@ ddgs_status ddgs_rads_sample(ddgs_ctx *c, int64_t n1, const uint32_t *mc_keys, i
     if (n2 > 0 && c->rads_w == 0) return fail(c, DDGS_ERR_STATE, "the volume has no weight (constant radiodensity)");
     HIP_TRY(c, hipSetDevice(c->device));
     hipStream_t s = c->stream;
+    uint32_t *k0 = nullptr, *k1 = nullptr, *v0 = nullptr, *v1 = nullptr;
+    uint2 *range = nullptr;
+    SortWs ws{};
+    const bool picks = n1e > 0 && M <= kPickMax;
     if (n1e > 0) {
-        uint32_t *k0, *k1, *v0, *v1;
         DDGS_TRY(ensure_t(c, "rads_k0", (size_t)M, &k0));
         DDGS_TRY(ensure_t(c, "rads_k1", (size_t)M, &k1));
         DDGS_TRY(ensure_t(c, "rads_v0", (size_t)M, &v0));
         DDGS_TRY(ensure_t(c, "rads_v1", (size_t)M, &v1));
-        SortWs ws;
+        if (picks) DDGS_TRY(ensure_t(c, "rads_krange", kKeyRangeBlocks, &range));
         DDGS_TRY(aux_sort_ws(c, M, &ws));
-        if (M <= kPickMax) {
-            HIP_TRY(c, radix_top_pass(mc_keys, M, k1, v1, ws, s));
-            HIP_TRY(c, launch_rads_pick(ws.tot, k1, v1, k0, v0, n1e, buf<float>(c, "rads_pts"), M, points, N, s));
-        } else {
-            HIP_TRY(c, hipMemcpyAsync(k0, mc_keys, sizeof(uint32_t) * M, hipMemcpyDeviceToDevice, s));
-            HIP_TRY(c, launch_iota(v0, M, s));
-            bool in_k1 = false;
-            HIP_TRY(c, radix_sort_pairs(k0, v0, k1, v1, M, nullptr, 32, ws, &in_k1, s));
-            HIP_TRY(c, launch_rads_gather(buf<float>(c, "rads_pts"), M, in_k1 ? v1 : v0, n1e, points, N, s));
-        }
     }
-    HIP_TRY(c, launch_rads_draws(c->rads_vol, buf<uint64_t>(c, "rads_swt"), buf<uint16_t>(c, "rads_w16"), dw_draws, n2,
-                                 points, N, n1e, s));
-    if (log_scale) {
-        const KnnGrid g = knn_grid(c->rads_vol, N);
-        const int64_t G = g.cells();
-        KnnBufs b;
-        const ddgs_status st = knn_uses_grid(N) ? knn_buffers(c, N, G, M, &b) : DDGS_ERR_OOM;
-        if (st == DDGS_OK) {
-            HIP_TRY(c, launch_fill_u32(b.cnt, 0u, G + 1, s));
-            HIP_TRY(c, launch_knn_count(g, points, N, b.cnt, s));
-            HIP_TRY(c, launch_exclusive_scan(b.cnt, nullptr, b.cur, G, b.ws, b.tot, s));
-            HIP_TRY(c, launch_knn_grid(g, points, N, b.cur, b.sorted, b.list, b.cnt + G, log_scale, s));
-        } else if (st == DDGS_ERR_OOM) {
-            HIP_TRY(c, launch_knn_brute(points, N, log_scale, s));
-        } else {
-            return st;
-        }
+    bool grid = log_scale && knn_uses_grid(N);
+    KnnGrid g{};
+    KnnBufs b{};
+    if (grid) {
+        g = knn_grid(c->rads_vol, N);
+        const ddgs_status st = knn_buffers(c, N, g.cells(), M, &b);
+        if (st != DDGS_OK && st != DDGS_ERR_OOM) return st;
+        grid = st == DDGS_OK;
+        // (the sort's buffers are the grid's too, which may have grown them)
+        if (grid) ws = b.ws;
+        else if (n1e > 0) DDGS_TRY(aux_sort_ws(c, M, &ws));
+    }
+    const int64_t G = g.cells();
+    HIP_TRY(c, launch_rads_begin(c->rads_vol,
+                                 RadsBegin{buf<uint64_t>(c, "rads_swt"), buf<uint16_t>(c, "rads_w16"), dw_draws, n2, N, n1e,
+                                           points, mc_keys, M, range, grid ? b.cnt : nullptr, G + 1},
+                                 s));
+    if (picks) {
+        HIP_TRY(c, radix_top_pass(mc_keys, M, k1, v1, ws, range, s));
+        HIP_TRY(c, launch_rads_pick(ws.tot, range, k1, v1, k0, v0, n1e, buf<float>(c, "rads_pts"), M, points, N, s));
+    } else if (n1e > 0) {
+        HIP_TRY(c, hipMemcpyAsync(k0, mc_keys, sizeof(uint32_t) * M, hipMemcpyDeviceToDevice, s));
+        HIP_TRY(c, launch_iota(v0, M, s));
+        bool in_k1 = false;
+        HIP_TRY(c, radix_sort_pairs(k0, v0, k1, v1, M, nullptr, 32, ws, &in_k1, s));
+        HIP_TRY(c, launch_rads_gather(buf<float>(c, "rads_pts"), M, in_k1 ? v1 : v0, n1e, points, N, s));
+    }
+    if (grid) {
+        HIP_TRY(c, launch_knn_count(g, points, N, b.cnt, s));
+        HIP_TRY(c, launch_exclusive_scan(b.cnt, nullptr, b.cur, G, b.ws, b.tot, s));
+        HIP_TRY(c, launch_knn_grid(g, points, N, b.cur, b.sorted, b.list, b.cnt + G, log_scale, s));
+    } else if (log_scale) {
+        HIP_TRY(c, launch_knn_brute(points, N, log_scale, s));
     }
     *n_iso = n1e + n2 / 2;
     return DDGS_OK;

@@ -370,11 +370,25 @@ hipError_t launch_exclusive_scan(const uint32_t *in, const uint32_t *gather, uin
 hipError_t radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1, int64_t n_cap,
                             const uint32_t *n_dev, int bits, const SortWs &ws, bool *in_k1, hipStream_t s,
                             const uint32_t *gsrc = nullptr, uint32_t *gdst = nullptr);
-// One stable pass by the keys' top kTopBits bits, values = indices; ws.tot holds
-// the digit totals afterwards (n < 2^21).
-constexpr int kTopBits = 9;
+// One stable pass by the top kTopBits bits of key - (least key), those from the
+// highest in which the keys differ on, so that keys spread over any interval fill
+// the buckets evenly; values = indices.  range [kKeyRangeBlocks]: least and largest
+// key of as many shares of the keys.  kout holds key - (least key) and ws.tot the
+// digit totals afterwards (n < 2^21).
+constexpr int kTopBits = 9, kKeyRangeBlocks = kWave;
+struct TopDigit {
+    uint32_t base;  // least key
+    int shift;      // the digit is (key - base) >> shift
+};
+__device__ __forceinline__ TopDigit top_digit(const uint2 *range)  // (every lane of the wave)
+{
+    const uint2 p = range[threadIdx.x & (kWave - 1)];
+    const uint32_t lo = wave_min(p.x), span = wave_max(p.y) - lo;
+    const int bits = span ? 32 - __clz((int)span) : 0;
+    return TopDigit{lo, bits > kTopBits ? bits - kTopBits : 0};
+}
 hipError_t radix_top_pass(const uint32_t *keys, int64_t n, uint32_t *kout, uint32_t *vout, const SortWs &ws,
-                          hipStream_t s);
+                          const uint2 *range, hipStream_t s);
 // (also clears the n_tiles tile ranges and turns the slot_nb block totals of
 // the slot numbering into the blocks' first slots, in place; cnt_sorted: tile
 // counts in depth order)
@@ -605,14 +619,28 @@ hipError_t launch_iota(uint32_t *p, int64_t n, hipStream_t s);
 hipError_t launch_rads_gather(const float *src, int64_t M, const uint32_t *idx, int64_t n1, float *out, int64_t N,
                               hipStream_t s);
 // The points of the n1 smallest of M <= kPickMax keys in key order (ties by
-// index) out of radix_top_pass' result (ka, va, totals tot); kb, vb: scratch of
-// the same size.  Up to kPickMax random keys a bucket of the top bits stays
-// well below the 1024 that its workgroup orders in LDS.
+// index) out of radix_top_pass' result (ka, va, totals tot, range); kb, vb: scratch
+// of the same size.  Up to kPickMax keys spread evenly over an interval a bucket of
+// the top bits stays well below the 1024 that its workgroup orders in LDS.
 constexpr int64_t kPickMax = (int64_t)1 << 18;
-hipError_t launch_rads_pick(const uint32_t *tot, uint32_t *ka, uint32_t *va, uint32_t *kb, uint32_t *vb, int64_t n1,
+hipError_t launch_rads_pick(const uint32_t *tot, const uint2 *range, uint32_t *ka, uint32_t *va, uint32_t *kb, uint32_t *vb, int64_t n1,
                             const float *src, int64_t M, float *out, int64_t N, hipStream_t s);
-hipError_t launch_rads_draws(const RadsVol &v, const uint64_t *swt, const uint16_t *w16, const uint64_t *draws,
-                             int64_t n2, float *out, int64_t N, int64_t first, hipStream_t s);
+// The n2 draws into out[.][first ..], and what the other launches of a sampling wait
+// for: the range of M keys (range NULL: not asked for) and the words clear[0,
+// n_clear) set to zero (NULL: none).
+struct RadsBegin {
+    const uint64_t *swt;
+    const uint16_t *w16;
+    const uint64_t *draws;
+    int64_t n2, N, first;
+    float *out;
+    const uint32_t *keys;
+    int64_t M;
+    uint2 *range;
+    uint32_t *clear;
+    int64_t n_clear;
+};
+hipError_t launch_rads_begin(const RadsVol &v, const RadsBegin &b, hipStream_t s);
 // Nearest-neighbour scales of pts [3][N] (log_scale ls [3][N]): by brute force,
 // or (knn_uses_grid) through a grid of cells: cnt [cells, cleared] receives
 // the cells' point counts; launch_knn_grid takes their exclusive prefix sums

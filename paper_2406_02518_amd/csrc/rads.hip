@@ -348,18 +348,20 @@ __global__ __launch_bounds__(kRadsBlock) void gather_kernel(const float *src, in
 }
 
 // The n1 smallest of M keys, ties by index, without sorting all of them: a
-// stable pass by the keys' top bits (radix_top_pass) leaves buckets of a few
-// hundred random keys, and one workgroup per bucket orders its own and writes
-// their points; the buckets behind the n1-th key are left alone.  Four launches
-// instead of the fifteen of a whole sort, each of which lasted a launch's few
-// microseconds (126k keys, n1 = 15000: 63 -> 26 us of the card).  In a bucket of up to
-// kPickLds keys an entry's place is the number of smaller ones, counted over
-// the bucket in LDS; a longer one (keys that are not random) is sorted by its
-// workgroup with three stable 8-bit passes through memory.
+// stable pass by the top bits of the keys' range (radix_top_pass) leaves buckets of
+// a few hundred evenly spread keys, and one workgroup per bucket orders its own and
+// writes their points; the buckets behind the n1-th key are left alone.  Five
+// launches instead of the fifteen of a whole sort, each of which lasted a launch's
+// few microseconds (126k keys, n1 = 15000, the call alone: random keys 102 -> 39 us;
+// a permutation, which the 32-bit keys' own top bits left in one bucket, 93 -> 38, by
+// those bits 1033).  In a bucket of up to kPickLds keys an entry's place is the number
+// of smaller ones, counted over the bucket in LDS; a longer one (keys crowded in a
+// part of their range) is sorted by its workgroup with up to three stable 8-bit
+// passes through memory (fourth powers of even ones 255 us, 24th powers 757).
 constexpr int kPickBlock = 512, kPickLds = 1024, kPickWaves = kPickBlock / kWave;
-__global__ __launch_bounds__(kPickBlock) void pick_kernel(const uint32_t *tot, uint32_t *ka, uint32_t *va, uint32_t *kb,
-                                                          uint32_t *vb, int64_t n1, const float *src, int64_t M,
-                                                          float *out, int64_t N)
+__global__ __launch_bounds__(kPickBlock) void pick_kernel(const uint32_t *tot, const uint2 *range, uint32_t *ka,
+                                                          uint32_t *va, uint32_t *kb, uint32_t *vb, int64_t n1,
+                                                          const float *src, int64_t M, float *out, int64_t N)
 {
     static_assert(kPickBlock == 1 << kTopBits, "one thread per bucket total");
     __shared__ __align__(16) uint32_t key[kPickLds];
@@ -418,7 +420,8 @@ __global__ __launch_bounds__(kPickBlock) void pick_kernel(const uint32_t *tot, u
     }
     kb += start;
     vb += start;
-    for (int shift = 0; shift < 24; shift += 8) {
+    const int low_bits = top_digit(range).shift;  // those that the top pass left
+    for (int shift = 0; shift < low_bits; shift += 8) {
         if (tid < 256) cur[tid] = 0u;
         __syncthreads();
         for (int j = tid; j < len; j += kPickBlock) atomicAdd(&cur[(ka[j] >> shift) & 255u], 1u);
@@ -478,16 +481,14 @@ __global__ __launch_bounds__(kPickBlock) void pick_kernel(const uint32_t *tot, u
 // last voxel if none does), one wave per draw: a 64-way search of the
 // segments' running sums, then the segment's words, 16 consecutive ones per
 // lane.
-__global__ __launch_bounds__(kRadsBlock) void draw_kernel(RadsVol v, uint32_t n, const uint64_t *swt, int64_t nseg,
-                                                          const uint16_t *w16, const uint64_t *draws, int64_t n2,
-                                                          float *out, int64_t N, int64_t first)
+__device__ __forceinline__ void draw_voxel(const RadsVol &v, uint32_t n, int64_t nseg, const RadsBegin &a, int64_t j)
 {
+    const uint64_t *const swt = a.swt;
+    const uint16_t *const w16 = a.w16;
     constexpr int PER = kRadsSeg / kWave;
     static_assert(PER == 16, "two 16-byte loads per lane");
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t j = (int64_t)blockIdx.x * (kRadsBlock / kWave) + threadIdx.x / kWave;
-    if (j >= n2) return;
-    const uint64_t r = draws[j];
+    const uint64_t r = a.draws[j];
     uint32_t pick = n - 1u;
     if (r < swt[nseg]) {
         // the segment: the last one whose running sum before it is at most r
@@ -522,10 +523,59 @@ __global__ __launch_bounds__(kRadsBlock) void draw_kernel(RadsVol v, uint32_t n,
     }
     if (lane != 0) return;
     const RadsVoxel c = voxel_of(v, pick);
-    out[first + j] = v.ox + (float)c.x * v.sx;
-    out[N + first + j] = v.oy + (float)c.y * v.sy;
-    out[2 * N + first + j] = v.oz + (float)c.z * v.sz;
+    float *const out = a.out + a.first + j;
+    out[0] = v.ox + (float)c.x * v.sx;
+    out[a.N] = v.oy + (float)c.y * v.sy;
+    out[2 * a.N] = v.oz + (float)c.z * v.sz;
 }
+
+// least and largest of share `b` of the keys (a share past the end: its last key)
+__device__ __forceinline__ void key_range(const RadsBegin &a, int b)
+{
+    __shared__ uint2 red[kRadsBlock / kWave];
+    constexpr int U = 8;  // loads in flight
+    const int64_t per = (a.M + kKeyRangeBlocks - 1) / kKeyRangeBlocks;
+    const int64_t b0 = min(b * per, a.M - 1), b1 = min(b0 + per, a.M);
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+    for (int64_t i = b0 + threadIdx.x; i < b1; i += U * kRadsBlock) {
+        uint32_t x[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) x[q] = a.keys[min(i + q * kRadsBlock, b1 - 1)];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            lo = min(lo, x[q]);
+            hi = max(hi, x[q]);
+        }
+    }
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = make_uint2(lo, hi);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < kRadsBlock / kWave; ++w) {
+        lo = min(lo, red[w].x);
+        hi = max(hi, red[w].y);
+    }
+    a.range[b] = make_uint2(lo, hi);
+}
+
+// One launch for what a sampling begins with: n_range blocks find the keys' range,
+// the next n_clear_blocks clear words, and the rest draw, one wave per draw.
+__global__ __launch_bounds__(kRadsBlock) void begin_kernel(RadsVol v, uint32_t n, int64_t nseg, RadsBegin a, int n_range,
+                                                           int n_clear_blocks)
+{
+    const int b = (int)blockIdx.x - n_range;
+    if (b < 0) {
+        key_range(a, (int)blockIdx.x);
+    } else if (b < n_clear_blocks) {
+        const int64_t j = (int64_t)b * kRadsBlock + threadIdx.x;
+        if (j < a.n_clear) a.clear[j] = 0u;
+    } else {
+        const int64_t j = (int64_t)(b - n_clear_blocks) * (kRadsBlock / kWave) + threadIdx.x / kWave;
+        if (j < a.n2) draw_voxel(v, n, nseg, a, j);
+    }
+}
+
 
 // ---------------------------------------------------- nearest neighbours
 // log sqrt(mean squared distance to the 3 nearest other points), exact.  The
@@ -794,22 +844,23 @@ hipError_t launch_rads_gather(const float *src, int64_t M, const uint32_t *idx, 
     return hipGetLastError();
 }
 
-hipError_t launch_rads_pick(const uint32_t *tot, uint32_t *ka, uint32_t *va, uint32_t *kb, uint32_t *vb, int64_t n1,
-                            const float *src, int64_t M, float *out, int64_t N, hipStream_t s)
+hipError_t launch_rads_pick(const uint32_t *tot, const uint2 *range, uint32_t *ka, uint32_t *va, uint32_t *kb,
+                            uint32_t *vb, int64_t n1, const float *src, int64_t M, float *out, int64_t N, hipStream_t s)
 {
     if (n1 == 0 || M == 0) return hipSuccess;
     if (M > kPickMax) return hipErrorInvalidValue;
-    pick_kernel<<<1 << kTopBits, kPickBlock, 0, s>>>(tot, ka, va, kb, vb, n1, src, M, out, N);
+    pick_kernel<<<1 << kTopBits, kPickBlock, 0, s>>>(tot, range, ka, va, kb, vb, n1, src, M, out, N);
     return hipGetLastError();
 }
 
-hipError_t launch_rads_draws(const RadsVol &v, const uint64_t *swt, const uint16_t *w16, const uint64_t *draws,
-                             int64_t n2, float *out, int64_t N, int64_t first, hipStream_t s)
+hipError_t launch_rads_begin(const RadsVol &v, const RadsBegin &b, hipStream_t s)
 {
-    if (n2 == 0) return hipSuccess;
     const int64_t n = (int64_t)v.nx * v.ny * v.nz;
-    draw_kernel<<<(unsigned)blocks(n2, kRadsBlock / kWave), kRadsBlock, 0, s>>>(v, (uint32_t)n, swt, rads_segments(n),
-                                                                                 w16, draws, n2, out, N, first);
+    if (b.range && b.M <= 0) return hipErrorInvalidValue;
+    const int64_t n_range = b.range ? kKeyRangeBlocks : 0, n_clear = b.clear ? blocks(b.n_clear, kRadsBlock) : 0;
+    const int64_t grid = n_range + n_clear + blocks(b.n2, kRadsBlock / kWave);
+    if (grid == 0) return hipSuccess;
+    begin_kernel<<<(unsigned)grid, kRadsBlock, 0, s>>>(v, (uint32_t)n, rads_segments(n), b, (int)n_range, (int)n_clear);
     return hipGetLastError();
 }
 

@@ -249,10 +249,13 @@ __device__ __forceinline__ int64_t runtime_n(int64_t n_cap, const uint32_t *n_de
     return m < n_cap ? m : n_cap;
 }
 
-// NB: digit values of a pass (256, or 512 where 9-bit digits save a pass)
+// NB: digit values of a pass (256, or 512 where 9-bit digits save a pass).
+// range (or null): the digit is the top one of the keys' range (top_digit), for the
+// count and the scatter alike.
 template <int IPT, int NB>
 __global__ __launch_bounds__(kBlock) void radix_count_kernel(const uint32_t *kin, int64_t n_cap, const uint32_t *n_dev,
-                                                             int shift, uint32_t mask, uint32_t *counts, int nblocks)
+                                                             int shift, uint32_t mask, uint32_t *counts, int nblocks,
+                                                             const uint2 *range)
 {
     constexpr int kRadixTile = kBlock * IPT;
     __shared__ uint32_t h[kWaves][NB];
@@ -268,10 +271,16 @@ __global__ __launch_bounds__(kBlock) void radix_count_kernel(const uint32_t *kin
     uint32_t kk[IPT];
 #pragma unroll
     for (int r = 0; r < IPT; ++r) kk[r] = kin[min(wbase + r * kWave + lane, last)];
+    uint32_t kbase = 0u;
+    if (range) {
+        const TopDigit t = top_digit(range);
+        kbase = t.base;
+        shift = t.shift;
+    }
 #pragma unroll
     for (int r = 0; r < IPT; ++r) {
         const int64_t idx = wbase + r * kWave + lane;
-        if (idx < n) atomicAdd(&h[w][(kk[r] >> shift) & mask], 1u);
+        if (idx < n) atomicAdd(&h[w][((kk[r] - kbase) >> shift) & mask], 1u);
     }
     __syncthreads();
     for (int d = threadIdx.x; d < NB; d += kBlock)
@@ -326,7 +335,8 @@ __global__ __launch_bounds__(kBlock) void radix_scatter_kernel(const uint32_t *k
                                                                uint32_t *kout, uint32_t *vout, int64_t n_cap,
                                                                const uint32_t *n_dev, int shift, int nbits,
                                                                const uint32_t *offsets, const uint32_t *tot,
-                                                               int nblocks, const uint32_t *gsrc, uint32_t *gdst)
+                                                               int nblocks, const uint32_t *gsrc, uint32_t *gdst,
+                                                               const uint2 *range)
 {
     constexpr int kRadixTile = kBlock * IPT;
     constexpr int DPT = NB / kBlock;  // digits per thread in the block-wide steps
@@ -354,6 +364,12 @@ __global__ __launch_bounds__(kBlock) void radix_scatter_kernel(const uint32_t *k
         const int64_t li = min(wbase + r * kWave + lane, n - 1);
         key[r] = kin[li];
         val[r] = vin ? vin[li] : (uint32_t)li;  // (no values: the indices)
+    }
+    if (range) {
+        const TopDigit t = top_digit(range);
+        shift = t.shift;
+#pragma unroll
+        for (int r = 0; r < IPT; ++r) key[r] -= t.base;
     }
 #pragma unroll
     for (int r = 0; r < IPT; ++r) {
@@ -604,10 +620,10 @@ hipError_t radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *
         auto pass = [&](auto ipt_c, auto nb_c) {
             constexpr int IPT = decltype(ipt_c)::value, NB = decltype(nb_c)::value;
             radix_count_kernel<IPT, NB><<<(unsigned)nblocks, kBlock, 0, s>>>(ka, n_cap, n_dev, shift, mask,
-                                                                            ws.counts, (int)nblocks);
+                                                                            ws.counts, (int)nblocks, nullptr);
             radix_prefix_kernel<<<NB, kBlock, 0, s>>>(ws.counts, (int)nblocks, ws.tot);
             radix_scatter_kernel<IPT, NB><<<(unsigned)nblocks, kBlock, 0, s>>>(
-                ka, va, kb, vb, n_cap, n_dev, shift, nbits, ws.counts, ws.tot, (int)nblocks, gs, gd);
+                ka, va, kb, vb, n_cap, n_dev, shift, nbits, ws.counts, ws.tot, (int)nblocks, gs, gd, nullptr);
         };
         using Small = std::integral_constant<int, kRadixIPTSmall>;
         using Large = std::integral_constant<int, kRadixIPTLarge>;
@@ -629,18 +645,19 @@ hipError_t radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *
 }
 
 hipError_t radix_top_pass(const uint32_t *keys, int64_t n, uint32_t *kout, uint32_t *vout, const SortWs &ws,
-                          hipStream_t s)
+                          const uint2 *range, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    if (!ws.counts || !ws.tot || sort_counts_words(n) > ws.counts_words || n >= kRadixSmallN) return hipErrorInvalidValue;
+    if (!ws.counts || !ws.tot || sort_counts_words(n) > ws.counts_words || n >= kRadixSmallN || !range)
+        return hipErrorInvalidValue;
     constexpr int NB = 1 << kTopBits;
     static_assert(NB <= kRadixMaxDigits, "digit totals");
     const int nblocks = (int)blocks_for(n, (int64_t)kBlock * kRadixIPTSmall);
-    radix_count_kernel<kRadixIPTSmall, NB><<<(unsigned)nblocks, kBlock, 0, s>>>(keys, n, nullptr, 32 - kTopBits, NB - 1u,
-                                                                               ws.counts, nblocks);
+    radix_count_kernel<kRadixIPTSmall, NB><<<(unsigned)nblocks, kBlock, 0, s>>>(keys, n, nullptr, 0, NB - 1u, ws.counts,
+                                                                               nblocks, range);
     radix_prefix_kernel<<<NB, kBlock, 0, s>>>(ws.counts, nblocks, ws.tot);
     radix_scatter_kernel<kRadixIPTSmall, NB><<<(unsigned)nblocks, kBlock, 0, s>>>(
-        keys, nullptr, kout, vout, n, nullptr, 32 - kTopBits, kTopBits, ws.counts, ws.tot, nblocks, nullptr, nullptr);
+        keys, nullptr, kout, vout, n, nullptr, 0, kTopBits, ws.counts, ws.tot, nblocks, nullptr, nullptr, range);
     return hipGetLastError();
 }
 
