@@ -785,6 +785,13 @@ __global__ __launch_bounds__(TW *TH) void raster_bwd_kernel(RasterArgs a)
 // general kernel above took 475 us at 16 x 16, a former one with a division
 // per entry and v_mfma_f32_16x16x4 for 8 x 8 tiles 189 us.  Bound by VALU
 // issue.
+//
+// Rounding, against 64 bits (2000 Gaussians / 64^2, geometric means of 32 models,
+// relative L2 in 1e-6; the kernels before / this one).  16 x 16: opacity 1.02 /
+// 1.05, mean 1.47 / 1.49, scale 1.35 / 1.38, rotation 1.88 / 1.90, pose 1.49 /
+// 1.34; 8 x 8: 1.03 / 1.05, 1.52 / 1.49, 1.61 / 1.38, 2.12 / 1.90, 1.43 / 1.40.  So up
+// to 3 % more in some groups, most of it the recurrence's, the rest the shift of
+// the moments to the mean.
 template <int TW, int TH>
 __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TW * TH == 64 ? 5 : 4))) void raster_bwd_parts_kernel(RasterArgs a)
 {
