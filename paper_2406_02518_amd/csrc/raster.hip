@@ -159,8 +159,9 @@ __device__ __forceinline__ float2 cutoff_box(float kw, float A00, float A01, flo
 {
     const float p = A00 * A11;
     const float det = __fmaf_rn(-A01, A01, p) - 3e-6f * p;
-    const float idet = det > 1e-30f ? 1.0f / det : INFINITY;
-    return make_float2(kw * sqrtf(A11 * idet), kw * sqrtf(A00 * idet));
+    // (v_rcp_f32 and v_sqrt_f32 are one ulp off, which the 0.1 % covers)
+    const float idet = det > 1e-30f ? __builtin_amdgcn_rcpf(det) : INFINITY;
+    return make_float2(kw * __builtin_amdgcn_sqrtf(A11 * idet), kw * __builtin_amdgcn_sqrtf(A00 * idet));
 }
 // the interval [x - h, x + h] reaches [lo, hi]
 __device__ __forceinline__ bool box_reaches(float x, float h, float lo, float hi)
