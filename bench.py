@@ -31,23 +31,27 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 #   forward  : offset 2, quadratic form d2 5 (3 multiplies, 2 fused), cut-off
 #              compare 1, exp 1, alpha G 1, min with sigma_max 1, T s 1,
 #              colour fma 1, 1 - s 1, T (1 - s) 1                         = 16
-#   backward : the forward's transmittance recomputation 15 (everything but
-#              the colour), tail update 1, dL/ds = g (c T - S / (1 - s)) 4
-#              (reciprocal, multiply, fused, multiply), clamp subgradient
-#              select 1, q = dL/ds G 1, dL/dc = g T s 1, the moments q dx,
-#              q dy, q dx^2, q dx dy, q dy^2 5, and the reduction of the 7
-#              gradient terms over the tile's pixels 7                    = 34
-# Peak: 256 CU x 64 lanes x 2.4 GHz = 39.3 T lane-op/s (one non-packed
-# VALU instruction per lane per cycle; packed FP32 is disabled).
+#   backward : offset 2, quadratic form 5, cut-off compare 1, exp 1, alpha G
+#              1, min with sigma_max 1, 1 - s 1, r = g T G 1, g s T 1, g T
+#              (1 - s) 1, tail fma 1; from the colour B seen behind the step
+#              c - B 1, B's own step 1 and q = dL/ds G = r (c - B) 1 (the
+#              division that starts B, one per eight steps, is left out);
+#              clamp subgradient select 1, the moments q dx, q dy, q dx^2,
+#              q dx dy, q dy^2 5, and the reduction of the 7 gradient terms
+#              over the tile's pixels 7                                   = 32
+# Peak: 256 CU x 128 lanes x 2.4 GHz = 78.6 T lane-op/s, half of the published
+# FP32 vector rate in flops.  (Packed FP32 is disabled; plain operations of one
+# wave were measured at 2.4 to 2.7 cycles per SIMD, close to the two that rate
+# takes.)
 LANE_OPS_FWD = 16
-LANE_OPS_BWD = 34
-PEAK_LANE_OPS = 39.3   # T lane-op/s
+LANE_OPS_BWD = 32
+PEAK_LANE_OPS = 78.6   # T lane-op/s
 # The same work counted in floating-point operations with a fused multiply-add
-# as 2 (forward 19, backward 52), against 78.6 TFLOP/s (256 CU x 4 SIMD x 16
-# lanes x 2 x 2.4 GHz, no packed FP32): the FMA-weighted view of one roofline.
+# as 2 (forward 19, backward 52), against the published 157.3 TFLOP/s (256 CU x
+# 4 SIMD x 32 lanes x 2 x 2.4 GHz): the FMA-weighted view of one roofline.
 FLOPS_FWD = 19
 FLOPS_BWD = 52
-PEAK_ALU_TFLOPS = 78.6
+PEAK_ALU_TFLOPS = 157.3
 PEAK_HBM_GBS = 8000.0
 
 
@@ -138,8 +142,9 @@ def traffic_from_profiles(kernel, workload):
 
 
 def valu_from_profiles(kernel, workload):
-    """VALU instructions per launch and the issue fraction from the committed
-    SQ counter summary, valid only while the kernel sources are unchanged."""
+    """VALU instructions per launch and the issue fraction (of two per CU and
+    cycle, the rate behind PEAK_LANE_OPS) from the committed SQ counter summary,
+    valid only while the kernel sources are unchanged."""
     path = os.path.join(ROOT, "profiles", f"valu_raster_{workload}.json")
     if not os.path.exists(path):
         return None
@@ -151,7 +156,7 @@ def valu_from_profiles(kernel, workload):
         if src.hexdigest() != d["sources_sha256"]:
             return None
         k = d["kernels"][kernel]
-        return {"valu_insts_per_launch": int(k["valu_insts"]), "issue_frac": round(k["valu_issue_frac"], 3)}
+        return {"valu_insts_per_launch": int(k["valu_insts"]), "issue_frac": round(k["valu_per_cu_cycle"] / 2.0, 3)}
     except Exception:  # noqa: BLE001 - a stale or unreadable summary means "not measured"
         return None
 
