@@ -1969,6 +1969,9 @@ ddgs_status ddgs_step_launch(ddgs_ctx *c)
     HIP_TRY(c, hipGraphLaunch(c->exec, c->stream));
     c->M = -1;  // unknown until ddgs_check
     c->total_pending = false;
+    // (the grid of a plain backward: a plain render since the capture may have had
+    // fewer work items)
+    c->max_items = (int)max_items_for(c, c->step_cap);
     c->rendered = true;
     c->r_model_gen = c->model_gen;
     c->r_views_gen = c->views_gen;

@@ -260,3 +260,39 @@ def test_num_rendered_after_a_change_of_stream():
         assert r.num_rendered() == exp
     finally:
         r.close()
+
+
+def test_backward_of_a_replay_after_a_smaller_plain_render():
+    """A plain render of fewer entries between the capture and a replay: a plain
+    backward behind the replay still covers all of the replay's work items."""
+    sc, near = _scene(9000), _view(10.0, 60, 52)
+    pose = near.pose.copy()
+    pose[0, 3] += 60.0  # most of the model beside the detector
+    aside = synth.view(60, 52, 0.9, 1000.0, 600.0, 10.0, pose=pose)
+    wt = torch.cos(torch.arange(60 * 52, device="cuda", dtype=torch.float32))  # (not the step's own)
+    r = _renderer()
+    try:
+        r.set_options(split=16)
+        r.set_scene(sc)
+        r.set_views([near])
+        r.render()
+        need = r.num_rendered()
+        exp = {k: v.clone() for k, v in r.backward(wt).items()}
+        torch.cuda.synchronize()
+        s = _capture(r, 0)
+        r.set_views([aside])
+        r.render()
+        assert r.num_rendered() < need // 2
+        r.set_views([near])
+        torch.cuda.synchronize()
+        binding.ddgs_step_launch(r.ctx)
+        assert r.check_step() == 0 and s["img"].any()
+        for g in s["grads"].values():
+            g.zero_()
+        torch.cuda.synchronize()
+        got = r.backward(wt)
+        torch.cuda.synchronize()
+        for k in exp:
+            assert torch.equal(got[k], exp[k]), k
+    finally:
+        r.close()
